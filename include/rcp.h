@@ -115,16 +115,21 @@ typedef struct {
  *     wave-cooperative pair search of the list build (the 64 lanes of a
  *     wave test the flattened candidates of all their cells together; the
  *     same pairs are listed); bit 7 = each update writes the whole 32-byte
- *     position record (x, y, z, D0) instead of the three coordinates;
+ *     position record (x, y, z, D0) instead of the three coordinates.  With
+ *     none of bits 0-5 and no fused_tail, and on packings with walls, frozen
+ *     spheres or two dimensions whatever they are, every wave takes a work
+ *     item on its own, one partner entry per lane;
  *   time_kernels: 0 = no timing; 1 = HIP events around the gradient + Adam
  *     and tail launches of the middle iteration (graph_iters / 2) of every
  *     batch of graph_iters (a uniform sample of one launch in graph_iters;
  *     event nodes cost a few microseconds each); 2 = around every launch
  *     (rcp_stats.kernel_ms and friends);
  *   row_cost, item_work: the rows of a packing (in list order) are cut into
- *     work items of item_work units, a row costing row_cost units plus one
- *     per listed partner, so each 256-thread block gets about the same
- *     gather work whether its rows are small spheres or large ones; 1 <=
+ *     work items of item_work / 6 units, a row costing 2/3 row_cost units
+ *     (rounded up) plus one per listed partner, so each wave of 64 (four to a
+ *     block) gets about the same gather work whether its rows are small
+ *     spheres or large ones; the kernels that variant bits 0-5 and fused_tail
+ *     select take a block's four items as one; 1 <=
  *     row_cost <= 65536 and 1 <= item_work <= R * row_cost, R = 512 with
  *     variant bit 5 and 256 otherwise (an item then never holds more than R
  *     rows). */
@@ -213,7 +218,7 @@ int rcp_version(void);
 const char *rcp_last_error(void);
 void rcp_params_default(rcp_params *p);
 /* Defaults: graph_iters 32, xcd_remap 1, fused_tail 0, variant 192 (the
- * cooperative pair search, the two-gather gradient + Adam kernel writing
+ * cooperative pair search, the wave-per-item gradient + Adam kernel writing
  * whole records), row_cost 6, item_work 1536, time_kernels 0. */
 void rcp_tuning_default(rcp_tuning *t);
 

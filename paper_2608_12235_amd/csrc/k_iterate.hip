@@ -161,19 +161,23 @@ __device__ __forceinline__ void pair_term(Acc &a, const P4 &qi, const P4 &qj, do
 
 // Adam on one coordinate (Kingma and Ba, bias corrected; ib1 = 1 / (1 -
 // beta1^t), ib2 = 1 / (1 - beta2^t)), then wrapped into [0, L) (L = 0 on an
-// axis bounded by walls leaves the coordinate as it is).
+// axis bounded by walls leaves the coordinate as it is).  The fused products
+// are written out, so that every kernel rounds a packing's step alike.
 __device__ __forceinline__ double adam_coord(double th, double g, double &m, double &v,
                                              double b1, double b2, double ib1, double ib2,
                                              double eta, double eps, double L)
 {
-    m = b1 * m + (1.0 - b1) * g;
-    v = b2 * v + (1.0 - b2) * (g * g);
+#pragma clang fp contract(off)
+    m = fma(1.0 - b1, g, b1 * m);
+    v = fma(1.0 - b2, g * g, b2 * v);
     const double mh = m * ib1, vh = v * ib2;
-    // sqrt(vh) as vh / sqrt(vh); below 1e-200 (where the estimate loses
-    // range, a rarely taken branch) the IEEE root
-    double sv = vh * fast_rsq(fmax(vh, 1e-200));
-    if (vh < 1e-200) sv = sqrt(vh);
-    double t = th - (eta * mh) * fast_rcp(sv + eps);
+    // sqrt(vh) as vh / sqrt(vh); below 1e-200, where the estimate loses range
+    // (0 among them: a sphere without contacts), of 2^600 vh
+    const bool tiny = vh < 1e-200;
+    const double vs = tiny ? vh * 0x1p600 : vh;
+    const double y = vs * fast_rsq(fmax(vs, 1e-300));
+    const double sv = tiny ? y * 0x1p-300 : y;
+    double t = fma(-(eta * mh), fast_rcp(sv + eps), th);
     if (t < 0.0) t += L;
     if (t >= L) t -= L;
     return t;
@@ -196,6 +200,7 @@ struct IterPtrs {
     double *m0, *m1, *m2, *v0, *v1, *v2;
     const float *r0, *r1, *r2;
     const int32_t *rp, *col;
+    const uint8_t *rlo;
 };
 
 __device__ __forceinline__ IterPtrs select_ptrs(const SegPtrs *__restrict__ P, int seg, int cur)
@@ -215,6 +220,7 @@ __device__ __forceinline__ IterPtrs select_ptrs(const SegPtrs *__restrict__ P, i
     p.r2 = s.xref[2];
     p.rp = s.rp;
     p.col = s.col;
+    p.rlo = s.rlo;
     return p;
 }
 
@@ -509,7 +515,7 @@ struct ColSrc {
 // their gathers are in flight together (kU = 2 or 4); the next step's
 // partner indices are requested before this step's terms are evaluated, so
 // their latency hides behind the arithmetic.
-template <int kU, bool kStage, bool kMixed = false, int kDim = 3>
+template <int kU, bool kStage>
 __device__ __forceinline__ void segment_terms(Acc &a, const ColSrc<kStage> &cols,
                                               const P4 *__restrict__ Q, int32_t q, int32_t qe,
                                               const P4 &qi, const IterScalars &c)
@@ -528,10 +534,10 @@ __device__ __forceinline__ void segment_terms(Acc &a, const ColSrc<kStage> &cols
                 j2 = cols.at(q + 2);
                 j3 = cols.at(q + 3);
             }
-            pair_term<false, kMixed, kDim>(a, qi, q0, c.kappa, c.L, c.iLa);
-            pair_term<false, kMixed, kDim>(a, qi, q1, c.kappa, c.L, c.iLa);
-            pair_term<false, kMixed, kDim>(a, qi, q2, c.kappa, c.L, c.iLa);
-            pair_term<false, kMixed, kDim>(a, qi, q3, c.kappa, c.L, c.iLa);
+            pair_term<false>(a, qi, q0, c.kappa, c.L, c.iLa);
+            pair_term<false>(a, qi, q1, c.kappa, c.L, c.iLa);
+            pair_term<false>(a, qi, q2, c.kappa, c.L, c.iLa);
+            pair_term<false>(a, qi, q3, c.kappa, c.L, c.iLa);
             if (!more) break;
         }
     }
@@ -545,8 +551,8 @@ __device__ __forceinline__ void segment_terms(Acc &a, const ColSrc<kStage> &cols
                 j0 = cols.at(q);
                 j1 = cols.at(q + 1);
             }
-            pair_term<false, kMixed, kDim>(a, qi, q0, c.kappa, c.L, c.iLa);
-            pair_term<false, kMixed, kDim>(a, qi, q1, c.kappa, c.L, c.iLa);
+            pair_term<false>(a, qi, q0, c.kappa, c.L, c.iLa);
+            pair_term<false>(a, qi, q1, c.kappa, c.L, c.iLa);
             if (!more) break;
         }
     }
@@ -554,11 +560,11 @@ __device__ __forceinline__ void segment_terms(Acc &a, const ColSrc<kStage> &cols
         const int32_t j0 = cols.at(q),
                       j1 = cols.at(q + 1);
         const P4 q0 = load_p4(Q, j0), q1 = load_p4(Q, j1);
-        pair_term<false, kMixed, kDim>(a, qi, q0, c.kappa, c.L, c.iLa);
-        pair_term<false, kMixed, kDim>(a, qi, q1, c.kappa, c.L, c.iLa);
+        pair_term<false>(a, qi, q0, c.kappa, c.L, c.iLa);
+        pair_term<false>(a, qi, q1, c.kappa, c.L, c.iLa);
     }
     if (q < qe)
-        pair_term<false, kMixed, kDim>(a, qi, load_p4(Q, cols.at(q)), c.kappa, c.L, c.iLa);
+        pair_term<false>(a, qi, load_p4(Q, cols.at(q)), c.kappa, c.L, c.iLa);
 }
 
 template <int kN>
@@ -584,6 +590,50 @@ struct NoHook {
     __device__ void operator()() const {}
 };
 
+// The item's partial sums (energy, kappa gradient, largest overlap, largest
+// displacement) from the threads' shares, to *out by thread 0; every thread
+// of the block must call it.
+template <bool kCoherentOut>
+__device__ __forceinline__ void block_partial(const Acc &a, double disp,
+                                              double (&red)[kWavesPerBlock][4], Part4 *out)
+{
+    const int t = threadIdx.x, lane = t & (kWave - 1), wv = t / kWave;
+    const double be = wave_sum_dpp(a.e);
+    const double bs = wave_sum_dpp(a.s);
+    const double bm = wave_max_dpp(a.m);
+    const double bd = wave_max_dpp(disp);
+    if (lane == 0) {
+        red[wv][0] = be;
+        red[wv][1] = bs;
+        red[wv][2] = bm;
+        red[wv][3] = bd;
+    }
+    __syncthreads();
+    if (t == 0) {
+        // (in pairs: half the chain of dependent additions)
+        static_assert(kWavesPerBlock == 4, "sums of four waves");
+        const double e = (red[0][0] + red[1][0]) + (red[2][0] + red[3][0]);
+        const double sd = (red[0][1] + red[1][1]) + (red[2][1] + red[3][1]);
+        const double m = fmax(fmax(red[0][2], red[1][2]), fmax(red[2][2], red[3][2]));
+        const double d = fmax(fmax(red[0][3], red[1][3]), fmax(red[2][3], red[3][3]));
+        if (kCoherentOut) {
+            // agent-scope stores reach the device's coherence point: the
+            // tail may run on another XCD
+            __hip_atomic_store(&out->e, e, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            __hip_atomic_store(&out->s, sd, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            __hip_atomic_store(&out->m, m, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            __hip_atomic_store(&out->d, d, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        } else {
+            Part4 o;
+            o.e = e;
+            o.s = sd;
+            o.m = m;
+            o.d = d;
+            *out = o;
+        }
+    }
+}
+
 // One work item: up to kR (256 or 512) consecutive rows [r0, r0 + nrow) of
 // one packing; rp_own[k] = rp[r0 + t + 256 k] for the rows this thread owns
 // and rp_end = rp[r0 + nrow] are given.
@@ -596,8 +646,7 @@ struct NoHook {
 // timing.  Phase 2: one thread per row applies Adam (coalesced).  hook() runs
 // between the phases (the persistent kernel prefetches there).  Thread 0
 // writes the item's partial sums to *out.  Every thread must call it.
-template <int kU, bool kEarly, bool kStage, int kR, class Hook, bool kCoherentOut = false,
-          bool kMixed = false, bool kWalls = false, int kDim = 3>
+template <int kU, bool kEarly, bool kStage, int kR, class Hook, bool kCoherentOut = false>
 __device__ __forceinline__ void item_body(const IterPtrs &p, const IterScalars &c, int64_t r0,
                                           int nrow, int32_t e0, int32_t e1,
                                           const int32_t *rp_own, int32_t rp_end,
@@ -623,7 +672,7 @@ __device__ __forceinline__ void item_body(const IterPtrs &p, const IterScalars &
     Pre pre = {0, 0, 0, 0, 0, 0, 0.f, 0.f, 0.f};
     if (kEarly && t < nrow) {
         oq = load_p4(Q, (int32_t)(r0 + t));
-        pre = preload<kDim>(p, r0 + t);
+        pre = preload(p, r0 + t);
     }
 #pragma unroll
     for (int k = 0; k < kOwn; ++k)
@@ -660,7 +709,7 @@ __device__ __forceinline__ void item_body(const IterPtrs &p, const IterScalars &
             const P4 qi = load_p4(Q, (int32_t)(r0 + r));
             const int32_t rend = L.srp[r + 1], qe = min(rend, ce);
             a.gx = a.gy = a.gz = 0.0;
-            segment_terms<kU, kStage, kMixed, kDim>(a, cols, Q, q, qe, qi, c);
+            segment_terms<kU, kStage>(a, cols, Q, q, qe, qi, c);
             const bool began_before = L.srp[r] < cs, goes_on = rend > ce;
             if (began_before) store3<kBlock>(L.A, t, a);
             else if (goes_on) store3<kBlock>(L.B, t, a);
@@ -683,7 +732,7 @@ __device__ __forceinline__ void item_body(const IterPtrs &p, const IterScalars &
         const int64_t io = r0 + row;
         if (!kEarly) {
             oq = load_p4(Q, (int32_t)io);
-            pre = preload<kDim>(p, io);
+            pre = preload(p, io);
         }
         const int32_t qb = L.srp[row], qe = L.srp[row + 1];
         double g[3] = {0, 0, 0};
@@ -702,57 +751,9 @@ __device__ __forceinline__ void item_body(const IterPtrs &p, const IterScalars &
                 }
             }
         }
-        if (kWalls) {
-            // the row's wall terms (a sphere against the walls, in full)
-            WallAcc w = {{0.0, 0.0, 0.0}, 0.0, 0.0, 0.0, 0.0};
-            const double px[3] = {oq.x, oq.y, oq.z};
-            wall_terms(px, c.kappa * oq.d, c.L, c.walls, c.round, w);
-#pragma unroll
-            for (int d = 0; d < 3; ++d) g[d] += w.g[d];
-            a.e += w.e;
-            a.s += w.s;
-            a.m = fmax(a.m, w.m);
-        }
-        bd = fmax(bd, update_particle<kMixed, kDim>(p, c, io, oq, pre, g[0], g[1], g[2], full));
+        bd = fmax(bd, update_particle(p, c, io, oq, pre, g[0], g[1], g[2], full));
     }
-    // block reduction of the four partials
-    const int lane = t & (kWave - 1);
-    const double be = wave_sum_dpp(a.e);
-    const double bs = wave_sum_dpp(a.s);
-    const double bm = wave_max_dpp(a.m);
-    bd = wave_max_dpp(bd);
-    const int wv = t / kWave;
-    if (lane == 0) {
-        L.red[wv][0] = be;
-        L.red[wv][1] = bs;
-        L.red[wv][2] = bm;
-        L.red[wv][3] = bd;
-    }
-    __syncthreads();
-    if (t == 0) {
-        double e = 0, sd = 0, m = 0, d = 0;
-        for (int k = 0; k < kWavesPerBlock; ++k) {
-            e += L.red[k][0];
-            sd += L.red[k][1];
-            m = fmax(m, L.red[k][2]);
-            d = fmax(d, L.red[k][3]);
-        }
-        if (kCoherentOut) {
-            // agent-scope stores reach the device's coherence point: the
-            // tail may run on another XCD
-            __hip_atomic_store(&out->e, e, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            __hip_atomic_store(&out->s, sd, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            __hip_atomic_store(&out->m, m, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            __hip_atomic_store(&out->d, d, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        } else {
-            Part4 o;
-            o.e = e;
-            o.s = sd;
-            o.m = m;
-            o.d = d;
-            *out = o;
-        }
-    }
+    block_partial<kCoherentOut>(a, bd, L.red, out);
 }
 
 template <bool kWalls = false>
@@ -779,21 +780,31 @@ __device__ __forceinline__ void load_scalars(const SegState *s, IterScalars &c)
     c.round = kWalls ? s->round : 0;
 }
 
+// The work item of a block of the other kernels: the rows of its
+// kWavesPerBlock consecutive items.
+__device__ __forceinline__ WorkItem block_item(const WorkItem *__restrict__ W, int64_t b)
+{
+    WorkItem w = W[b * kWavesPerBlock];
+    const WorkItem z = W[b * kWavesPerBlock + kWavesPerBlock - 1];
+    w.e1 = z.e1;
+    w.end = z.end;
+    return w;
+}
+
 // One block per work item; kWaves > 1 asks the compiler for that many
 // waves per SIMD (fewer registers, a little spilling).
-template <bool kFusedTail, int kU, bool kEarly, bool kStage, int kWaves, bool kMixed = false,
-          bool kWalls = false, int kDim = 3>
+template <bool kFusedTail, int kU, bool kEarly, bool kStage, int kWaves>
 __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(kWaves))) void k_iterate(const SegPtrs *__restrict__ P,
                                                    SegState *__restrict__ S,
                                                    const WorkItem *__restrict__ W,
                                                    double *__restrict__ partials, int flags)
 {
     const int b = (flags & 1) ? remap_block((int)blockIdx.x, (int)gridDim.x) : (int)blockIdx.x;
-    const WorkItem w = W[b];
+    const WorkItem w = block_item(W, b);
     SegState *s = S + w.seg;
     if (s->flags & F_IDLE) return;
     IterScalars c;
-    load_scalars<kWalls>(s, c);
+    load_scalars(s, c);
     const IterPtrs p = select_ptrs(P, w.seg, s->cur);
     __shared__ ItemLds L;
     __shared__ int32_t scol[kStage ? kColStage : 1];
@@ -802,7 +813,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(kWaves))
     const int nrow = (int)(w.end - w.begin);
     const int32_t rp_t = t < nrow ? gload(p.rp, r0 + t) : 0;
     const int32_t rp_end = gload(p.rp, r0 + nrow);
-    item_body<kU, kEarly, kStage, kBlock, NoHook, kFusedTail, kMixed, kWalls, kDim>(
+    item_body<kU, kEarly, kStage, kBlock, NoHook, kFusedTail>(
         p, c, r0, nrow, w.e0, w.e1, &rp_t, rp_end, L, scol,
         reinterpret_cast<Part4 *>(partials) + b, NoHook(), (flags & 4) != 0);
     if (kFusedTail) {
@@ -827,6 +838,192 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(kWaves))
     }
 }
 
+// ------------------------------------------------------ a wave per item
+// The default gradient + Adam kernel: each wave takes one work item (at most
+// 64 rows) on its own, without a barrier between its phases.  The item's
+// partner entries are taken in rounds of 64, one per lane: coalesced partner
+// indices and one pair term per lane, with the next round's gathers and the
+// indices of the one after it in flight.  An entry's own row comes from the
+// list (its low eight bits) and that row's record from LDS.  The terms of
+// the gradient go to LDS and are added per row, by one lane in entry order,
+// or where the item has few rows by the 2, 4, ... 64 lanes it has per row
+// and then across them, always in the same order: the sum does not depend
+// on timing.  One lane per row then applies Adam (coalesced).
+//
+// What bounds it: on 1e6 spheres (2.3 partners a row, 189 MB a launch by the
+// 176 + 4 (1 + partners) bytes a row count) memory, 42.2 us or 4.5 TB/s
+// where a plain copy of that size runs at 5.2; below about 1e5 spheres the
+// wave's chain of dependent steps (item, indices, gathers, pair term, row
+// sums, moments).  The block-per-item form (k_iterate above: equal chunks of
+// entries per thread, found by bisection, two barriers a block) takes 46.9
+// us there and, on the same states, 136 against 126 us on 3e6 spheres of
+// size ratio 5e5, 17.8 against 13.8 us on 1e5 spheres with 5.2 partners,
+// 15.5 against 9.2 us on 8784 with rows up to 284, 15.3 against 10.3 us on
+// 1e5 disks.  Registers matter: at 75 (six waves per SIMD) 128 us on 3e6
+// spheres, at 62-70 (seven) 122-126; loading the moments before the
+// partner loop (+15 registers) takes 47 us on 1e6.
+struct WaveLds {
+    P4 own[kWave];
+    double F[3][kWave];
+    double G[3][kWave];
+    int32_t srp[kWave + 4];
+};
+struct ItemsLds {
+    WaveLds w[kWavesPerBlock];
+    double red[kWavesPerBlock][4];
+};
+
+// Sum of v over the groups of 2^sh lanes (sh uniform), in every lane of the
+// group.
+__device__ __forceinline__ double group_sum(double v, int sh)
+{
+    if (sh > 0) v += dpp_f64<0xb1>(0.0, v);    // quad_perm [1, 0, 3, 2]
+    if (sh > 1) v += dpp_f64<0x4e>(0.0, v);    // quad_perm [2, 3, 0, 1]
+    if (sh > 2) v += dpp_f64<0x141>(0.0, v);   // row_half_mirror
+    if (sh > 3) v += dpp_f64<0x140>(0.0, v);   // row_mirror
+    if (sh > 4) v += __shfl_xor(v, 16, kWave);
+    if (sh > 5) v += __shfl_xor(v, 32, kWave);
+    return v;
+}
+
+// A block one of whose items has more entries than this takes its items one
+// after the other with all four waves, each wave every fourth round: rows are
+// not cut, so an item grows past its share (256 units by default) only by
+// one long row, and a wave alone would take it at about 2 us per round of
+// 64 (on 1.2e5 spheres around frozen ones, rows of up to 2006: 48 us with
+// the split, 72 us without; with the limit at 256 dense lists' ordinary
+// items split too: 22 against 15 us on 1e5 spheres).
+constexpr int kSplit = 512;
+
+template <bool kMixed, bool kWalls, int kDim>
+__global__ __launch_bounds__(kBlock) void
+k_iterate_wave(const SegPtrs *__restrict__ P, SegState *__restrict__ S,
+               const WorkItem *__restrict__ W, double *__restrict__ partials, int flags)
+{
+    __shared__ ItemsLds L;
+    const int b = (flags & 1) ? remap_block((int)blockIdx.x, (int)gridDim.x) : (int)blockIdx.x;
+    const int lane = threadIdx.x & (kWave - 1);
+    const int wv = __builtin_amdgcn_readfirstlane((int)threadIdx.x / kWave);
+    const WorkItem *WB = W + (int64_t)b * kWavesPerBlock;
+    // the same packing for every item of a block (0 when there is only one:
+    // its record is then read alongside the items, not after them)
+    const int seg = (flags & 8) ? 0 : WB->seg;
+    SegState *s = S + seg;
+    const bool idle = (s->flags & F_IDLE) != 0;
+    IterScalars c;
+    load_scalars<kWalls>(s, c);
+    const IterPtrs p = select_ptrs(P, seg, s->cur);
+    bool split = false;
+#pragma unroll
+    for (int i = 0; i < kWavesPerBlock; ++i) split = split || WB[i].e1 - WB[i].e0 > kSplit;
+    if (idle) return;
+    Acc a = {0, 0, 0, 0, 0, 0, 0};   // e, s, m: this lane's totals
+    double g[3];
+    const int first = split ? wv : 0, step = split ? kWavesPerBlock : 1;
+    WaveLds &M = L.w[wv];
+    __builtin_amdgcn_s_setprio(2);
+#pragma unroll 1
+    for (int i = split ? 0 : wv;;) {
+        const WorkItem w = WB[i];
+        const int nrow = (int)(w.end - w.begin);
+        const int32_t ne = w.e1 - w.e0;
+        g[0] = g[1] = g[2] = 0.0;    // this lane's part of its row's gradient
+        // lanes per row: 2^sh, the most that give every row its lanes
+        const int sh = nrow > 1 ? __builtin_clz((unsigned)(nrow - 1)) - 26 : 6;
+        if (ne > 0) {
+            // This lane's entries: j1, r1 of the next round, q0, r0 (record,
+            // row) of the round at hand.  Past the item's end its last
+            // entry and row are read again, so that no load needs a branch.
+            const int32_t el = ne - 1;
+            const int32_t *col = p.col + w.e0;
+            const uint8_t *rlo = p.rlo + w.e0;
+            const int32_t k0 = first * kWave + lane, kst = step * kWave;
+            const int32_t j0 = gload(col, min(k0, el));
+            uint32_t r0 = gload(rlo, min(k0, el));
+            int32_t j1 = gload(col, min(k0 + kst, el));
+            uint32_t r1 = gload(rlo, min(k0 + kst, el));
+            const int64_t ro = w.begin + min(lane, nrow - 1);
+            const P4 oq = load_p4(p.q, (int32_t)ro);
+            const int32_t rpt = gload(p.rp, ro) - w.e0;
+            P4 q0 = load_p4(p.q, j0);
+            M.own[lane] = oq;
+            M.srp[lane] = lane < nrow ? rpt : ne;
+            if (lane == 0) M.srp[kWave] = ne;
+            __builtin_amdgcn_wave_barrier();
+            const int row = lane >> sh, sub = lane & ((1 << sh) - 1);
+            const int32_t rb = M.srp[row], re = M.srp[row + 1];
+            for (int32_t base = first * kWave; base < ne; base += kst) {
+                const uint32_t own = (r0 - (uint32_t)w.begin) & (kWave - 1);
+                const P4 q1 = load_p4(p.q, j1);
+                r0 = r1;
+                j1 = gload(col, min(base + 2 * kst + lane, el));
+                r1 = gload(rlo, min(base + 2 * kst + lane, el));
+                if (base + lane < ne) {
+                    a.gx = a.gy = a.gz = 0.0;
+                    pair_term<false, kMixed, kDim>(a, M.own[own], q0, c.kappa, c.L, c.iLa);
+                    M.F[0][lane] = a.gx;
+                    M.F[1][lane] = a.gy;
+                    if (kDim == 3) M.F[2][lane] = a.gz;
+                }
+                __builtin_amdgcn_wave_barrier();
+                const int32_t hi = min(re - base, kWave);
+                for (int32_t k = max(rb - base, 0) + sub; k < hi; k += 1 << sh) {
+                    g[0] += M.F[0][k];
+                    g[1] += M.F[1][k];
+                    if (kDim == 3) g[2] += M.F[2][k];
+                }
+                __builtin_amdgcn_wave_barrier();
+                q0 = q1;
+            }
+            if (sh > 0) {
+                // across the row's lanes, then to lane `row`
+#pragma unroll
+                for (int d = 0; d < kDim; ++d)
+                    g[d] = __shfl(group_sum(g[d], sh), (lane << sh) & 63, kWave);
+            }
+        }
+        if (!split) break;
+        // the four waves' sums of a row meet at the item's own wave, in wave
+        // order
+#pragma unroll
+        for (int d = 0; d < 3; ++d) M.F[d][lane] = g[d];
+        __syncthreads();
+        if (i == wv) {
+#pragma unroll
+            for (int d = 0; d < 3; ++d)
+                M.G[d][lane] = ((L.w[0].F[d][lane] + L.w[1].F[d][lane]) + L.w[2].F[d][lane]) +
+                        L.w[3].F[d][lane];
+        }
+        __syncthreads();
+        if (++i == kWavesPerBlock) {
+#pragma unroll
+            for (int d = 0; d < 3; ++d) g[d] = M.G[d][lane];
+            break;
+        }
+    }
+    __builtin_amdgcn_s_setprio(0);
+    double bd = 0;
+    const int64_t io = WB[wv].begin + lane;
+    if (io < WB[wv].end) {
+        const P4 oq = load_p4(p.q, (int32_t)io);
+        const Pre pre = preload<kDim>(p, io);
+        if (kWalls) {
+            // the row's wall terms (a sphere against the walls, in full)
+            WallAcc wl = {{0.0, 0.0, 0.0}, 0.0, 0.0, 0.0, 0.0};
+            const double px[3] = {oq.x, oq.y, oq.z};
+            wall_terms(px, c.kappa * oq.d, c.L, c.walls, c.round, wl);
+#pragma unroll
+            for (int d = 0; d < 3; ++d) g[d] += wl.g[d];
+            a.e += wl.e;
+            a.s += wl.s;
+            a.m = fmax(a.m, wl.m);
+        }
+        bd = update_particle<kMixed, kDim>(p, c, io, oq, pre, g[0], g[1], g[2],
+                                           (flags & 4) != 0);
+    }
+    block_partial<false>(a, bd, L.red, reinterpret_cast<Part4 *>(partials) + b);
+}
+
 // Items of up to 512 rows: two rows per thread in the Adam phase, so half as
 // many blocks carry the per-item set-up, synchronisation and reduction.
 template <int kU>
@@ -836,7 +1033,7 @@ __global__ __launch_bounds__(kBlock) void k_iterate512(const SegPtrs *__restrict
                                                       double *__restrict__ partials, int flags)
 {
     const int b = (flags & 1) ? remap_block((int)blockIdx.x, (int)gridDim.x) : (int)blockIdx.x;
-    const WorkItem w = W[b];
+    const WorkItem w = block_item(W, b);
     SegState *s = S + w.seg;
     if (s->flags & F_IDLE) return;
     IterScalars c;
@@ -887,7 +1084,7 @@ __global__ __launch_bounds__(kBlock) void k_iterate_persist(const SegPtrs *__res
     if (item >= hi) return;
     __shared__ ItemLds L;
     const int t = threadIdx.x;
-    WorkItem wn = W[item];
+    WorkItem wn = block_item(W, item);
     int cseg = -1;
     bool idle = true;
     IterScalars c;
@@ -897,7 +1094,7 @@ __global__ __launch_bounds__(kBlock) void k_iterate_persist(const SegPtrs *__res
     for (;;) {
         const WorkItem w = wn;
         const int next = item + nbx;
-        if (next < hi) wn = W[next];
+        if (next < hi) wn = block_item(W, next);
         if (w.seg != cseg) {
             cseg = w.seg;
             const SegState *s = S + cseg;
@@ -938,13 +1135,20 @@ __global__ __launch_bounds__(kBlock) void k_iterate_persist(const SegPtrs *__res
     }
 }
 
-template <bool kF, int kU, bool kE, bool kNT, int kW, bool kMixed = false, bool kWalls = false,
-          int kDim = 3>
+template <bool kF, int kU, bool kE, bool kNT, int kW>
 static void launch_one(const SegPtrs *P, SegState *S, const WorkItem *W, double *partials,
                        int nitems, int f, hipStream_t st)
 {
-    hipLaunchKernelGGL((k_iterate<kF, kU, kE, kNT, kW, kMixed, kWalls, kDim>), dim3(nitems),
-                       dim3(kBlock), 0, st, P, S, W, partials, f);
+    hipLaunchKernelGGL((k_iterate<kF, kU, kE, kNT, kW>), dim3(nitems), dim3(kBlock), 0, st, P, S,
+                       W, partials, f);
+}
+
+template <bool kMixed, bool kWalls, int kDim>
+static void launch_wave(const SegPtrs *P, SegState *S, const WorkItem *W, double *partials,
+                        int nitems, int f, hipStream_t st)
+{
+    hipLaunchKernelGGL((k_iterate_wave<kMixed, kWalls, kDim>), dim3(nitems), dim3(kBlock), 0, st,
+                       P, S, W, partials, f);
 }
 
 template <bool kF, int kW>
@@ -952,7 +1156,12 @@ static void launch_basic(const SegPtrs *P, SegState *S, const WorkItem *W, doubl
                          int nitems, int f, int variant, hipStream_t st)
 {
     switch (variant & 7) {
-    case 0: launch_one<kF, 2, false, false, kW>(P, S, W, partials, nitems, f, st); break;
+    case 0:
+        // (without the fused tail and at the compiler's own register count
+        // the wave kernel runs instead, see launch_iterate)
+        if constexpr (kF || kW > 1)
+            launch_one<kF, 2, false, false, kW>(P, S, W, partials, nitems, f, st);
+        break;
     case 1: launch_one<kF, 4, false, false, kW>(P, S, W, partials, nitems, f, st); break;
     case 2: launch_one<kF, 2, true, false, kW>(P, S, W, partials, nitems, f, st); break;
     case 3: launch_one<kF, 4, true, false, kW>(P, S, W, partials, nitems, f, st); break;
@@ -999,26 +1208,24 @@ void launch_iterate(const SegPtrs *P, SegState *S, const WorkItem *W, double *pa
                     int nitems, int flags, hipStream_t st)
 {
     // bit 0: XCD-aware order; bit 1: fused tail; bit 2: whole 32-byte
-    // records written; bit 4: some packing has frozen spheres (then the
-    // two-gather kernel with the mixed pair terms runs, whatever the
-    // variant); bit 5: some packing has walls (then the two-gather kernel
-    // with the wall terms runs, whatever the variant; never together with
-    // bit 4); bit 6: two dimensions (the two-gather kernel for two
-    // coordinates, whatever the variant); bits 8-13: kernel variant (see
-    // launch_variant)
-    const int f = flags & 5, variant = (flags >> 8) & 63;
+    // records written; bit 3: one packing; bit 4: some packing has frozen
+    // spheres (then the wave kernel with the mixed pair terms runs, whatever
+    // the variant); bit 5: some packing has walls (then the wave kernel with
+    // the wall terms runs, whatever the variant; never together with bit 4);
+    // bit 6: two dimensions (the wave kernel for two coordinates, whatever
+    // the variant); bits 8-13: kernel variant (see launch_variant; the wave
+    // kernel when none of them is set and the tail is not fused)
+    const int f = flags & 13, variant = (flags >> 8) & 63;
     if (flags & 64) {
-        if (flags & 32)
-            launch_one<false, 2, false, false, 1, false, true, 2>(P, S, W, partials, nitems, f, st);
-        else if (flags & 16)
-            launch_one<false, 2, false, false, 1, true, false, 2>(P, S, W, partials, nitems, f, st);
-        else
-            launch_one<false, 2, false, false, 1, false, false, 2>(P, S, W, partials, nitems, f,
-                                                                   st);
+        if (flags & 32) launch_wave<false, true, 2>(P, S, W, partials, nitems, f, st);
+        else if (flags & 16) launch_wave<true, false, 2>(P, S, W, partials, nitems, f, st);
+        else launch_wave<false, false, 2>(P, S, W, partials, nitems, f, st);
     } else if (flags & 32)
-        launch_one<false, 2, false, false, 1, false, true>(P, S, W, partials, nitems, f, st);
+        launch_wave<false, true, 3>(P, S, W, partials, nitems, f, st);
     else if (flags & 16)
-        launch_one<false, 2, false, false, 1, true>(P, S, W, partials, nitems, f, st);
+        launch_wave<true, false, 3>(P, S, W, partials, nitems, f, st);
+    else if (variant == 0 && !(flags & 2))
+        launch_wave<false, false, 3>(P, S, W, partials, nitems, f, st);
     else if (variant & 40) launch_variant<false>(P, S, W, partials, nitems, f, variant, st);
     else if (flags & 2) launch_variant<true>(P, S, W, partials, nitems, f, variant, st);
     else launch_variant<false>(P, S, W, partials, nitems, f, variant, st);

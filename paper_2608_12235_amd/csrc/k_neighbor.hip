@@ -861,12 +861,16 @@ void launch_search_seg(const FrontJob *jobs, int J, int64_t nb, int max_nlev, in
 // q (empty rows included).  Thread m closes the rows after the last entry.
 __device__ __forceinline__ void csr_one(const uint64_t *__restrict__ srt, int64_t m, int row_bits,
                                         int64_t n, int32_t *__restrict__ rp,
-                                        int32_t *__restrict__ col, int64_t q)
+                                        int32_t *__restrict__ col, uint8_t *__restrict__ rlo,
+                                        int64_t q)
 {
     const uint64_t mask = (1ull << row_bits) - 1ull;
     const int64_t prev = q == 0 ? -1 : (int64_t)(srt[q - 1] >> row_bits);
     const int64_t r = q == m ? n : (int64_t)(srt[q] >> row_bits);
-    if (q < m) col[q] = (int32_t)(srt[q] & mask);
+    if (q < m) {
+        col[q] = (int32_t)(srt[q] & mask);
+        rlo[q] = (uint8_t)r;
+    }
     for (int64_t rr = prev + 1; rr <= r; ++rr) rp[rr] = (int32_t)q;
 }
 
@@ -916,7 +920,7 @@ __global__ __launch_bounds__(kBlock) void k_csr_seg(const BackJob *__restrict__ 
 {
     const BackJob &B = jobs[job_of(jobs, J, blockIdx.x, &BackJob::bc0)];
     const int64_t q = ((int64_t)blockIdx.x - B.bc0) * kBlock + threadIdx.x;
-    if (q <= B.m) csr_one(B.srt, B.m, B.row_bits, B.n, B.rp, B.col, q);
+    if (q <= B.m) csr_one(B.srt, B.m, B.row_bits, B.n, B.rp, B.col, B.rlo, q);
 }
 
 void launch_keys_seg(const FrontJob *jobs, int J, int64_t nb, hipStream_t s)

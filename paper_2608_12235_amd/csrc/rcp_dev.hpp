@@ -55,6 +55,7 @@ struct SegPtrs {
     uint8_t *lev;         // size class
     int32_t *rp;          // row pointers (n + 1) into col
     int32_t *col;         // partners (segment-local sorted indices)
+    uint8_t *rlo;         // low eight bits of each entry's row
 };
 
 // Scalars of one segment.  "host" fields are set by the host; the rest are
@@ -97,7 +98,8 @@ __host__ __device__ inline void seg_bias_terms(SegState &s)
     s.ib2n = 1.0 / (1.0 - s.b2t * s.beta2);
 }
 
-// One block of the iteration grid: rows [begin, end) of packing seg.
+// One wave of the iteration grid: rows [begin, end) of packing seg.  The
+// four items of a block are consecutive and of one packing.
 struct WorkItem {
     int32_t seg;
     int32_t e0, e1;       // its CSR entries [e0, e1) = [rp[begin], rp[end])

@@ -91,6 +91,7 @@ struct BackJob {
     int64_t m, n;
     int32_t row_bits, seg;
     int32_t *rp, *col;
+    uint8_t *rlo;
     WorkItem *W;            // the packing's work-item slots
     int64_t nslots;
     int32_t row_cost, item_work;
@@ -207,9 +208,10 @@ void launch_place_round(const PlaceArgs &a, int c, int64_t lo, int64_t hi, hipSt
 // flags bit 0: XCD-aware block order; bit 1: the last block of each packing
 // runs its tail (otherwise launch_tail must follow); bit 2: whole 32-byte
 // position records written (else the three coordinates only).
-// Work items of packing seg (nslots slots at W): rows are cut so that an
-// item covers item_work units of row_cost * row + row pointer; rp == nullptr
-// leaves every slot empty.
+// bit 3: one packing (number 0).
+// Work items of packing seg (nslots slots at W, four a block): rows are cut
+// so that an item covers item_work units of row_cost * row + row pointer; rp
+// == nullptr leaves every slot empty.
 void launch_items(const int32_t *rp, int64_t n, int seg, int row_cost, int item_work,
                   WorkItem *W, int64_t nslots, hipStream_t st);
 void launch_iterate(const SegPtrs *P, SegState *S, const WorkItem *W, double *partials,

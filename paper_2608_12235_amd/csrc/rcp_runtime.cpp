@@ -109,7 +109,8 @@ struct Seg {
     uint8_t *LEV[2] = {};
     float *XREF[3] = {};
     int32_t *rp = nullptr, *col = nullptr;
-    int64_t col_cap = 0;
+    uint8_t *rlo = nullptr;          // low eight bits of each entry's row
+    int64_t col_cap = 0;             // entries col and rlo hold
     int set = 0;
     int cur = 0;          // host copy of the live position buffer
     int64_t npairs = 0, nnz = 0, maxdeg = 0, list_est = 0;
@@ -223,6 +224,21 @@ static void ptrs_of(const Seg &s, SegPtrs &p)
     p.lev = s.LEV[s.set];
     p.rp = s.rp;
     p.col = s.col;
+    p.rlo = s.rlo;
+}
+
+// Room for at least m entries in a packing's list (contents discarded).
+static int grow_cols(Seg &s, int64_t m)
+{
+    if (m <= s.col_cap) return RCP_OK;
+    dfree(s.col);
+    dfree(s.rlo);
+    s.col_cap = 0;
+    const int64_t cap = std::max<int64_t>(m + m / 4, 1024);
+    CHK(dalloc(&s.col, (size_t)cap));
+    CHK(dalloc(&s.rlo, (size_t)cap));
+    s.col_cap = cap;
+    return RCP_OK;
 }
 
 static int rebuild_events(rcp_ctx *c, std::pair<hipEvent_t, hipEvent_t> &ev)
@@ -301,12 +317,35 @@ static int scratch_address(double **out)
 constexpr double kXrefErr = 1.7320508075688772 * 0x1p-23;
 
 // ------------------------------------------------------------ work table
-// Work-item slots for packing k: enough for row_cost * n + slot_entries
-// units of item_work each (see rcp_tuning), plus one.
+// The cut of the rows into work items, one a wave, four a block (the kernels
+// that take a block's rows together join its four): a row costs row_units
+// plus one per partner, an item holds wave_work units.  A wave takes a sixth
+// of the tuning's item_work, and a row two thirds of its row_cost: by the
+// defaults (6, 1536) 256 units at 4 a row, so up to 64 rows, about 40 on the
+// dense million-sphere state (2.3 partners a row).  Measured there, on 3e6
+// spheres of size ratio 5e5 and on 1e5 spheres with 5.2 partners, us per
+// launch: 42.2 / 126 / 13.8; with a quarter of both, 384 units at 6, 42.8 /
+// 127 / 16.0, with 256 at 5 46.7 / 130 / 14.3, with 192 at 3 43.1 / 128 /
+// 13.7 (and more partials for the tail).  item_work <= 256 row_cost keeps an
+// item within the wave kernel's 64 rows; with variant bit 5 (512 row_cost)
+// they are cut to that when the packings are of a kind that only the wave
+// kernel takes.
+static int row_units(const rcp_ctx *c) { return (2 * c->tuning.row_cost + 2) / 3; }
+
+static int wave_work(const rcp_ctx *c)
+{
+    const int wk = std::max(1, c->tuning.item_work / 6);
+    return c->any_mixed || c->any_walls || c->dim == 2
+               ? (int)std::min<int64_t>(wk, (int64_t)kWave * row_units(c))
+               : wk;
+}
+
+// Work-item slots for packing k: enough for row_units * n + slot_entries
+// units of wave_work each, plus one, in whole blocks.
 static int64_t slots_for(const rcp_ctx *c, int64_t n, int64_t entries)
 {
-    const int64_t rc = c->tuning.row_cost, wk = c->tuning.item_work;
-    return (rc * n + entries) / wk + 2;
+    const int64_t k = (row_units(c) * n + entries) / wave_work(c) + 2;
+    return (k + kWavesPerBlock - 1) / kWavesPerBlock * kWavesPerBlock;
 }
 
 // Cut the rows of a built packing into work items (device kernel on its
@@ -314,9 +353,9 @@ static int64_t slots_for(const rcp_ctx *c, int64_t n, int64_t entries)
 static void fill_items(rcp_ctx *c, int k, hipStream_t st)
 {
     Seg &s = c->segs[k];
-    WorkItem *w = c->d_work + s.first_item;
-    launch_items(s.built ? s.rp : nullptr, s.n, k, c->tuning.row_cost, c->tuning.item_work, w,
-                 s.blocks, st);
+    WorkItem *w = c->d_work + s.first_item * kWavesPerBlock;
+    launch_items(s.built ? s.rp : nullptr, s.n, k, row_units(c), wave_work(c), w,
+                 (int64_t)s.blocks * kWavesPerBlock, st);
 }
 
 // Lay out the work-item slots of all packings (a graph captured before is
@@ -327,7 +366,7 @@ static int build_work(rcp_ctx *c)
     for (size_t k = 0; k < c->segs.size(); ++k) {
         Seg &s = c->segs[k];
         // a finished packing gets no slots (its blocks would only exit)
-        const int64_t nb = s.parked ? 0 : slots_for(c, s.n, s.slot_entries);
+        const int64_t nb = s.parked ? 0 : slots_for(c, s.n, s.slot_entries) / kWavesPerBlock;
         if (nb > (int64_t)INT32_MAX / 4 || total + nb > (int64_t)INT32_MAX / 4)
             return fail(RCP_ENOMEM, "work table too large");
         s.blocks = (int)nb;
@@ -339,7 +378,7 @@ static int build_work(rcp_ctx *c)
         dfree(c->d_partials);
         c->d_work = nullptr;
         c->d_partials = nullptr;
-        CHK(dalloc(&c->d_work, (size_t)total));
+        CHK(dalloc(&c->d_work, (size_t)total * kWavesPerBlock));
         CHK(dalloc(&c->d_partials, 4 * (size_t)total));
         c->items_cap = total;
     }
@@ -731,16 +770,17 @@ static int build_backs(rcp_ctx *c, std::vector<BuildJob> &jobs, const std::vecto
         B.seg = j.k;
         B.rp = s.rp;
         B.col = s.col;
-        B.W = c->d_work + s.first_item;
-        B.nslots = s.blocks;
-        B.row_cost = c->tuning.row_cost;
-        B.item_work = c->tuning.item_work;
+        B.rlo = s.rlo;
+        B.W = c->d_work + s.first_item * kWavesPerBlock;
+        B.nslots = (int64_t)s.blocks * kWavesPerBlock;
+        B.row_cost = row_units(c);
+        B.item_work = wave_work(c);
         s.list_est = m;
         s.built = true;
         // the work table holds this list's items; it is laid out again when
         // it is too small, or more than twice too large (idle items still
         // cost a launch slot and a partial for the tail to read)
-        B.fill = (slots_for(c, s.n, m) <= s.blocks && slots_for(c, s.n, 2 * m) >= s.blocks) ? 1 : 0;
+        B.fill = (slots_for(c, s.n, m) <= B.nslots && slots_for(c, s.n, 2 * m) >= B.nslots) ? 1 : 0;
         if (!B.fill) {
             s.slot_entries = m + m / 4;
             *relayout = true;
@@ -757,7 +797,7 @@ static int build_backs(rcp_ctx *c, std::vector<BuildJob> &jobs, const std::vecto
         B.bc0 = nbc;
         nbc += (m + 1 + kBlock - 1) / kBlock;
         B.bs0 = nbs;
-        nbs += (s.blocks + kBlock - 1) / kBlock;
+        nbs += (B.nslots + kBlock - 1) / kBlock;
         B.br0 = nbr;
         nbr += (s.n + kBlock - 1) / kBlock;
         s.npairs = m / 2;
@@ -846,12 +886,7 @@ static int rebuild_batch(rcp_ctx *c, const std::vector<int> &ks, const std::vect
             continue;
         }
         ok.push_back((int)q);
-        Seg &s = c->segs[jobs[q].k];
-        if (ms[q] > s.col_cap) {
-            dfree(s.col);
-            s.col_cap = std::max<int64_t>(ms[q] + ms[q] / 4, 1024);
-            CHK(dalloc(&s.col, (size_t)s.col_cap));
-        }
+        CHK(grow_cols(c->segs[jobs[q].k], ms[q]));
     }
     bool relayout = false;
     CHK(build_backs(c, jobs, ok, ms, &relayout));
@@ -871,12 +906,7 @@ static int rebuild_batch(rcp_ctx *c, const std::vector<int> &ks, const std::vect
         std::vector<int64_t> m1(1, (int64_t)c->h_bcount[0]);
         CHK(check_list_size(jobs[q].k, m1[0]));
         if (m1[0] > one[0].lcap) return fail(RCP_ENOMEM, "pair list overflow after regrowth");
-        Seg &s = c->segs[jobs[q].k];
-        if (m1[0] > s.col_cap) {
-            dfree(s.col);
-            s.col_cap = std::max<int64_t>(m1[0] + m1[0] / 4, 1024);
-            CHK(dalloc(&s.col, (size_t)s.col_cap));
-        }
+        CHK(grow_cols(c->segs[jobs[q].k], m1[0]));
         CHK(build_backs(c, one, std::vector<int>{0}, m1, &relayout));
     }
     HIPCHK(hipEventRecord(ev.second, c->stream));
@@ -933,6 +963,7 @@ static bool slot_timed(const rcp_ctx *c, int64_t slot)
 static int iterate_flags(const rcp_ctx *c)
 {
     return (c->tuning.xcd_remap ? 1 : 0) | ((c->tuning.variant & 128) ? 4 : 0) |
+           (c->segs.size() == 1 ? 8 : 0) |
            (c->any_mixed ? 16 : 0) | (c->any_walls ? 32 : 0) | (c->dim == 2 ? 64 : 0) |
            ((c->tuning.variant & 63) << 8);
 }
@@ -1506,9 +1537,10 @@ static int seg_setup(rcp_ctx *c, int k, int64_t n, const double *d0, double L, d
     }
     for (int a = 0; a < 3; ++a) CHK(dalloc(&s.XREF[a], n));
     CHK(dalloc(&s.rp, n + 1));
-    s.col_cap = std::max<int64_t>(8 * n, 1024);
-    CHK(dalloc(&s.col, s.col_cap));
-    s.slot_entries = s.col_cap;
+    s.slot_entries = std::max<int64_t>(8 * n, 1024);
+    CHK(dalloc(&s.col, s.slot_entries));
+    CHK(dalloc(&s.rlo, s.slot_entries));
+    s.col_cap = s.slot_entries;
     std::vector<float> soa(n);
     for (int a = 0; a < 3; ++a) {
         for (int64_t i = 0; i < n; ++i) soa[i] = (float)x[3 * i + a];
@@ -1576,6 +1608,7 @@ static void destroy_ctx(rcp_ctx *c)
         for (int a = 0; a < 3; ++a) dfree(s.XREF[a]);
         dfree(s.rp);
         dfree(s.col);
+        dfree(s.rlo);
     }
     dfree(c->d_ptrs);
     dfree(c->d_state);
@@ -1658,8 +1691,7 @@ void rcp_tuning_default(rcp_tuning *t)
     // cooperative pair search; whole 32-byte records written (measured at
     // least as fast as writing the three coordinates alone)
     t->variant = 64 | 128;
-    // work items of about 185 rows on the C3 state: measured best with the
-    // partner phase at issue priority 2 (8 / 2048 before it)
+    // work items: see wave_work
     t->row_cost = 6;
     t->item_work = 1536;
     t->time_kernels = 0;
@@ -1953,9 +1985,11 @@ int rcp_set_frozen(rcp_ctx *c, int k, const uint8_t *mask)
     s.frozen = s.mixed ? fz : std::vector<uint8_t>();
     s.sum3_frozen = f3;
     s.sum3_grow = sum3 + cs3;
+    const int cut = wave_work(c);
     c->any_mixed = false;
     for (const Seg &q : c->segs) c->any_mixed = c->any_mixed || q.mixed;
     c->graph_valid = false;
+    if (wave_work(c) != cut) CHK(build_work(c));
     return RCP_OK;
 }
 
@@ -1981,9 +2015,11 @@ int rcp_set_boundary(rcp_ctx *c, int k, uint32_t walls, uint32_t round)
     s.walls = (int32_t)walls;
     s.round = (int32_t)round;
     s.built = false;
+    const int cut = wave_work(c);
     c->any_walls = false;
     for (const Seg &q : c->segs) c->any_walls = c->any_walls || (q.walls | q.round) != 0;
     c->graph_valid = false;
+    if (wave_work(c) != cut) CHK(build_work(c));
     return RCP_OK;
 }
 

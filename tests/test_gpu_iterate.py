@@ -1,0 +1,88 @@
+"""The wave-per-item gradient + Adam kernel at the edges of its work items,
+against the FP64 CPU oracle.
+
+A large sphere with `k` small partners gives one row of k entries beside k
+rows of a few: k below, at and above a round of 64 entries, two rounds, the
+512 entries from which a block shares its items, and many times that.  The
+cuts run from one row an item to 64 and to items of thousands of entries.
+Bars: positions within 1e-9 of the step size per step plus 4e-16 L, kappa to
+1e-12, as for the Adam steps elsewhere.
+"""
+import numpy as np
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def rcp():
+    torch = pytest.importorskip("torch")
+    if not torch.cuda.is_available():
+        pytest.skip("no HIP device")
+    import paper_2608_12235_amd as m
+    m.lib()
+    return m
+
+
+def _star(k, dim, seed):
+    """One sphere of diameter 8 at the centre, k of diameter 0.8 to 1.2 whose
+    centres lie on a shell they overlap it from, 37 more in a corner."""
+    rng = np.random.default_rng(seed)
+    L, big = 24.0, 8.0
+    u = rng.standard_normal((k, dim))
+    u /= np.linalg.norm(u, axis=1)[:, None]
+    d = 0.8 + 0.4 * rng.random(k + 37)
+    x = np.concatenate([np.full((1, dim), 0.5 * L),
+                        0.5 * L + u * (0.45 * big + 0.4 * d[:k, None]),
+                        rng.random((37, dim)) * 4.0])
+    return np.concatenate([[big], d]), x, L
+
+
+@pytest.mark.parametrize("k", [1, 62, 63, 64, 65, 128, 129, 511, 512, 513, 4000])
+@pytest.mark.parametrize("row_cost,item_work,kind", [
+    (6, 1536, "plain"), (6, 1536, "frozen"), (6, 1536, "walls"), (6, 1536, "disks"),
+    (1, 1, "plain"), (4, 1024, "plain"), (64, 16384, "plain"), (6, 3072, "wide")])
+def test_long_rows_and_item_cuts(rcp, orc, k, row_cost, item_work, kind):
+    if kind != "plain" and k not in (64, 513, 4000):
+        pytest.skip("plain packings run every length")
+    dim = 2 if kind == "disks" else 3
+    d0, x, L = _star(k, dim, 17 + k)
+    mu, ex, ek, steps = 1e-4, 1e-3, 1e-4, 3
+    frozen = np.zeros(len(d0), np.uint8)
+    if kind in ("frozen", "wide"):
+        frozen[0] = 1
+        frozen[2::5] = 1
+    bnd = (7, 0) if kind == "walls" else None
+    P = orc.default_params(d0, s=0.3, g=0.02)
+    p = rcp.Packing(d0, L, 1.0, 0, init="none", dim=dim, boundary=bnd,
+                    params=rcp.make_params(skin_s=0.3, skin_g=0.02, eps_x=P.eps_x),
+                    tuning=rcp.make_tuning(row_cost=row_cost, item_work=item_work,
+                                           variant=192 | (32 if kind == "wide" else 0)))
+    p.set_state(x, 1.0)
+    if frozen.any():
+        p.set_frozen(frozen)
+    p.adam_step(mu, ex, ek, steps)
+    xg, kg = p.get_state()
+    assert p.stats()["max_degree"] >= k
+    p.close()
+    x3 = np.zeros((len(d0), 3))
+    x3[:, :dim] = x
+    try:
+        if dim == 2:
+            orc.set_dim(2)
+        if frozen.any():
+            orc.set_frozen(frozen)
+        if bnd:
+            orc.set_boundary(*bnd)
+        st = orc.RunState(x3, d0, L, 1.0)
+        orc.run(st, P, orc.oracle.absolute_schedule(mu, ex, ek, steps))
+    finally:
+        orc.set_frozen(None)
+        orc.set_boundary(0, 0)
+        if dim == 2:
+            orc.set_dim(3)
+    d = np.abs(xg - st.x[:, :dim])
+    if bnd is None:
+        d = np.minimum(d, L - d)
+    assert d.max() <= 1e-9 * ex * steps + 4e-16 * L, d.max()
+    assert kg == pytest.approx(st.kappa[0], rel=1e-12)
