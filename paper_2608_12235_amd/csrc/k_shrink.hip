@@ -147,18 +147,26 @@ void launch_shrink(const SegPtrs *P, const SegState *S, int seg, int64_t n, doub
                        part + nblocks);
 }
 
-__global__ __launch_bounds__(kWave) void k_max_finish(const double *__restrict__ part, int nb,
-                                                     double *__restrict__ out)
+constexpr int kMaxBlock = 1024;
+
+__global__ __launch_bounds__(kMaxBlock) void k_max_finish(const double *__restrict__ part, int nb,
+                                                         double *__restrict__ out)
 {
     double m = 0.0;
-    for (int b = threadIdx.x; b < nb; b += kWave) m = fmax(m, part[b]);
-    m = wave_max(m);
-    if (threadIdx.x == 0) out[0] = m;
+    for (int b = threadIdx.x; b < nb; b += kMaxBlock) m = fmax(m, part[b]);
+    m = wave_max_dpp(m);
+    __shared__ double red[kMaxBlock / kWave];
+    if ((threadIdx.x & (kWave - 1)) == 0) red[threadIdx.x / kWave] = m;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        for (int k = 1; k < kMaxBlock / kWave; ++k) m = fmax(m, red[k]);
+        out[0] = m;
+    }
 }
 
 void launch_max_finish(const double *part, int nblocks, double *out, hipStream_t st)
 {
-    hipLaunchKernelGGL(k_max_finish, dim3(1), dim3(kWave), 0, st, part, nblocks, out);
+    hipLaunchKernelGGL(k_max_finish, dim3(1), dim3(kMaxBlock), 0, st, part, nblocks, out);
 }
 
 }  // namespace rcp

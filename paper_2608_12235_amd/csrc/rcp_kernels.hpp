@@ -228,18 +228,30 @@ void launch_sched_start(SegState *S, int seg, const SchedDev &q, int reset_adam,
                         int64_t iter_limit, hipStream_t s);
 void launch_set_flags(SegState *S, int seg, int32_t clear, int32_t set, hipStream_t s);
 
-// Energy terms / gradient of one segment at positions given in user order
-// (xu, n x 3 row-major, device) or at its current state (xu == nullptr).
-struct EvalOut {
-    double *part;     // per-block partials: E_ov, S_drd, max delta, n_overlap
-    double *gu;       // dE/dx in user order (n x 3) or nullptr
-};
+// Energy terms of one segment at positions given in user order (xu, n x 3
+// row-major, device): per-block partials E_ov, S_drd, max delta, n_overlap.
 void launch_eval(const SegPtrs *P, const SegState *S, int seg, int64_t n, const double *xu,
-                 double kappa, const EvalOut &o, int nblocks, hipStream_t s);
+                 double kappa, double *part, int nblocks, hipStream_t s);
 // Final reduction of launch_eval partials into out[0..5]: E_ov, E_growth,
 // gk_ov, gk_growth, max delta, n_overlap (mu and sum D0 given).
+// (E, gk: where not null, E[0..1] = total energy and max delta, gk[0] = total
+// dE/dkappa).
 void launch_eval_finish(const double *part, int nblocks, double kappa, double mu,
-                        const SegState *S, int seg, double *out, hipStream_t s);
+                        const SegState *S, int seg, double *out, double *E, double *gk,
+                        hipStream_t s);
+struct EvalOut {
+    double *part;     // the partials of launch_eval
+    double *gu;       // dE/dx in user order (n x 3) or nullptr
+};
+// The terms of launch_eval by work items (nblocks blocks of four at W), over
+// the positions Q in list order (nullptr: the current buffer); flags bits 4
+// and 5 as in launch_iterate.
+void launch_eval_wave(const SegPtrs *P, const SegState *S, int seg, const WorkItem *W, const P4 *Q,
+                      double kappa, int flags, const EvalOut &o, int nblocks, hipStream_t s);
+// Positions xu (user order, n x 3) into Q (list order, the current records'
+// D0), and per block the largest displacement^2 against the list's xref.
+void launch_gather_disp(const SegPtrs *P, const SegState *S, int seg, int64_t n, const double *xu,
+                        P4 *Q, double *part, int nblocks, hipStream_t s);
 // Max displacement^2 of xu (user order, n x 3) against the list's xref.
 void launch_disp(const SegPtrs *P, const SegState *S, int seg, int64_t n, const double *xu,
                  double *part, int nblocks, hipStream_t s);

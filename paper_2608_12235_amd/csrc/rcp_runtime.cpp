@@ -109,7 +109,7 @@ struct Seg {
     uint8_t *LEV[2] = {};
     float *XREF[3] = {};
     int32_t *rp = nullptr, *col = nullptr;
-    uint8_t *rlo = nullptr;          // low eight bits of each entry's row
+    uint8_t *rlo = nullptr;          // low eight bits of each entry's row (in col's memory)
     int64_t col_cap = 0;             // entries col and rlo hold
     int set = 0;
     int cur = 0;          // host copy of the live position buffer
@@ -196,6 +196,10 @@ struct rcp_ctx {
     double *out = nullptr;           // small device results
     double *xtmp = nullptr;          // staging of user-order positions
     int64_t xtmp_cap = 0;
+    P4 *qtmp = nullptr;              // given positions in list order
+    int64_t qtmp_cap = 0;
+    WorkItem *eitems = nullptr;      // work items of an evaluation (see eval_current)
+    int64_t eitems_cap = 0;
     double *h_out = nullptr;         // pinned small results
     // iteration graphs by length (see graph_len); graph_valid = false
     // drops them all before the next launch
@@ -227,18 +231,22 @@ static void ptrs_of(const Seg &s, SegPtrs &p)
     p.rlo = s.rlo;
 }
 
-// Room for at least m entries in a packing's list (contents discarded).
-static int grow_cols(Seg &s, int64_t m)
+// A packing's list with room for cap entries (contents discarded): partner
+// indices and row bytes in one allocation.
+static int alloc_cols(Seg &s, int64_t cap)
 {
-    if (m <= s.col_cap) return RCP_OK;
     dfree(s.col);
-    dfree(s.rlo);
+    s.rlo = nullptr;
     s.col_cap = 0;
-    const int64_t cap = std::max<int64_t>(m + m / 4, 1024);
-    CHK(dalloc(&s.col, (size_t)cap));
-    CHK(dalloc(&s.rlo, (size_t)cap));
+    CHK(dalloc(&s.col, (size_t)(cap + (cap + 3) / 4)));
+    s.rlo = (uint8_t *)(s.col + cap);
     s.col_cap = cap;
     return RCP_OK;
+}
+
+static int grow_cols(Seg &s, int64_t m)
+{
+    return m <= s.col_cap ? RCP_OK : alloc_cols(s, std::max<int64_t>(m + m / 4, 1024));
 }
 
 static int rebuild_events(rcp_ctx *c, std::pair<hipEvent_t, hipEvent_t> &ev)
@@ -1538,9 +1546,7 @@ static int seg_setup(rcp_ctx *c, int k, int64_t n, const double *d0, double L, d
     for (int a = 0; a < 3; ++a) CHK(dalloc(&s.XREF[a], n));
     CHK(dalloc(&s.rp, n + 1));
     s.slot_entries = std::max<int64_t>(8 * n, 1024);
-    CHK(dalloc(&s.col, s.slot_entries));
-    CHK(dalloc(&s.rlo, s.slot_entries));
-    s.col_cap = s.slot_entries;
+    CHK(alloc_cols(s, s.slot_entries));
     std::vector<float> soa(n);
     for (int a = 0; a < 3; ++a) {
         for (int64_t i = 0; i < n; ++i) soa[i] = (float)x[3 * i + a];
@@ -1608,7 +1614,6 @@ static void destroy_ctx(rcp_ctx *c)
         for (int a = 0; a < 3; ++a) dfree(s.XREF[a]);
         dfree(s.rp);
         dfree(s.col);
-        dfree(s.rlo);
     }
     dfree(c->d_ptrs);
     dfree(c->d_state);
@@ -1642,6 +1647,8 @@ static void destroy_ctx(rcp_ctx *c)
     dfree(c->part);
     dfree(c->out);
     dfree(c->xtmp);
+    dfree(c->qtmp);
+    dfree(c->eitems);
     if (c->h_state) (void)hipHostFree(c->h_state);
     if (c->h_out) (void)hipHostFree(c->h_out);
     if (c->h_layout) (void)hipHostFree(c->h_layout);
@@ -2310,17 +2317,31 @@ int rcp_get_pairs(rcp_ctx *c, int k, int32_t *pi, int32_t *pj, int64_t cap, int6
     return RCP_OK;
 }
 
-static int eval_current(rcp_ctx *c, int k, const double *xu, double kappa, double mu,
-                        double *gu_dev, hipStream_t st)
+// Energy terms of packing k (its list built) at kappa into c->out, at the
+// positions q in list order or (nullptr) its current ones; the gradient to gu
+// (user order, n x 3) where given; E, gk as in launch_eval_finish.
+static int eval_current(rcp_ctx *c, int k, const P4 *q, double kappa, double mu, double *gu_dev,
+                        double *E, double *gk, hipStream_t st)
 {
     Seg &s = c->segs[k];
-    const int nb = (int)std::max<int64_t>(1, (s.n + kBlock - 1) / kBlock);
+    // the packing's items in the work table; a finished packing has given
+    // them up, and its rows are cut here
+    const WorkItem *w = c->d_work + s.first_item * kWavesPerBlock;
+    int nb = s.blocks;
+    if (s.parked) {
+        const int64_t slots = slots_for(c, s.n, s.nnz);
+        CHK(dgrow(&c->eitems, &c->eitems_cap, slots));
+        launch_items(s.rp, s.n, k, row_units(c), wave_work(c), c->eitems, slots, st);
+        w = c->eitems;
+        nb = (int)(slots / kWavesPerBlock);
+    }
     CHK(dgrow(&c->part, &c->part_cap, 4 * (int64_t)nb + 8));
     EvalOut o;
     o.part = c->part;
     o.gu = gu_dev;
-    launch_eval(c->d_ptrs, c->d_state, k, s.n, xu, kappa, o, nb, st);
-    launch_eval_finish(c->part, nb, kappa, mu, c->d_state, k, c->out, st);
+    const int flags = (s.mixed ? 16 : 0) | ((s.walls | s.round) ? 32 : 0);
+    launch_eval_wave(c->d_ptrs, c->d_state, k, w, q, kappa, flags, o, nb, st);
+    launch_eval_finish(c->part, nb, kappa, mu, c->d_state, k, c->out, E, gk, st);
     return RCP_OK;
 }
 
@@ -2339,7 +2360,7 @@ int rcp_energy_grad(rcp_ctx *c, int k, double mu, rcp_energy *e, double *grad_x)
         CHK(dgrow(&c->xtmp, &c->xtmp_cap, 3 * s.n));
         gdev = c->xtmp;
     }
-    CHK(eval_current(c, k, nullptr, c->h_state[k].kappa, mu, gdev, c->stream));
+    CHK(eval_current(c, k, nullptr, c->h_state[k].kappa, mu, gdev, nullptr, nullptr, c->stream));
     double o[6];
     HIPCHK(hipMemcpyAsync(o, c->out, sizeof o, hipMemcpyDeviceToHost, c->stream));
     std::vector<double> g3(grad_x && c->dim != 3 ? 3 * s.n : 0);
@@ -2546,27 +2567,36 @@ int rcp_shrink(rcp_ctx *c, int k, double *kappa_shrunk, double *phi)
     return RCP_OK;
 }
 
-// Make the list valid for user-order device positions x_dev at kappa.
-static int ensure_valid_at(rcp_ctx *c, const double *x_dev, double kappa, hipStream_t st)
+// Make the list valid for user-order device positions x_dev at kappa; *q
+// receives the positions in list order (nullptr: they are the current ones).
+// The context's record and the displacement come back in one round trip.
+static int ensure_valid_at(rcp_ctx *c, const double *x_dev, double kappa, hipStream_t st,
+                           const P4 **q)
 {
     if (st != c->stream) HIPCHK(hipStreamSynchronize(c->stream));
-    CHK(pull_state(c));
     Seg &s = c->segs[0];
     SegState &h = c->h_state[0];
-    bool ok = s.built && !(h.flags & (F_REBUILD | F_STALE));
+    *q = nullptr;
+    bool ok = s.built;
     if (ok) {
         const int nb = (int)std::max<int64_t>(1, (s.n + kBlock - 1) / kBlock);
         CHK(dgrow(&c->part, &c->part_cap, 4 * (int64_t)nb + 8));
-        launch_disp(c->d_ptrs, c->d_state, 0, s.n, x_dev, c->part, nb, st);
+        CHK(dgrow(&c->qtmp, &c->qtmp_cap, s.n));
+        launch_gather_disp(c->d_ptrs, c->d_state, 0, s.n, x_dev, c->qtmp, c->part, nb, st);
         launch_max_finish(c->part, nb, c->out + 8, st);
-        double d2 = 0;
-        HIPCHK(hipMemcpyAsync(&d2, c->out + 8, sizeof d2, hipMemcpyDeviceToHost, st));
+        HIPCHK(hipMemcpyAsync(c->h_out, c->out + 8, sizeof(double), hipMemcpyDeviceToHost, st));
+        HIPCHK(hipMemcpyAsync(c->h_state, c->d_state, sizeof(SegState) * c->segs.size(),
+                              hipMemcpyDeviceToHost, st));
         HIPCHK(hipStreamSynchronize(st));
+        for (size_t k = 0; k < c->segs.size(); ++k) c->segs[k].cur = c->h_state[k].cur;
         // the test the iteration tail applies (see k_iterate.hip)
         const double excess = std::max(0.0, kappa - h.kappa_lim);
-        ok = 2.0 * std::sqrt(d2) + excess * h.d0max_k <= 2.0 * h.disp_lim;
+        ok = !(h.flags & (F_REBUILD | F_STALE)) &&
+             2.0 * std::sqrt(c->h_out[0]) + excess * h.d0max_k <= 2.0 * h.disp_lim;
+        *q = c->qtmp;
     }
     if (!ok) {
+        *q = nullptr;
         HIPCHK(hipStreamSynchronize(st));
         CHK(rcp_set_state(c, 0, x_dev, kappa, 1));
         CHK(rebuild(c, 0, kappa));
@@ -2575,23 +2605,15 @@ static int ensure_valid_at(rcp_ctx *c, const double *x_dev, double kappa, hipStr
     return RCP_OK;
 }
 
-__global__ void k_energy_out(const double *o, double *E)
-{
-    E[0] = o[0] + o[1];
-    E[1] = o[4];
-}
-
-__global__ void k_gk_out(const double *o, double *gk) { gk[0] = o[2] + o[3]; }
-
 int rcp_energy_dev(rcp_ctx *c, const double *x_dev, double kappa, double mu, double *E_dev,
                    void *stream)
 {
     if (!c || !x_dev || !E_dev) return fail(RCP_EINVAL, "null argument");
     if (c->dim != 3) return fail(RCP_EINVAL, "device position arrays need dim = 3");
     hipStream_t st = (hipStream_t)stream;   // NULL: the null stream
-    CHK(ensure_valid_at(c, x_dev, kappa, st));
-    CHK(eval_current(c, 0, x_dev, kappa, mu, nullptr, st));
-    hipLaunchKernelGGL(k_energy_out, dim3(1), dim3(1), 0, st, c->out, E_dev);
+    const P4 *q = nullptr;
+    CHK(ensure_valid_at(c, x_dev, kappa, st, &q));
+    CHK(eval_current(c, 0, q, kappa, mu, nullptr, E_dev, nullptr, st));
     HIPCHK(hipGetLastError());
     return RCP_OK;
 }
@@ -2602,9 +2624,9 @@ int rcp_adjoint_dev(rcp_ctx *c, const double *x_dev, double kappa, double mu, do
     if (!c || !x_dev || !gx_dev || !gk_dev) return fail(RCP_EINVAL, "null argument");
     if (c->dim != 3) return fail(RCP_EINVAL, "device position arrays need dim = 3");
     hipStream_t st = (hipStream_t)stream;   // NULL: the null stream
-    CHK(ensure_valid_at(c, x_dev, kappa, st));
-    CHK(eval_current(c, 0, x_dev, kappa, mu, gx_dev, st));
-    hipLaunchKernelGGL(k_gk_out, dim3(1), dim3(1), 0, st, c->out, gk_dev);
+    const P4 *q = nullptr;
+    CHK(ensure_valid_at(c, x_dev, kappa, st, &q));
+    CHK(eval_current(c, 0, q, kappa, mu, gx_dev, nullptr, gk_dev, st));
     HIPCHK(hipGetLastError());
     return RCP_OK;
 }
@@ -2645,12 +2667,8 @@ int rcp_energy_dev_static(rcp_ctx *c, const double *x_dev, double kappa, double 
         return fail(RCP_ESTATE,
                     "rcp_energy_dev_static: the neighbour list is not valid at these positions "
                     "and kappa (rebuild it with rcp_neighbor_build or rcp_energy_dev)");
-    EvalOut o;
-    o.part = part;
-    o.gu = nullptr;
-    launch_eval(c->d_ptrs, c->d_state, 0, s.n, x_dev, kappa, o, (int)nb, st);
-    launch_eval_finish(part, (int)nb, kappa, mu, c->d_state, 0, res + 8, st);
-    hipLaunchKernelGGL(k_energy_out, dim3(1), dim3(1), 0, st, res + 8, E_dev);
+    launch_eval(c->d_ptrs, c->d_state, 0, s.n, x_dev, kappa, part, (int)nb, st);
+    launch_eval_finish(part, (int)nb, kappa, mu, c->d_state, 0, res + 8, E_dev, nullptr, st);
     HIPCHK(hipGetLastError());
     return RCP_OK;
 }

@@ -86,3 +86,44 @@ def test_long_rows_and_item_cuts(rcp, orc, k, row_cost, item_work, kind):
         d = np.minimum(d, L - d)
     assert d.max() <= 1e-9 * ex * steps + 4e-16 * L, d.max()
     assert kg == pytest.approx(st.kappa[0], rel=1e-12)
+
+
+@pytest.mark.parametrize("k", [1, 64, 513, 4000])
+@pytest.mark.parametrize("kind", ["plain", "frozen", "walls", "parked"])
+def test_energy_of_long_rows(rcp, orc, k, kind):
+    # the evaluation by work items: 1e-10 per component of the summed
+    # |contributions|, as elsewhere.  "parked": the packing of a census that
+    # finished first has given up its items, and its rows are cut again.
+    d0, x, L = _star(k, 3, 29 + k)
+    frozen = np.zeros(len(d0), np.uint8)
+    bnd = (7, 0) if kind == "walls" else None
+    if kind == "parked":
+        p = rcp.Packing([d0, np.ones(30)], [L, L], 1.0, 0, init="none")
+        p.set_state(x, 1.0, 0)
+        p.set_state(np.random.default_rng(1).random((30, 3)) * L, 1.0, 1)
+        p.inflate_run([rcp.schedule_from_rungs([(1e-4, 1e-4, 0.0, 1.0, b)]) for b in (3, 200)])
+        x, kappa = p.get_state(0)
+    else:
+        p = rcp.Packing(d0, L, 1.0, 0, init="none", boundary=bnd)
+        p.set_state(x, 1.0)
+        kappa = 1.0
+        if kind == "frozen":
+            frozen[0] = 1
+            frozen[2::5] = 1
+            p.set_frozen(frozen)
+    e = p.energy_grad(mu=0.3)
+    p.close()
+    try:
+        if kind == "frozen":
+            orc.set_frozen(frozen)
+        if bnd:
+            orc.set_boundary(*bnd)
+        pi, pj = orc.pairs_brute(x, d0, L, kappa, 0.0, 0.0)
+        r = orc.energy_grad(x, d0, L, kappa, 0.3, pi, pj)
+    finally:
+        orc.set_frozen(None)
+        orc.set_boundary(0, 0)
+    assert e["n_overlap"] == r["n_overlap"] and r["n_overlap"] >= k
+    assert e["E_overlap"] == pytest.approx(r["E_ov"], rel=1e-10)
+    assert e["dE_dkappa_overlap"] == pytest.approx(r["gk_ov"], rel=1e-10)
+    assert np.all(np.abs(e["g"] - r["g"]) <= 1e-10 * r["gscale"])
