@@ -143,7 +143,18 @@ struct PlaceGrid {
     uint64_t mask;       // slots - 1 (a power of two)
     int64_t nc;          // cells per axis
     double inv_w;        // nc / L
+    double dmax;         // largest diameter of the class
+    int64_t end;         // ranks past the class's last
     int32_t any, pad;    // the class has spheres
+};
+// Where a placement stands (device): the round's window [lo, hi) of ranks and
+// its class, the lowest rank of it still unplaced, the rounds so far; fail:
+// a sphere ran out of attempts; done: nothing is left to do.
+struct PlaceState {
+    int64_t lo, hi;
+    unsigned long long first;
+    int64_t rounds;
+    int32_t cls, fail, done, pad;
 };
 constexpr int kPlaceMaxClasses = 64;
 struct PlaceArgs {
@@ -168,8 +179,8 @@ struct PlaceArgs {
     PlaceSlot *ptab;         // the round's proposal table
     uint64_t pmask;
     int64_t pcap;
-    unsigned long long *first;   // lowest rank of the window still unplaced
-    int32_t *fail;               // set when a sphere ran out of attempts
+    int64_t window;          // proposals a round
+    PlaceState *st;
     PlaceGrid grid[kPlaceMaxClasses];
 };
 
@@ -200,9 +211,14 @@ void launch_seat(const SeatArgs &a, int64_t ng, hipStream_t st);
 // elsewhere.
 void launch_set_frozen(const SegPtrs *P, int seg, int64_t n, const uint8_t *mask, hipStream_t st);
 
-// One round over ranks [lo, hi) of class c (clear the proposal table,
-// propose and validate, resolve conflicts and commit).
-void launch_place_round(const PlaceArgs &a, int c, int64_t lo, int64_t hi, hipStream_t st);
+// Before the first round: diameters by sphere (d0) from the records, empty
+// class tables (tcap slots in all), nothing placed, and the sort keys and
+// values whose stable sort ranks the spheres, largest first.
+void launch_place_init(const PlaceArgs &a, const P4 *Q, const int32_t *orig, double *d0,
+                       int64_t tcap, uint64_t *keys, uint32_t *vals, hipStream_t st);
+// One round (move the window and clear the proposal table, propose and
+// validate, resolve conflicts and commit); nothing once the state says done.
+void launch_place_round(const PlaceArgs &a, hipStream_t st);
 
 // -------------------------------------------------------- k_iterate.hip
 // flags bit 0: XCD-aware block order; bit 1: the last block of each packing

@@ -101,6 +101,8 @@ struct Seg {
     std::vector<double> dmax_upto;   // max D0 over classes <= l
     std::vector<double> dmax_lev;    // max D0 in class l
     std::vector<int64_t> lev_count;
+    std::vector<int64_t> pcount;     // placement classes floor(log2(D0 / D0_min)):
+    std::vector<double> pdmax;       // spheres and largest D0 of each
     // device arrays; M, V, ORIG, LEV are double-buffered for the Morton
     // permutation (live set `set`); positions with D0 ping-pong through Q
     P4 *Q[2] = {};
@@ -1288,27 +1290,11 @@ static int place_device(rcp_ctx *c, int k, uint64_t seed, int64_t window, int64_
     CHK(pull_state(c));
     Seg &s = c->segs[k];
     const int64_t n = s.n;
-    const std::vector<double> &d0 = s.d0h;
     const double kappa = c->h_state[k].kappa;   // placement at the current scale
-    // ranks: largest first, ties by index; classes floor(log2(D0 / D0_min))
-    std::vector<int32_t> ord(n);
-    for (int64_t i = 0; i < n; ++i) ord[i] = (int32_t)i;
-    std::stable_sort(ord.begin(), ord.end(), [&](int32_t a, int32_t b) { return d0[a] > d0[b]; });
-    std::vector<int> cls(n);
-    int ncls = 1;
-    for (int64_t r = 0; r < n; ++r) {
-        int e;
-        std::frexp(d0[ord[r]] / s.d0min, &e);
-        cls[r] = std::max(0, e - 1);
-        ncls = std::max(ncls, cls[r] + 1);
-    }
+    // classes floor(log2(D0 / D0_min)), largest first: their counts and
+    // largest diameters from the set-up
+    const int ncls = (int)s.pcount.size();
     if (ncls > kPlaceMaxClasses) return fail(RCP_EINVAL, "size ratio too large for placement");
-    std::vector<int64_t> count(ncls, 0);
-    std::vector<double> dmax(ncls, 0.0);
-    for (int64_t r = 0; r < n; ++r) {
-        count[cls[r]]++;
-        dmax[cls[r]] = std::max(dmax[cls[r]], d0[ord[r]]);
-    }
     PlaceArgs a;
     std::memset(&a, 0, sizeof a);
     a.n = n;
@@ -1321,17 +1307,20 @@ static int place_device(rcp_ctx *c, int k, uint64_t seed, int64_t window, int64_
     a.ncls = ncls;
     a.walls = s.walls;
     a.round = s.round;
-    int64_t tcap = 0;
-    for (int q = 0; q < ncls; ++q) {
+    int64_t tcap = 0, end = 0;
+    for (int q = ncls - 1; q >= 0; --q) {
         PlaceGrid &g = a.grid[q];
-        const double h = kappa * dmax[q] * (1.0 + 1e-12);
+        const double h = kappa * s.pdmax[q] * (1.0 + 1e-12);
         int64_t nc = h > 0 ? (int64_t)std::floor(s.L / h) : 1;
         nc = std::max<int64_t>(1, std::min<int64_t>(nc, (int64_t)1 << 20));
         g.nc = nc;
         g.inv_w = (double)nc / s.L;
-        g.any = count[q] > 0;
+        g.dmax = s.pdmax[q];
+        end += s.pcount[q];
+        g.end = end;
+        g.any = s.pcount[q] > 0;
         uint64_t cap = 16;
-        while (cap < (uint64_t)(2 * count[q] + 2)) cap <<= 1;
+        while (cap < (uint64_t)(2 * s.pcount[q] + 2)) cap <<= 1;
         g.off = tcap;
         g.mask = cap - 1;
         tcap += (int64_t)cap;
@@ -1341,93 +1330,79 @@ static int place_device(rcp_ctx *c, int k, uint64_t seed, int64_t window, int64_
     while (pc < (uint64_t)(2 * W)) pc <<= 1;
     a.pcap = (int64_t)pc;
     a.pmask = pc - 1;
-    // device buffers for the placement only
-    int32_t *d_ord = nullptr, *d_att = nullptr, *d_next = nullptr, *d_pnext = nullptr,
-            *d_fail = nullptr;
-    double *d_d0 = nullptr, *d_x = nullptr, *d_prop = nullptr;
-    uint8_t *d_placed = nullptr, *d_valid = nullptr;
-    PlaceSlot *d_tab = nullptr, *d_ptab = nullptr;
-    unsigned long long *d_first = nullptr;
-    auto release = [&]() {
-        dfree(d_ord); dfree(d_att); dfree(d_next); dfree(d_pnext); dfree(d_fail);
-        dfree(d_d0); dfree(d_x); dfree(d_prop); dfree(d_placed); dfree(d_valid);
-        dfree(d_tab); dfree(d_ptab); dfree(d_first);
+    a.window = W;
+    // one allocation for the placement's arrays, given back at its end; the
+    // ranks are sorted in the list build's buffers
+    size_t off = 0;
+    auto take = [&](size_t bytes) {
+        const size_t o = off;
+        off += (bytes + 255) / 256 * 256;
+        return o;
     };
-    int rc = RCP_OK;
+    const size_t o_tab = take(sizeof(PlaceSlot) * tcap), o_ptab = take(sizeof(PlaceSlot) * a.pcap),
+                 o_d0 = take(8 * n), o_x = take(24 * n), o_prop = take(24 * W),
+                 o_att = take(4 * n), o_next = take(4 * n), o_pnext = take(4 * W),
+                 o_placed = take(n), o_valid = take(W), o_st = take(sizeof(PlaceState)),
+                 o_seg = take(sizeof(SortSeg));
+    const int64_t tiles = (n + kSortTile - 1) / kSortTile;
+    CHK(dgrow(&c->skA, &c->skA_cap, n));
+    CHK(dgrow(&c->skB, &c->skB_cap, n));
+    CHK(dgrow(&c->svA, &c->svA_cap, n));
+    CHK(dgrow(&c->svB, &c->svB_cap, n));
+    CHK(dgrow(&c->shist, &c->shist_cap, 256 * tiles));
+    CHK(dgrow(&c->stot, &c->stot_cap, 256));
+    char *ws = nullptr;
+    CHK(dalloc(&ws, off));
+    double *d0 = (double *)(ws + o_d0), *x = (double *)(ws + o_x);
+    a.tab = (PlaceSlot *)(ws + o_tab);
+    a.ptab = (PlaceSlot *)(ws + o_ptab);
+    a.d0 = d0;
+    a.x = x;
+    a.prop = (double *)(ws + o_prop);
+    a.att = (int32_t *)(ws + o_att);
+    a.next = (int32_t *)(ws + o_next);
+    a.pnext = (int32_t *)(ws + o_pnext);
+    a.placed = (uint8_t *)(ws + o_placed);
+    a.valid = (uint8_t *)(ws + o_valid);
+    a.st = (PlaceState *)(ws + o_st);
+    launch_place_init(a, s.Q[s.cur], s.ORIG[s.set], d0, tcap, c->skA, c->svA, c->stream);
+    SortSeg g;
+    g.k[0] = c->skA;
+    g.k[1] = c->skB;
+    g.v[0] = c->svA;
+    g.v[1] = c->svB;
+    g.n = n;
+    g.t0 = 0;
+    g.nt = tiles;
+    SortSeg *dseg = (SortSeg *)(ws + o_seg);
+    launch_put_segs(dseg, &g, 1, c->stream);
+    const int par = radix_sort_segs(dseg, 1, tiles, 64, true, c->shist, c->stot, c->stream);
+    a.ord = (const int32_t *)(par ? c->svB : c->svA);
+    // the state comes back once for several rounds (three launches each)
+    constexpr int kRounds = 8;
+    PlaceState *h = (PlaceState *)c->h_out;
+    static_assert(sizeof(PlaceState) <= 16 * sizeof(double), "fits the pinned results");
+    hipError_t e = hipSuccess;
     do {
-        if ((rc = dalloc(&d_ord, n)) || (rc = dalloc(&d_att, n)) || (rc = dalloc(&d_next, n)) ||
-            (rc = dalloc(&d_pnext, W)) || (rc = dalloc(&d_fail, 1)) || (rc = dalloc(&d_d0, n)) ||
-            (rc = dalloc(&d_x, 3 * n)) || (rc = dalloc(&d_prop, 3 * W)) ||
-            (rc = dalloc(&d_placed, n)) || (rc = dalloc(&d_valid, W)) ||
-            (rc = dalloc(&d_tab, tcap)) || (rc = dalloc(&d_ptab, a.pcap)) ||
-            (rc = dalloc(&d_first, 1)))
+        for (int r = 0; r < kRounds; ++r) launch_place_round(a, c->stream);
+        if ((e = hipGetLastError()) != hipSuccess ||
+            (e = hipMemcpyAsync(h, a.st, sizeof *h, hipMemcpyDeviceToHost, c->stream)) !=
+                hipSuccess ||
+            (e = hipStreamSynchronize(c->stream)) != hipSuccess)
             break;
-        hipError_t e = hipMemcpyAsync(d_ord, ord.data(), sizeof(int32_t) * n,
-                                      hipMemcpyHostToDevice, c->stream);
-        if (e == hipSuccess)
-            e = hipMemcpyAsync(d_d0, d0.data(), sizeof(double) * n, hipMemcpyHostToDevice,
-                               c->stream);
-        if (e == hipSuccess) e = hipMemsetAsync(d_att, 0, sizeof(int32_t) * n, c->stream);
-        if (e == hipSuccess) e = hipMemsetAsync(d_placed, 0, n, c->stream);
-        if (e == hipSuccess) e = hipMemsetAsync(d_fail, 0, sizeof(int32_t), c->stream);
-        if (e == hipSuccess) e = hipMemsetAsync(d_tab, 0xff, sizeof(PlaceSlot) * tcap, c->stream);
-        if (e != hipSuccess) {
-            rc = fail(RCP_EDEVICE, "placement set-up: %s", hipGetErrorString(e));
-            break;
-        }
-        a.ord = d_ord;
-        a.d0 = d_d0;
-        a.x = d_x;
-        a.att = d_att;
-        a.placed = d_placed;
-        a.next = d_next;
-        a.tab = d_tab;
-        a.prop = d_prop;
-        a.valid = d_valid;
-        a.pnext = d_pnext;
-        a.ptab = d_ptab;
-        a.first = d_first;
-        a.fail = d_fail;
-        int64_t nround = 0;
-        int64_t cb = 0;
-        while (cb < n && rc == RCP_OK) {
-            int64_t ce = cb;
-            while (ce < n && cls[ce] == cls[cb]) ++ce;
-            int64_t lo = cb;
-            while (lo < ce) {
-                const int64_t hi = std::min(lo + W, ce);
-                unsigned long long h_hi = (unsigned long long)hi;
-                if ((e = hipMemcpyAsync(d_first, &h_hi, sizeof h_hi, hipMemcpyHostToDevice,
-                                        c->stream)) != hipSuccess)
-                    break;
-                launch_place_round(a, cls[cb], lo, hi, c->stream);
-                unsigned long long first = 0;
-                int32_t failed = 0;
-                if ((e = hipGetLastError()) != hipSuccess ||
-                    (e = hipMemcpyAsync(&first, d_first, sizeof first, hipMemcpyDeviceToHost,
-                                        c->stream)) != hipSuccess ||
-                    (e = hipMemcpyAsync(&failed, d_fail, sizeof failed, hipMemcpyDeviceToHost,
-                                        c->stream)) != hipSuccess ||
-                    (e = hipStreamSynchronize(c->stream)) != hipSuccess)
-                    break;
-                ++nround;
-                if (failed) {
-                    rc = fail(RCP_EPLACE, "packing %d: a sphere exceeded %lld placement attempts",
-                              k, (long long)max_attempts);
-                    break;
-                }
-                lo = (int64_t)first;
-            }
-            if (e != hipSuccess && rc == RCP_OK)
-                rc = fail(RCP_EDEVICE, "placement: %s", hipGetErrorString(e));
-            cb = ce;
-        }
-        if (rc != RCP_OK) break;
-        if (rounds) *rounds = nround;
-        rc = set_state3(c, k, d_x, kappa, 1);
-    } while (0);
+    } while (!h->done && !h->fail);
+    int rc = RCP_OK;
+    if (e != hipSuccess)
+        rc = fail(RCP_EDEVICE, "placement: %s", hipGetErrorString(e));
+    else if (h->fail)
+        rc = fail(RCP_EPLACE, "packing %d: a sphere exceeded %lld placement attempts", k,
+                  (long long)max_attempts);
+    if (rc == RCP_OK) {
+        if (rounds) *rounds = h->rounds;
+        rc = set_state3(c, k, x, kappa, 1);
+    }
     const hipError_t se = hipStreamSynchronize(c->stream);
-    release();
+    dfree(ws);
     if (rc == RCP_OK && se != hipSuccess)
         return fail(RCP_EDEVICE, "placement: %s", hipGetErrorString(se));
     return rc;
@@ -1489,10 +1464,19 @@ static int seg_setup(rcp_ctx *c, int k, int64_t n, const double *d0, double L, d
     const int p = std::max(1, c->params.level_ratio_pow2);
     std::vector<int> cls(n);
     int ncls = 1;
+    s.pcount.clear();
+    s.pdmax.clear();
     for (int64_t i = 0; i < n; ++i) {
         int e;
         std::frexp(d0[i] / s.d0min, &e);
-        cls[i] = std::max(0, e - 1) / p;
+        const size_t pc = (size_t)std::max(0, e - 1);
+        if (pc >= s.pcount.size()) {
+            s.pcount.resize(pc + 1, 0);
+            s.pdmax.resize(pc + 1, 0.0);
+        }
+        s.pcount[pc]++;
+        s.pdmax[pc] = std::max(s.pdmax[pc], d0[i]);
+        cls[i] = (int)pc / p;
         if (cls[i] >= 4 * kMaxLevels) return fail(RCP_EINVAL, "size ratio too large");
         ncls = std::max(ncls, cls[i] + 1);
     }

@@ -62,3 +62,20 @@ def test_device_placement_init_mode(rcp, orc):
     p.close()
     xo, _ = orc.rsa_rounds(d0, L, 1.0, seed, rcp._lib.RCP_PLACE_WINDOW)
     assert np.array_equal(xg, xo)
+
+
+@pytest.mark.parametrize("big", [0.30, 0.34, 0.42, 0.45])
+@pytest.mark.parametrize("window", [1, 7, 4096])
+def test_device_placement_few_cells_per_axis(rcp, orc, big, window):
+    # a sphere of 0.3 to 0.45 of the box: three cells per axis in its class's
+    # grid, or two (every cell is then searched once), next to classes of
+    # many; equal diameters rank by index
+    L = 20.0
+    d0 = np.concatenate([np.full(300, 0.5), [big * L], np.full(60, 1.3), np.linspace(0.6, 0.9, 40)])
+    p = rcp.Packing(d0, L, 1.0, 0, init="none")
+    r = p.place_device(11, window)
+    x, _ = p.get_state()
+    p.close()
+    xo, ro = orc.rsa_rounds(d0, L, 1.0, 11, window)
+    assert r == ro
+    assert np.array_equal(x, xo)
