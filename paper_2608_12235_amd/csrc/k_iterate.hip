@@ -426,6 +426,38 @@ __device__ __forceinline__ Part4 load_part(const Part4 *p)
     return kCoherent ? load_part_coherent(p) : *p;
 }
 
+// Packings of up to kPreMax blocks: their partials are added by 256 threads,
+// four each, wherever that happens (here, or at the start of the next
+// iteration's kernel), so that the sums have the same bits.
+constexpr int kPreMax = 4 * kBlock;
+
+struct Part4x4 {
+    Part4 p[4];
+};
+
+__device__ __forceinline__ Part4x4 load_small(int nb, int64_t b0, const double *partials)
+{
+    const Part4 *P = reinterpret_cast<const Part4 *>(partials) + b0;
+    const int t = threadIdx.x;
+    Part4x4 r;
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+        r.p[k] = Part4{0, 0, 0, 0};
+        if (k * kBlock < nb && t < kBlock && t + k * kBlock < nb) r.p[k] = P[t + k * kBlock];
+    }
+    return r;
+}
+
+__device__ __forceinline__ Part4 add_small(const Part4x4 &r)
+{
+    Part4 a;
+    a.e = (r.p[0].e + r.p[1].e) + (r.p[2].e + r.p[3].e);
+    a.s = (r.p[0].s + r.p[1].s) + (r.p[2].s + r.p[3].s);
+    a.m = fmax(fmax(r.p[0].m, r.p[1].m), fmax(r.p[2].m, r.p[3].m));
+    a.d = fmax(fmax(r.p[0].d, r.p[1].d), fmax(r.p[2].d, r.p[3].d));
+    return a;
+}
+
 // This thread's share of a packing's block partials: partials t, t + kT,
 // t + 2 kT, ... in rounds of eight whose loads are all in flight together,
 // combined in a fixed order.
@@ -888,93 +920,145 @@ __device__ __forceinline__ double group_sum(double v, int sh)
     return v;
 }
 
-// A block one of whose items has more entries than this takes its items one
-// after the other with all four waves, each wave every fourth round: rows are
-// not cut, so an item grows past its share (256 units by default) only by
-// one long row, and a wave alone would take it at about 2 us per round of
-// 64 (on 1.2e5 spheres around frozen ones, rows of up to 2006: 48 us with
-// the split, 72 us without; with the limit at 256 dense lists' ordinary
-// items split too: 22 against 15 us on 1e5 spheres).
-constexpr int kSplit = 512;
+// A block whose items have more entries than this together takes them one
+// after the other with all four waves, each wave every fourth round: rows
+// are not cut, so by default an item grows past its 256 units only by one
+// long row, and a wave alone would take it at about 2 us per round of 64 (on
+// 1.2e5 spheres around frozen ones, rows of up to 2006: 48 us with the split,
+// 72 us without; where dense lists' ordinary items split too, 22 against 15
+// us on 1e5 spheres).
+constexpr int kSplit = 1536;
 
-// Gradient of the rows of this wave's item of the block's four WB: row k's
+// What a block of the wave kernels must know before its first vector load,
+// read as one batch of scalar loads: left to themselves these reads, each
+// behind a branch or an address that depends on the one before, make a chain
+// of six (41.6 against 39.4 us on 1e6 spheres, 9.1 against 8.7 on 8784).
+struct BlockHead {
+    WorkItem w;              // this wave's item
+    int32_t e0, e1;          // entries of the block's four
+    int32_t flags, cur, nb;  // of the packing
+    int64_t bfirst;
+    const P4 *qa, *qb;       // its position buffers and list
+    const int32_t *rp, *col;
+    const uint8_t *rlo;
+};
+
+__device__ __forceinline__ BlockHead block_head(const SegPtrs *P, const SegState *s, int seg,
+                                                const WorkItem *WB, int wv)
+{
+    BlockHead h;
+    h.w = WB[wv];
+    h.e0 = WB[0].e0;
+    h.e1 = WB[kWavesPerBlock - 1].e1;
+    h.flags = s->flags;
+    h.cur = s->cur;
+    h.nb = s->nblocks;
+    h.bfirst = s->bfirst;
+    const SegPtrs &t = P[seg];
+    h.qa = t.p[0];
+    h.qb = t.p[1];
+    h.rp = t.rp;
+    h.col = t.col;
+    h.rlo = t.rlo;
+    // every value is needed here: the loads are issued together, ahead of
+    // one wait (the statement itself is empty)
+    asm volatile(""
+                 : "+s"(h.w.e0), "+s"(h.w.e1), "+s"(h.w.begin), "+s"(h.w.end), "+s"(h.e0),
+                   "+s"(h.e1), "+s"(h.flags), "+s"(h.cur), "+s"(h.nb), "+s"(h.bfirst), "+s"(h.qa),
+                   "+s"(h.qb), "+s"(h.rp), "+s"(h.col), "+s"(h.rlo));
+    return h;
+}
+
+// Gradient of the rows of this wave's item w of the block's four WB: row k's
 // in lane k's g, over the positions Q and the list (rp, col, rlo).  Energy,
 // kappa-gradient, largest-overlap (and, kCount, contact) terms are added to a
 // (per lane; their sum over the block is the block's).  Every thread of the
 // block must call it.
-template <bool kCount, bool kMixed, int kDim>
-__device__ __forceinline__ void block_gradient(const P4 *__restrict__ Q, const int32_t *rp,
+// hook() runs once, after the first item's loads are issued and before the
+// first pair term: it may set kappa, box and iLa, and when it returns false
+// nothing further is done and neither is the caller to.
+struct AlwaysTrue {
+    __device__ bool operator()() const { return true; }
+};
+
+template <bool kCount, bool kMixed, int kDim, class Hook = AlwaysTrue>
+__device__ __forceinline__ bool block_gradient(const P4 *__restrict__ Q, const int32_t *rp,
                                                const int32_t *pcol, const uint8_t *prlo,
-                                               const WorkItem *WB, double kappa, double box,
+                                               const WorkItem *WB, WorkItem w, bool split,
+                                               const double &kappa, const double &box,
                                                const double (&iLa)[3], ItemsLds &L, Acc &a,
-                                               double (&g)[3])
+                                               double (&g)[3], Hook hook = Hook())
 {
     const int lane = threadIdx.x & (kWave - 1);
     const int wv = __builtin_amdgcn_readfirstlane((int)threadIdx.x / kWave);
-    bool split = false;
-#pragma unroll
-    for (int i = 0; i < kWavesPerBlock; ++i) split = split || WB[i].e1 - WB[i].e0 > kSplit;
     const int first = split ? wv : 0, step = split ? kWavesPerBlock : 1;
     WaveLds &M = L.w[wv];
+    bool hooked = false;
 #pragma unroll 1
     for (int i = split ? 0 : wv;;) {
-        const WorkItem w = WB[i];
+        if (split) w = WB[i];
         const int nrow = (int)(w.end - w.begin);
         const int32_t ne = w.e1 - w.e0;
         g[0] = g[1] = g[2] = 0.0;    // this lane's part of its row's gradient
         // lanes per row: 2^sh, the most that give every row its lanes
         const int sh = nrow > 1 ? __builtin_clz((unsigned)(nrow - 1)) - 26 : 6;
-        if (ne > 0) {
-            // This lane's entries: j1, r1 of the next round, q0, r0 (record,
-            // row) of the round at hand.  Past the item's end its last
-            // entry and row are read again, so that no load needs a branch.
-            const int32_t el = ne - 1;
-            const int32_t *col = pcol + w.e0;
-            const uint8_t *rlo = prlo + w.e0;
-            const int32_t k0 = first * kWave + lane, kst = step * kWave;
-            const int32_t j0 = gload(col, min(k0, el));
-            uint32_t r0 = gload(rlo, min(k0, el));
-            int32_t j1 = gload(col, min(k0 + kst, el));
-            uint32_t r1 = gload(rlo, min(k0 + kst, el));
-            const int64_t ro = w.begin + min(lane, nrow - 1);
-            const P4 oq = load_p4(Q, (int32_t)ro);
-            const int32_t rpt = gload(rp, ro) - w.e0;
-            P4 q0 = load_p4(Q, j0);
-            M.own[lane] = oq;
-            M.srp[lane] = lane < nrow ? rpt : ne;
-            if (lane == 0) M.srp[kWave] = ne;
+        // This lane's entries: j1, r1 of the next round, q0, r0 (record, row)
+        // of the round at hand.  Past the item's end its last entry and row
+        // are read again, so that no load needs a branch (an item without
+        // entries reads the list's next one, or its padding, and gathers
+        // sphere 0; one without rows starts at row 1 or later and reads the
+        // row before it).
+        const bool any = ne > 0;
+        const int32_t el = any ? ne - 1 : 0;
+        const int32_t *col = pcol + w.e0;
+        const uint8_t *rlo = prlo + w.e0;
+        const int32_t k0 = first * kWave + lane, kst = step * kWave;
+        const int32_t j0 = gload(col, min(k0, el));
+        uint32_t r0 = gload(rlo, min(k0, el));
+        int32_t j1 = gload(col, min(k0 + kst, el));
+        uint32_t r1 = gload(rlo, min(k0 + kst, el));
+        const int64_t ro = w.begin + min(lane, nrow - 1);
+        const P4 oq = load_p4(Q, (int32_t)ro);
+        const int32_t rpt = gload(rp, ro) - w.e0;
+        P4 q0 = load_p4(Q, any ? j0 : 0);
+        M.own[lane] = oq;
+        M.srp[lane] = lane < nrow ? rpt : ne;
+        if (lane == 0) M.srp[kWave] = ne;
+        if (!hooked) {
+            hooked = true;
+            if (!hook()) return false;
+        }
+        __builtin_amdgcn_wave_barrier();
+        const int row = lane >> sh, sub = lane & ((1 << sh) - 1);
+        const int32_t rb = M.srp[row], re = M.srp[row + 1];
+        for (int32_t base = first * kWave; base < ne; base += kst) {
+            const uint32_t own = (r0 - (uint32_t)w.begin) & (kWave - 1);
+            const P4 q1 = load_p4(Q, j1);
+            r0 = r1;
+            j1 = gload(col, min(base + 2 * kst + lane, el));
+            r1 = gload(rlo, min(base + 2 * kst + lane, el));
+            if (base + lane < ne) {
+                a.gx = a.gy = a.gz = 0.0;
+                pair_term<kCount, kMixed, kDim>(a, M.own[own], q0, kappa, box, iLa);
+                M.F[0][lane] = a.gx;
+                M.F[1][lane] = a.gy;
+                if (kDim == 3) M.F[2][lane] = a.gz;
+            }
             __builtin_amdgcn_wave_barrier();
-            const int row = lane >> sh, sub = lane & ((1 << sh) - 1);
-            const int32_t rb = M.srp[row], re = M.srp[row + 1];
-            for (int32_t base = first * kWave; base < ne; base += kst) {
-                const uint32_t own = (r0 - (uint32_t)w.begin) & (kWave - 1);
-                const P4 q1 = load_p4(Q, j1);
-                r0 = r1;
-                j1 = gload(col, min(base + 2 * kst + lane, el));
-                r1 = gload(rlo, min(base + 2 * kst + lane, el));
-                if (base + lane < ne) {
-                    a.gx = a.gy = a.gz = 0.0;
-                    pair_term<kCount, kMixed, kDim>(a, M.own[own], q0, kappa, box, iLa);
-                    M.F[0][lane] = a.gx;
-                    M.F[1][lane] = a.gy;
-                    if (kDim == 3) M.F[2][lane] = a.gz;
-                }
-                __builtin_amdgcn_wave_barrier();
-                const int32_t hi = min(re - base, kWave);
-                for (int32_t k = max(rb - base, 0) + sub; k < hi; k += 1 << sh) {
-                    g[0] += M.F[0][k];
-                    g[1] += M.F[1][k];
-                    if (kDim == 3) g[2] += M.F[2][k];
-                }
-                __builtin_amdgcn_wave_barrier();
-                q0 = q1;
+            const int32_t hi = min(re - base, kWave);
+            for (int32_t k = max(rb - base, 0) + sub; k < hi; k += 1 << sh) {
+                g[0] += M.F[0][k];
+                g[1] += M.F[1][k];
+                if (kDim == 3) g[2] += M.F[2][k];
             }
-            if (sh > 0) {
-                // across the row's lanes, then to lane `row`
+            __builtin_amdgcn_wave_barrier();
+            q0 = q1;
+        }
+        if (sh > 0) {
+            // across the row's lanes, then to lane `row`
 #pragma unroll
-                for (int d = 0; d < kDim; ++d)
-                    g[d] = __shfl(group_sum(g[d], sh), (lane << sh) & 63, kWave);
-            }
+            for (int d = 0; d < kDim; ++d)
+                g[d] = __shfl(group_sum(g[d], sh), (lane << sh) & 63, kWave);
         }
         if (!split) break;
         // the four waves' sums of a row meet at the item's own wave, in wave
@@ -995,14 +1079,30 @@ __device__ __forceinline__ void block_gradient(const P4 *__restrict__ Q, const i
             break;
         }
     }
+    return true;
 }
 
-template <bool kMixed, bool kWalls, int kDim>
+// A double every lane of the wave holds alike, in scalar registers.
+__device__ __forceinline__ double uniform_f64(double v) { return readlane_f64(v, 0); }
+
+// kPre: the block first does the tail of the iteration before (record S,
+// partial sums pin) for itself: every block of a packing reduces the sums and
+// runs the step on kappa and the schedule in LDS, in the shadow of its first
+// gathers; the packing's first block writes the new record to So.  Then an
+// iteration is one launch instead of two: 8.5 us on 512 spheres where the two
+// take 7.7 + 4.1 and a gap of about 2, 14.9 on 1e5 (1021 blocks) where they
+// take 13.3 + 4.6.  Up to kPreMax blocks in all: every block reads all its
+// packing's partials, and the step's registers (110) leave four waves per
+// SIMD, at which 1024 blocks are all resident; a census of 1200 blocks takes
+// 20.0 us this way against 17.3 + 4.8.
+template <bool kMixed, bool kWalls, int kDim, bool kPre>
 __global__ __launch_bounds__(kBlock) void
-k_iterate_wave(const SegPtrs *__restrict__ P, SegState *__restrict__ S,
-               const WorkItem *__restrict__ W, double *__restrict__ partials, int flags)
+k_iterate_wave(const SegPtrs *__restrict__ P, const SegState *__restrict__ S,
+               SegState *__restrict__ So, const WorkItem *__restrict__ W,
+               const double *__restrict__ pin, double *__restrict__ partials, int flags)
 {
     __shared__ ItemsLds L;
+    __shared__ SegState ls[1];   // kPre only
     const int b = (flags & 1) ? remap_block((int)blockIdx.x, (int)gridDim.x) : (int)blockIdx.x;
     const int lane = threadIdx.x & (kWave - 1);
     const int wv = __builtin_amdgcn_readfirstlane((int)threadIdx.x / kWave);
@@ -1010,20 +1110,70 @@ k_iterate_wave(const SegPtrs *__restrict__ P, SegState *__restrict__ S,
     // the same packing for every item of a block (0 when there is only one:
     // its record is then read alongside the items, not after them)
     const int seg = (flags & 8) ? 0 : WB->seg;
-    SegState *s = S + seg;
-    const bool idle = (s->flags & F_IDLE) != 0;
+    const SegState *s = S + seg;
+    const BlockHead h = block_head(P, s, seg, WB, wv);
+    const bool idle = (h.flags & F_IDLE) != 0;
+    // the tail turns the position buffers unless it makes the packing idle
+    const int cur = kPre ? h.cur ^ 1 : h.cur;
+    constexpr int kWords = (int)(sizeof(SegState) / 8);
+    static_assert(kWords <= kBlock, "the record is copied in one pass");
+    const bool lead = kPre && b == (int)h.bfirst;
+    const uint64_t *src = reinterpret_cast<const uint64_t *>(s);
+    uint64_t *dst = reinterpret_cast<uint64_t *>(So + seg);
+    if (idle) {
+        if (lead && threadIdx.x < kWords) dst[threadIdx.x] = src[threadIdx.x];
+        return;
+    }
+    Part4x4 mine;
+    uint64_t word = 0;
+    if (kPre) {
+        mine = load_small(h.nb, h.bfirst, pin);
+        if (threadIdx.x < kWords) word = gload(src, threadIdx.x);
+    }
+    const P4 *q = cur ? h.qb : h.qa;
     IterScalars c;
-    load_scalars<kWalls>(s, c);
-    const IterPtrs p = select_ptrs(P, seg, s->cur);
-    if (idle) return;
+    // (read behind the first vector loads)
+    auto scalars = [&]() -> bool {
+        load_scalars<kWalls>(s, c);
+        if (!kPre) return true;
+        const Part4 t = add_small(mine);
+        const double e = wave_sum_dpp(t.e), sd = wave_sum_dpp(t.s);
+        const double m = wave_max_dpp(t.m), d = wave_max_dpp(t.d);
+        uint64_t *lw = reinterpret_cast<uint64_t *>(ls);
+        if (threadIdx.x < kWords) lw[threadIdx.x] = word;
+        if (lane == 0) {
+            L.red[wv][0] = e;
+            L.red[wv][1] = sd;
+            L.red[wv][2] = m;
+            L.red[wv][3] = d;
+        }
+        __syncthreads();
+        if (threadIdx.x == 0)
+            tail_logic(ls, (L.red[0][0] + L.red[1][0]) + (L.red[2][0] + L.red[3][0]),
+                       (L.red[0][1] + L.red[1][1]) + (L.red[2][1] + L.red[3][1]),
+                       fmax(fmax(L.red[0][2], L.red[1][2]), fmax(L.red[2][2], L.red[3][2])),
+                       fmax(fmax(L.red[0][3], L.red[1][3]), fmax(L.red[2][3], L.red[3][3])));
+        __syncthreads();
+        if (lead && threadIdx.x < kWords) dst[threadIdx.x] = lw[threadIdx.x];
+        c.kappa = uniform_f64(ls->kappa);
+        c.ib1 = uniform_f64(ls->ib1n);
+        c.ib2 = uniform_f64(ls->ib2n);
+        c.eta = uniform_f64(ls->eta_x);
+        return (__builtin_amdgcn_readfirstlane(ls->flags) & F_IDLE) == 0;
+    };
     Acc a = {0, 0, 0, 0, 0, 0, 0};   // e, s, m: this lane's totals
     double g[3];
     __builtin_amdgcn_s_setprio(2);
-    block_gradient<false, kMixed, kDim>(p.q, p.rp, p.col, p.rlo, WB, c.kappa, c.L, c.iLa, L, a, g);
+    if (!block_gradient<false, kMixed, kDim>(q, h.rp, h.col, h.rlo, WB, h.w, h.e1 - h.e0 > kSplit,
+                                             c.kappa, c.L, c.iLa, L, a, g, scalars))
+        return;
+    IterPtrs p = select_ptrs(P, seg, cur);
+    p.q = q;
+    p.qo = const_cast<P4 *>(cur ? h.qa : h.qb);
     __builtin_amdgcn_s_setprio(0);
     double bd = 0;
-    const int64_t io = WB[wv].begin + lane;
-    if (io < WB[wv].end) {
+    const int64_t io = h.w.begin + lane;
+    if (io < h.w.end) {
         const P4 oq = load_p4(p.q, (int32_t)io);
         const Pre pre = preload<kDim>(p, io);
         if (kWalls) {
@@ -1162,12 +1312,40 @@ static void launch_one(const SegPtrs *P, SegState *S, const WorkItem *W, double 
                        W, partials, f);
 }
 
-template <bool kMixed, bool kWalls, int kDim>
-static void launch_wave(const SegPtrs *P, SegState *S, const WorkItem *W, double *partials,
-                        int nitems, int f, hipStream_t st)
+template <bool kPre>
+static void launch_wave(const SegPtrs *P, const SegState *S, SegState *So, const WorkItem *W,
+                        const double *pin, double *partials, int nitems, int flags, hipStream_t st)
 {
-    hipLaunchKernelGGL((k_iterate_wave<kMixed, kWalls, kDim>), dim3(nitems), dim3(kBlock), 0, st,
-                       P, S, W, partials, f);
+    const int f = flags & 13;
+    const dim3 g(nitems), t(kBlock);
+#define RCP_WAVE(mixed, walls, dim)                                                            \
+    hipLaunchKernelGGL((k_iterate_wave<mixed, walls, dim, kPre>), g, t, 0, st, P, S, So, W, pin, \
+                       partials, f)
+    if (flags & 64) {
+        if (flags & 32) RCP_WAVE(false, true, 2);
+        else if (flags & 16) RCP_WAVE(true, false, 2);
+        else RCP_WAVE(false, false, 2);
+    } else if (flags & 32)
+        RCP_WAVE(false, true, 3);
+    else if (flags & 16)
+        RCP_WAVE(true, false, 3);
+    else
+        RCP_WAVE(false, false, 3);
+#undef RCP_WAVE
+}
+
+bool iterate_takes_waves(int flags)
+{
+    return (flags & (16 | 32 | 64)) || !(((flags >> 8) & 63) || (flags & 2));
+}
+
+int max_pre_blocks() { return kPreMax; }
+
+void launch_iterate_pre(const SegPtrs *P, const SegState *S, SegState *So, const WorkItem *W,
+                        const double *pin, double *partials, int nitems, int flags,
+                        hipStream_t st)
+{
+    launch_wave<true>(P, S, So, W, pin, partials, nitems, flags, st);
 }
 
 template <bool kF, int kW>
@@ -1235,16 +1413,8 @@ void launch_iterate(const SegPtrs *P, SegState *S, const WorkItem *W, double *pa
     // the variant); bits 8-13: kernel variant (see launch_variant; the wave
     // kernel when none of them is set and the tail is not fused)
     const int f = flags & 13, variant = (flags >> 8) & 63;
-    if (flags & 64) {
-        if (flags & 32) launch_wave<false, true, 2>(P, S, W, partials, nitems, f, st);
-        else if (flags & 16) launch_wave<true, false, 2>(P, S, W, partials, nitems, f, st);
-        else launch_wave<false, false, 2>(P, S, W, partials, nitems, f, st);
-    } else if (flags & 32)
-        launch_wave<false, true, 3>(P, S, W, partials, nitems, f, st);
-    else if (flags & 16)
-        launch_wave<true, false, 3>(P, S, W, partials, nitems, f, st);
-    else if (variant == 0 && !(flags & 2))
-        launch_wave<false, false, 3>(P, S, W, partials, nitems, f, st);
+    if (iterate_takes_waves(flags))
+        launch_wave<false>(P, S, nullptr, W, nullptr, partials, nitems, flags, st);
     else if (variant & 40) launch_variant<false>(P, S, W, partials, nitems, f, variant, st);
     else if (flags & 2) launch_variant<true>(P, S, W, partials, nitems, f, variant, st);
     else launch_variant<false>(P, S, W, partials, nitems, f, variant, st);
@@ -1256,31 +1426,45 @@ constexpr int kTailBlock = 1024;
 // parallel pass, the tail works on the copy (its many dependent reads and
 // writes then cost LDS latency, not memory latency) and the block writes the
 // record back.
-__global__ __launch_bounds__(kTailBlock) void k_tail(SegState *__restrict__ S,
+// The record is read from S and written to So (which may be S).
+// kOne: 1, 2: the only packing, of up to kPreMax blocks or more (its range is
+// then known at the launch); 0: any.
+template <int kOne>
+__global__ __launch_bounds__(kTailBlock) void k_tail(const SegState *S, SegState *So,
                                                     const double *__restrict__ partials,
                                                     int64_t b0, int64_t nb)
 {
     static_assert(sizeof(SegState) % 8 == 0, "SegState is copied in 8-byte words");
     constexpr int kWords = (int)(sizeof(SegState) / 8);
     __shared__ SegState ls;
-    SegState *gs = S + blockIdx.x;
+    const SegState *gs = S + blockIdx.x;
+    // a packing without blocks (finished, its items given up) has no record
+    // in the second set: the one in the first stands
+    if (S != So && So[blockIdx.x].nblocks == 0) return;
     // the partials are loaded before the record is copied, so the two
     // latencies overlap (an idle packing's stale partials are then dropped);
-    // with one packing their range comes with the launch (nb >= 0), so the
-    // loads need not wait for the record
-    if (nb < 0) {
+    // with one packing their range comes with the launch, so the loads need
+    // not wait for the record
+    if (kOne == 0) {
         nb = gs->nblocks;
         b0 = gs->bfirst;
     }
-    const Part4 mine = thread_partials<kTailBlock, false>(nb, b0, partials);
-    uint64_t *src = reinterpret_cast<uint64_t *>(gs);
+    const bool small = kOne == 0 ? nb <= kPreMax : kOne == 1;
+    const Part4 mine = small ? add_small(load_small((int)nb, b0, partials))
+                             : thread_partials<kTailBlock, false>(nb, b0, partials);
+    const uint64_t *src = reinterpret_cast<const uint64_t *>(gs);
+    uint64_t *out = reinterpret_cast<uint64_t *>(So + blockIdx.x);
     uint64_t *dst = reinterpret_cast<uint64_t *>(&ls);
     for (int k = threadIdx.x; k < kWords; k += kTailBlock) dst[k] = src[k];
     __syncthreads();
-    if (ls.flags & F_IDLE) return;
+    if (ls.flags & F_IDLE) {
+        if (S != So)
+            for (int k = threadIdx.x; k < kWords; k += kTailBlock) out[k] = dst[k];
+        return;
+    }
     block_tail<kTailBlock>(&ls, mine);
     __syncthreads();
-    for (int k = threadIdx.x; k < kWords; k += kTailBlock) src[k] = dst[k];
+    for (int k = threadIdx.x; k < kWords; k += kTailBlock) out[k] = dst[k];
 }
 
 // Work items.  Row i of a packing has work coordinate w(i) = rc * i + rp[i]
@@ -1429,11 +1613,16 @@ void launch_set_layout(SegState *S, int nseg, const int64_t *lay, hipStream_t st
                            dim3(kBlock), 0, st, S, nseg, lay);
 }
 
-void launch_tail(SegState *S, const double *partials, int nseg, int64_t b0, int64_t nb,
-                 hipStream_t st)
+void launch_tail(const SegState *S, SegState *So, const double *partials, int nseg, int64_t b0,
+                 int64_t nb, hipStream_t st)
 {
-    if (nseg != 1) b0 = 0, nb = -1;
-    hipLaunchKernelGGL(k_tail, dim3(nseg), dim3(kTailBlock), 0, st, S, partials, b0, nb);
+    const dim3 g(nseg), t(kTailBlock);
+    if (nseg != 1)
+        hipLaunchKernelGGL(k_tail<0>, g, t, 0, st, S, So, partials, (int64_t)0, (int64_t)0);
+    else if (nb <= kPreMax)
+        hipLaunchKernelGGL(k_tail<1>, g, t, 0, st, S, So, partials, b0, nb);
+    else
+        hipLaunchKernelGGL(k_tail<2>, g, t, 0, st, S, So, partials, b0, nb);
 }
 
 __global__ void k_sched_start(SegState *S, int seg, SchedDev q, int reset_adam,
@@ -1571,8 +1760,8 @@ k_eval_wave(const SegPtrs *__restrict__ P, const SegState *__restrict__ S, int s
     const int b = remap_block((int)blockIdx.x, (int)gridDim.x);
     const WorkItem *WB = W + (int64_t)b * kWavesPerBlock;
     const SegState *s = S + seg;
-    const IterPtrs p = select_ptrs(P, seg, s->cur);
-    const P4 *q = Q ? Q : p.q;
+    const BlockHead h = block_head(P, s, seg, WB, wv);
+    const P4 *q = Q ? Q : (h.cur ? h.qb : h.qa);
     const double box = s->L, iL = 1.0 / box;
     const int32_t walls = kWalls ? s->walls : 0, round = kWalls ? s->round : 0;
     double iLa[3];
@@ -1580,9 +1769,10 @@ k_eval_wave(const SegPtrs *__restrict__ P, const SegState *__restrict__ S, int s
     for (int d = 0; d < 3; ++d) iLa[d] = (((walls | round) >> d) & 1) ? 0.0 : iL;
     Acc a = {0, 0, 0, 0, 0, 0, 0};
     double g[3];
-    block_gradient<true, kMixed, 3>(q, p.rp, p.col, p.rlo, WB, kappa, box, iLa, L, a, g);
-    const int64_t i = WB[wv].begin + lane;
-    if (i < WB[wv].end) {
+    (void)block_gradient<true, kMixed, 3>(q, h.rp, h.col, h.rlo, WB, h.w, h.e1 - h.e0 > kSplit,
+                                          kappa, box, iLa, L, a, g);
+    const int64_t i = h.w.begin + lane;
+    if (i < h.w.end) {
         if (kWalls) {
             const P4 qi = load_p4(q, (int32_t)i);
             WallAcc w = {{0.0, 0.0, 0.0}, 0.0, 0.0, 0.0, 0.0};

@@ -232,10 +232,21 @@ void launch_items(const int32_t *rp, int64_t n, int seg, int row_cost, int item_
                   WorkItem *W, int64_t nslots, hipStream_t st);
 void launch_iterate(const SegPtrs *P, SegState *S, const WorkItem *W, double *partials,
                     int nitems, int flags, hipStream_t s);
-// b0, nb: the work-item range of the only packing when nseg == 1 (its
-// layout at launch or capture time), else ignored.
-void launch_tail(SegState *S, const double *partials, int nseg, int64_t b0, int64_t nb,
-                 hipStream_t s);
+// Whether launch_iterate runs the wave kernel for these flags, and the most
+// blocks launch_iterate_pre takes (all packings together).
+bool iterate_takes_waves(int flags);
+int max_pre_blocks();
+// The tail of the iteration before (records S, partials pin), then an
+// iteration: records to So, partials to partials (other memory than S and
+// pin).
+void launch_iterate_pre(const SegPtrs *P, const SegState *S, SegState *So, const WorkItem *W,
+                        const double *pin, double *partials, int nitems, int flags,
+                        hipStream_t st);
+// Records from S to So (may be the same).  b0, nb: the work-item range of
+// the only packing when nseg == 1 (its layout at launch or capture time),
+// else ignored.
+void launch_tail(const SegState *S, SegState *So, const double *partials, int nseg, int64_t b0,
+                 int64_t nb, hipStream_t s);
 // nblocks and bfirst of every packing from lay (2 int64 per packing, device).
 void launch_set_layout(SegState *S, int nseg, const int64_t *lay, hipStream_t s);
 // Start a schedule on segment seg: copy the table, reset the position in it,

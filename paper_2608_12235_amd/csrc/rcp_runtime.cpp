@@ -156,12 +156,12 @@ struct rcp_ctx {
     rcp_tuning tuning{};
     std::vector<Seg> segs;
     SegPtrs *d_ptrs = nullptr;
-    SegState *d_state = nullptr;
+    SegState *d_state = nullptr;    // (and a second set of records, see launch_iterations)
     SegState *h_state = nullptr;    // pinned mirror of d_state
     WorkItem *d_work = nullptr;
     int nitems = 0;
     int64_t items_cap = 0;
-    double *d_partials = nullptr;
+    double *d_partials = nullptr;   // two sets of items_cap
     uint32_t *totals = nullptr;      // small device counters
     // list builds: lane 0 runs on the context's stream, further lanes (for
     // builds of several packings at once) on streams of their own
@@ -240,7 +240,8 @@ static int alloc_cols(Seg &s, int64_t cap)
     dfree(s.col);
     s.rlo = nullptr;
     s.col_cap = 0;
-    CHK(dalloc(&s.col, (size_t)(cap + (cap + 3) / 4)));
+    // (one entry and one byte more than the capacity: see block_gradient)
+    CHK(dalloc(&s.col, (size_t)(cap + (cap + 1 + 3) / 4)));
     s.rlo = (uint8_t *)(s.col + cap);
     s.col_cap = cap;
     return RCP_OK;
@@ -389,7 +390,7 @@ static int build_work(rcp_ctx *c)
         c->d_work = nullptr;
         c->d_partials = nullptr;
         CHK(dalloc(&c->d_work, (size_t)total * kWavesPerBlock));
-        CHK(dalloc(&c->d_partials, 4 * (size_t)total));
+        CHK(dalloc(&c->d_partials, 2 * 4 * (size_t)total));
         c->items_cap = total;
     }
     c->nitems = (int)total;
@@ -788,9 +789,9 @@ static int build_backs(rcp_ctx *c, std::vector<BuildJob> &jobs, const std::vecto
         s.list_est = m;
         s.built = true;
         // the work table holds this list's items; it is laid out again when
-        // it is too small, or more than twice too large (idle items still
-        // cost a launch slot and a partial for the tail to read)
-        B.fill = (slots_for(c, s.n, m) <= B.nslots && slots_for(c, s.n, 2 * m) >= B.nslots) ? 1 : 0;
+        // it is too small, or would do for a list one and a half times as
+        // long (idle items still cost a launch slot and a partial to read)
+        B.fill = (slots_for(c, s.n, m) <= B.nslots && slots_for(c, s.n, m + m / 2) >= B.nslots) ? 1 : 0;
         if (!B.fill) {
             s.slot_entries = m + m / 4;
             *relayout = true;
@@ -986,21 +987,44 @@ static bool tail_fused(const rcp_ctx *c)
     return c->tuning.fused_tail && !c->any_mixed && !c->any_walls && c->dim == 3;
 }
 
-// One iteration: gradient + Adam kernel and tail kernel, bracketed by the
-// slot's three events when the slot is timed.
-static int launch_one_iteration(rcp_ctx *c, int slot)
+// Whether the tail of an iteration runs at the start of the next one's
+// kernel: the wave kernel, no more blocks in all than that form takes (see
+// kPreMax), and no launches to be timed apart.
+static bool tail_ahead(const rcp_ctx *c)
 {
-    const int flags = iterate_flags(c) | (tail_fused(c) ? 2 : 0);
-    const bool timed = slot_timed(c, slot) && 3 * slot + 2 < (int)c->kev.size();
-    if (timed) CHK(record_event(c, c->kev[3 * slot]));
-    if (c->nitems > 0)
-        launch_iterate(c->d_ptrs, c->d_state, c->d_work, c->d_partials, c->nitems, flags,
-                       c->stream);
-    if (timed) CHK(record_event(c, c->kev[3 * slot + 1]));
-    if (!tail_fused(c))
-        launch_tail(c->d_state, c->d_partials, (int)c->segs.size(), c->segs[0].first_item,
-                    c->segs[0].blocks, c->stream);
-    if (timed) CHK(record_event(c, c->kev[3 * slot + 2]));
+    if (c->tuning.time_kernels || tail_fused(c) || !iterate_takes_waves(iterate_flags(c)))
+        return false;
+    return c->nitems <= max_pre_blocks();
+}
+
+// K iterations: gradient + Adam kernel and tail kernel each, bracketed by
+// the slot's three events when the slot is timed.  With the tail ahead,
+// records and partials go back and forth between two sets and only the last
+// tail is a launch of its own; it leaves the records in the first set.
+static int launch_iterations(rcp_ctx *c, int K)
+{
+    const bool fused = tail_fused(c), ahead = tail_ahead(c);
+    const int flags = iterate_flags(c) | (fused ? 2 : 0), ns = (int)c->segs.size();
+    SegState *S[2] = {c->d_state, c->d_state + ns};
+    double *part[2] = {c->d_partials, c->d_partials + 4 * c->items_cap};
+    for (int slot = 0; slot < K; ++slot) {
+        const int now = ahead ? slot & 1 : 0;
+        const bool timed = slot_timed(c, slot) && 3 * slot + 2 < (int)c->kev.size();
+        if (timed) CHK(record_event(c, c->kev[3 * slot]));
+        if (c->nitems > 0) {
+            if (ahead && slot > 0)
+                launch_iterate_pre(c->d_ptrs, S[now ^ 1], S[now], c->d_work, part[now ^ 1],
+                                   part[now], c->nitems, flags, c->stream);
+            else
+                launch_iterate(c->d_ptrs, S[now], c->d_work, part[now], c->nitems, flags,
+                               c->stream);
+        }
+        if (timed) CHK(record_event(c, c->kev[3 * slot + 1]));
+        if (!fused && (!ahead || slot == K - 1))
+            launch_tail(S[now], S[0], part[now], ns, c->segs[0].first_item, c->segs[0].blocks,
+                        c->stream);
+        if (timed) CHK(record_event(c, c->kev[3 * slot + 2]));
+    }
     return RCP_OK;
 }
 
@@ -1049,8 +1073,7 @@ static int graph_for(rcp_ctx *c, int K, hipGraphExec_t *out)
     if (c->tuning.time_kernels) CHK(ensure_kernel_events(c, std::max(1, c->tuning.graph_iters)));
     hipGraph_t g = nullptr;
     HIPCHK(hipStreamBeginCapture(c->stream, hipStreamCaptureModeRelaxed));
-    int rc = RCP_OK;
-    for (int it = 0; it < K && rc == RCP_OK; ++it) rc = launch_one_iteration(c, it);
+    const int rc = launch_iterations(c, K);
     const hipError_t ee = hipStreamEndCapture(c->stream, &g);
     if (rc != RCP_OK) {
         if (g) (void)hipGraphDestroy(g);
@@ -1163,7 +1186,7 @@ static int run_loop(rcp_ctx *c)
             HIPCHK(hipGraphLaunch(gx, c->stream));
             c->stats.graph_launches += 1;
         } else {
-            CHK(launch_one_iteration(c, 0));
+            CHK(launch_iterations(c, 1));
         }
         HIPCHK(hipEventRecord(c->e1, c->stream));
         std::vector<int64_t> prev(c->segs.size());
@@ -1766,7 +1789,7 @@ int rcp_census_init(int dim, int n_prob, const int64_t *n, const double *const *
         }
         if ((rc = scratch_address(&c->scratch)) != RCP_OK) break;
         if ((rc = dalloc(&c->d_ptrs, n_prob)) != RCP_OK) break;
-        if ((rc = dalloc(&c->d_state, n_prob)) != RCP_OK) break;
+        if ((rc = dalloc(&c->d_state, 2 * (size_t)n_prob)) != RCP_OK) break;
         if ((rc = dalloc(&c->totals, 16)) != RCP_OK) break;
         if ((rc = dalloc(&c->out, 16)) != RCP_OK) break;
         if ((e = hipHostMalloc((void **)&c->h_state, sizeof(SegState) * n_prob, 0)) != hipSuccess) {
@@ -2701,8 +2724,8 @@ int rcp_time_iterations(rcp_ctx *c, int64_t n_iters, double *iterate_us, double 
             launch_iterate(c->d_ptrs, c->d_state, c->d_work, c->d_partials, c->nitems, flags,
                            c->stream);
             (void)hipEventRecord(ev[3 * b + 1], c->stream);
-            launch_tail(c->d_state, c->d_partials, ns, c->segs[0].first_item, c->segs[0].blocks,
-                        c->stream);
+            launch_tail(c->d_state, c->d_state, c->d_partials, ns, c->segs[0].first_item,
+                        c->segs[0].blocks, c->stream);
             (void)hipEventRecord(ev[3 * b + 2], c->stream);
         }
         if ((rc = pull_state(c)) != RCP_OK) break;

@@ -127,3 +127,36 @@ def test_energy_of_long_rows(rcp, orc, k, kind):
     assert e["E_overlap"] == pytest.approx(r["E_ov"], rel=1e-10)
     assert e["dE_dkappa_overlap"] == pytest.approx(r["gk_ov"], rel=1e-10)
     assert np.all(np.abs(e["g"] - r["g"]) <= 1e-10 * r["gscale"])
+
+
+@pytest.mark.parametrize("n", [3, 300, 3000, 70000])
+def test_tail_placement_changes_nothing(rcp, n):
+    # the tail at the start of the next kernel (one packing of up to 1024
+    # blocks), as a launch of its own (launches timed, one iteration a
+    # launch), and beside packings of another size that end early and late:
+    # the same bits
+    def packing(ns, **kw):
+        ds = [0.7 + 0.6 * np.random.default_rng(m).random(m) for m in ns]
+        Ls = [float((np.pi / 6 * np.sum(d ** 3) / 0.55) ** (1 / 3)) if m > 3 else 9.0
+              for m, d in zip(ns, ds)]
+        p = rcp.Packing(ds, Ls, 1.0, 0, init="none", params=rcp.make_params(skin_s=0.4),
+                        tuning=rcp.make_tuning(**kw))
+        for k, (m, L) in enumerate(zip(ns, Ls)):
+            p.set_state(np.random.default_rng(100 + m).random((m, 3)) * L, 1.0, k)
+        # rung ends, a cap and a list build fall inside the graphs
+        p.inflate_run([rcp.schedule_from_rungs([(1e-3, 3e-3, 3e-4, 1.0, 9 + m % 5),
+                                                (1e-4, 2e-3, 2e-4, 0.99, 12)]) for m in ns])
+        out = [p.get_state(k) for k in range(len(ns))] + [p.get_optimizer(k) for k in range(len(ns))]
+        p.close()
+        return out
+    a = packing([n])
+    for kw in (dict(graph_iters=1), dict(graph_iters=7), dict(time_kernels=2)):
+        b = packing([n], **kw)
+        assert np.array_equal(a[0][0], b[0][0]) and a[0][1] == b[0][1], kw
+        assert np.array_equal(a[1][0], b[1][0]) and np.array_equal(a[1][1], b[1][1])
+        assert a[1][2] == b[1][2]
+    m = 400 if n < 1000 else 900
+    for kw in (dict(graph_iters=8), dict(graph_iters=8, time_kernels=1)):
+        b = packing([m, n, m + 1], **kw)
+        assert np.array_equal(a[0][0], b[1][0]) and a[0][1] == b[1][1], kw
+        assert np.array_equal(a[1][0], b[4][0]) and a[1][2] == b[4][2]
