@@ -920,14 +920,14 @@ __device__ __forceinline__ double group_sum(double v, int sh)
     return v;
 }
 
-// A block whose items have more entries than this together takes them one
-// after the other with all four waves, each wave every fourth round: rows
-// are not cut, so by default an item grows past its 256 units only by one
-// long row, and a wave alone would take it at about 2 us per round of 64 (on
-// 1.2e5 spheres around frozen ones, rows of up to 2006: 48 us with the split,
-// 72 us without; where dense lists' ordinary items split too, 22 against 15
-// us on 1e5 spheres).
-constexpr int kSplit = 1536;
+// A block whose items have more entries together than six of their size
+// (1536 by default) takes them one after the other with all four waves, each
+// wave every fourth round: rows are not cut, so an item grows past its size
+// only by one long row, and a wave alone would take it at about 2 us per
+// round of 64 (on 1.2e5 spheres around frozen ones, rows of up to 2006: 48
+// us with the split, 72 us without; where dense lists' ordinary items split
+// too, 22 against 15 us on 1e5 spheres).
+constexpr int kSplitItems = 6;
 
 // What a block of the wave kernels must know before its first vector load,
 // read as one batch of scalar loads: left to themselves these reads, each
@@ -963,8 +963,8 @@ __device__ __forceinline__ BlockHead block_head(const SegPtrs *P, const SegState
     // every value is needed here: the loads are issued together, ahead of
     // one wait (the statement itself is empty)
     asm volatile(""
-                 : "+s"(h.w.e0), "+s"(h.w.e1), "+s"(h.w.begin), "+s"(h.w.end), "+s"(h.e0),
-                   "+s"(h.e1), "+s"(h.flags), "+s"(h.cur), "+s"(h.nb), "+s"(h.bfirst), "+s"(h.qa),
+                 : "+s"(h.w.e0), "+s"(h.w.e1), "+s"(h.w.split), "+s"(h.w.begin), "+s"(h.w.end),
+                   "+s"(h.e0), "+s"(h.e1), "+s"(h.flags), "+s"(h.cur), "+s"(h.nb), "+s"(h.bfirst), "+s"(h.qa),
                    "+s"(h.qb), "+s"(h.rp), "+s"(h.col), "+s"(h.rlo));
     return h;
 }
@@ -1164,7 +1164,7 @@ k_iterate_wave(const SegPtrs *__restrict__ P, const SegState *__restrict__ S,
     Acc a = {0, 0, 0, 0, 0, 0, 0};   // e, s, m: this lane's totals
     double g[3];
     __builtin_amdgcn_s_setprio(2);
-    if (!block_gradient<false, kMixed, kDim>(q, h.rp, h.col, h.rlo, WB, h.w, h.e1 - h.e0 > kSplit,
+    if (!block_gradient<false, kMixed, kDim>(q, h.rp, h.col, h.rlo, WB, h.w, h.e1 - h.e0 > h.w.split,
                                              c.kappa, c.L, c.iLa, L, a, g, scalars))
         return;
     IterPtrs p = select_ptrs(P, seg, cur);
@@ -1476,14 +1476,14 @@ __global__ __launch_bounds__(kTailBlock) void k_tail(const SegState *S, SegState
 // holds more than 256 rows.
 __global__ __launch_bounds__(kBlock) void k_items_fill(WorkItem *__restrict__ W, int64_t nslots,
                                                       int seg, const int32_t *__restrict__ rp,
-                                                      int64_t n)
+                                                      int64_t n, int item_work)
 {
     const int64_t b = (int64_t)blockIdx.x * kBlock + threadIdx.x;
     if (b >= nslots) return;
     WorkItem w;
     w.seg = seg;
     w.e0 = w.e1 = rp ? rp[n] : 0;
-    w.pad = 0;
+    w.split = kSplitItems * item_work;
     w.begin = n;
     w.end = n;
     W[b] = w;
@@ -1514,7 +1514,7 @@ void launch_items(const int32_t *rp, int64_t n, int seg, int row_cost, int item_
     if (nslots <= 0) return;
     const unsigned gf = (unsigned)((nslots + kBlock - 1) / kBlock);
     hipLaunchKernelGGL(k_items_fill, dim3(gf), dim3(kBlock), 0, st, W, nslots, seg, rp,
-                       rp ? n : (int64_t)0);
+                       rp ? n : (int64_t)0, item_work);
     if (!rp || n <= 0) return;
     const unsigned gi = (unsigned)((n + kBlock - 1) / kBlock);
     hipLaunchKernelGGL(k_items, dim3(gi), dim3(kBlock), 0, st, rp, n, (int64_t)row_cost,
@@ -1543,7 +1543,7 @@ __global__ __launch_bounds__(kBlock) void k_items_fill_seg(const BackJob *__rest
     WorkItem w;
     w.seg = B.seg;
     w.e0 = w.e1 = B.rp ? B.rp[B.n] : 0;
-    w.pad = 0;
+    w.split = kSplitItems * B.item_work;
     w.begin = B.n;
     w.end = B.n;
     B.W[b] = w;
@@ -1769,7 +1769,7 @@ k_eval_wave(const SegPtrs *__restrict__ P, const SegState *__restrict__ S, int s
     for (int d = 0; d < 3; ++d) iLa[d] = (((walls | round) >> d) & 1) ? 0.0 : iL;
     Acc a = {0, 0, 0, 0, 0, 0, 0};
     double g[3];
-    (void)block_gradient<true, kMixed, 3>(q, h.rp, h.col, h.rlo, WB, h.w, h.e1 - h.e0 > kSplit,
+    (void)block_gradient<true, kMixed, 3>(q, h.rp, h.col, h.rlo, WB, h.w, h.e1 - h.e0 > h.w.split,
                                           kappa, box, iLa, L, a, g);
     const int64_t i = h.w.begin + lane;
     if (i < h.w.end) {

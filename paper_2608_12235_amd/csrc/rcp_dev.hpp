@@ -103,7 +103,7 @@ __host__ __device__ inline void seg_bias_terms(SegState &s)
 struct WorkItem {
     int32_t seg;
     int32_t e0, e1;       // its CSR entries [e0, e1) = [rp[begin], rp[end])
-    int32_t pad;
+    int32_t split;        // entries above which its block's items are shared
     int64_t begin, end;   // its rows
 };
 
