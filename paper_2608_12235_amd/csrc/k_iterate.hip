@@ -1625,11 +1625,26 @@ void launch_tail(const SegState *S, SegState *So, const double *partials, int ns
         hipLaunchKernelGGL(k_tail<2>, g, t, 0, st, S, So, partials, b0, nb);
 }
 
-__global__ void k_sched_start(SegState *S, int seg, SchedDev q, int reset_adam,
-                              int64_t iter_limit)
+__global__ __launch_bounds__(kBlock) void k_start(const SegPtrs *__restrict__ P,
+                                                 SegState *__restrict__ S, SchedDev q0,
+                                                 const SchedDev *__restrict__ qs, int reset_adam,
+                                                 int32_t set_flags, int64_t iter_limit)
 {
+    const int seg = (int)blockIdx.y;
     SegState *s = S + seg;
-    s->sched = q;
+    if (reset_adam) {
+        const SegPtrs &p = P[seg];
+        const int64_t n = s->n, step = (int64_t)gridDim.x * kBlock;
+        for (int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x; i < n; i += step) {
+#pragma unroll
+            for (int a = 0; a < 3; ++a) {
+                gstore(p.m[a], i, 0.0);
+                gstore(p.v[a], i, 0.0);
+            }
+        }
+    }
+    if (blockIdx.x != 0 || threadIdx.x != 0) return;
+    s->sched = qs ? qs[seg] : q0;
     s->rung = 0;
     s->it_rung = 0;
     s->iters = 0;
@@ -1642,15 +1657,19 @@ __global__ void k_sched_start(SegState *S, int seg, SchedDev q, int reset_adam,
         s->mk = 0.0;
         s->vk = 0.0;
     }
-    s->flags &= ~(F_STOP | F_CAP | F_HOLD | F_NONFINITE | F_ABORT);
+    s->flags = (s->flags & ~(F_STOP | F_CAP | F_HOLD | F_NONFINITE | F_ABORT)) | set_flags;
     rung_start(s, 0);
 }
 
-void launch_sched_start(SegState *S, int seg, const SchedDev &q, int reset_adam,
-                        int64_t iter_limit, hipStream_t st)
+void launch_start(const SegPtrs *P, SegState *S, int nseg, int64_t nmax, const SchedDev &q0,
+                  const SchedDev *qs, int reset_adam, int32_t set_flags, int64_t iter_limit,
+                  hipStream_t st)
 {
-    hipLaunchKernelGGL(k_sched_start, dim3(1), dim3(1), 0, st, S, seg, q, reset_adam,
-                       iter_limit);
+    if (nseg <= 0) return;
+    const int64_t want = (nmax + kBlock - 1) / kBlock, most = std::max(1, 8192 / nseg);
+    const unsigned gx = reset_adam ? (unsigned)std::max<int64_t>(1, std::min(want, most)) : 1u;
+    hipLaunchKernelGGL(k_start, dim3(gx, nseg), dim3(kBlock), 0, st, P, S, q0, qs, reset_adam,
+                       set_flags, iter_limit);
 }
 
 __global__ void k_set_flags(SegState *S, int seg, int32_t clear, int32_t set)
@@ -1977,21 +1996,6 @@ void launch_set_frozen(const SegPtrs *P, int seg, int64_t n, const uint8_t *mask
                            0, st, P, seg, n, mask);
 }
 
-__global__ __launch_bounds__(kBlock) void k_set_positions(const SegPtrs *__restrict__ P,
-                                                         int seg, int64_t n,
-                                                         const double *__restrict__ xu, int cur)
-{
-    P4 *Q = cur ? P[seg].p[1] : P[seg].p[0];
-    const int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x;
-    if (i >= n) return;
-    const int64_t u = P[seg].orig[i];
-    P4 q = Q[i];
-    q.x = xu[3 * u];
-    q.y = xu[3 * u + 1];
-    q.z = xu[3 * u + 2];
-    Q[i] = q;
-}
-
 // Adam moments of packing seg between list order and user order (mu, vu:
 // n x 3 row-major): dir 0 copies the list's moments out, dir 1 in.
 __global__ __launch_bounds__(kBlock) void k_moments_io(const SegPtrs *__restrict__ P, int seg,
@@ -2020,15 +2024,6 @@ void launch_moments_io(const SegPtrs *P, int seg, int64_t n, double *mu, double 
     if (n <= 0) return;
     hipLaunchKernelGGL(k_moments_io, dim3((unsigned)((n + kBlock - 1) / kBlock)), dim3(kBlock), 0,
                        st, P, seg, n, mu, vu, dir);
-}
-
-void launch_set_positions(const SegPtrs *P, SegState *S, int seg, int64_t n, const double *xu,
-                          int cur, hipStream_t st)
-{
-    (void)S;
-    if (n <= 0) return;
-    hipLaunchKernelGGL(k_set_positions, dim3((unsigned)((n + kBlock - 1) / kBlock)), dim3(kBlock),
-                       0, st, P, seg, n, xu, cur);
 }
 
 }  // namespace rcp

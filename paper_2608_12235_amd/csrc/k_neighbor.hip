@@ -81,23 +81,10 @@ __global__ void k_fill_u32(uint32_t *__restrict__ p, int64_t n, uint32_t v)
     if (i < n) p[i] = v;
 }
 
-__global__ void k_fill_f64(double *__restrict__ p, int64_t n, double v)
-{
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < n) p[i] = v;
-}
-
 void launch_fill_u32(uint32_t *p, int64_t n, uint32_t v, hipStream_t s)
 {
     if (n <= 0) return;
     hipLaunchKernelGGL(k_fill_u32, dim3((unsigned)((n + kBlock - 1) / kBlock)), dim3(kBlock), 0, s,
-                       p, n, v);
-}
-
-void launch_fill_f64(double *p, int64_t n, double v, hipStream_t s)
-{
-    if (n <= 0) return;
-    hipLaunchKernelGGL(k_fill_f64, dim3((unsigned)((n + kBlock - 1) / kBlock)), dim3(kBlock), 0, s,
                        p, n, v);
 }
 

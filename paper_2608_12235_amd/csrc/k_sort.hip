@@ -231,13 +231,13 @@ int radix_sort_segs(const SortSeg *sg, int nseg, int64_t ntiles, int nbits, bool
 
 // ------------------------------------------------ positions out of list order
 // Positions of packing seg from list order back into user order (xu:
-// n x 3 row-major), the reverse of k_set_positions; orig is a permutation
+// n x 3 row-major), the reverse of k_set_state; orig is a permutation
 // of [0, n).
 __global__ __launch_bounds__(kBlock) void k_get_positions(const SegPtrs *__restrict__ P,
-                                                         int seg, int64_t n,
-                                                         double *__restrict__ xu, int cur)
+                                                         const SegState *__restrict__ S, int seg,
+                                                         int64_t n, double *__restrict__ xu)
 {
-    const P4 *Q = cur ? P[seg].p[1] : P[seg].p[0];
+    const P4 *Q = S[seg].cur ? P[seg].p[1] : P[seg].p[0];
     const int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x;
     if (i >= n) return;
     const int64_t u = P[seg].orig[i];
@@ -247,12 +247,90 @@ __global__ __launch_bounds__(kBlock) void k_get_positions(const SegPtrs *__restr
     xu[3 * u + 2] = q.z;
 }
 
-void launch_get_positions(const SegPtrs *P, int seg, int64_t n, double *xu, int cur,
+void launch_get_positions(const SegPtrs *P, const SegState *S, int seg, int64_t n, double *xu,
                           hipStream_t st)
 {
     if (n <= 0) return;
     hipLaunchKernelGGL(k_get_positions, dim3((unsigned)((n + kBlock - 1) / kBlock)), dim3(kBlock),
-                       0, st, P, seg, n, xu, cur);
+                       0, st, P, S, seg, n, xu);
+}
+
+// ------------------------------------------------------ state and schedules
+// Positions handed in by the host: in [-L, 2L) and finite, else *bad; wrapped
+// into [0, L) on the axes that have images (bit a of bounded: axis a has
+// none).
+__global__ __launch_bounds__(kBlock) void k_check_positions(double *__restrict__ x, int64_t n3,
+                                                           double L, int bounded,
+                                                           uint32_t *__restrict__ bad)
+{
+    const int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x;
+    if (i >= n3) return;
+    double v = x[i];
+    if (!(v >= -L && v < 2 * L)) {
+        *bad = 1u;
+        return;
+    }
+    if ((bounded >> (int)(i % 3)) & 1) return;
+    if (v < 0) v += L;
+    if (v >= L) v -= L;
+    x[i] = v;
+}
+
+void launch_check_positions(double *x, int64_t n, double L, int bounded, uint32_t *bad,
+                            hipStream_t st)
+{
+    launch_fill_u32(bad, 1, 0u, st);
+    hipLaunchKernelGGL(k_check_positions, dim3((unsigned)((3 * n + kBlock - 1) / kBlock)),
+                       dim3(kBlock), 0, st, x, 3 * n, L, bounded, bad);
+}
+
+// A state handed in (user order xu): positions into the current buffer, zero
+// moments, kappa; the optimiser at its start, no list, on hold.  Nothing if
+// *bad.
+__global__ __launch_bounds__(kBlock) void k_set_state(const SegPtrs *__restrict__ P,
+                                                     SegState *__restrict__ S, int seg, int64_t n,
+                                                     const double *__restrict__ xu, double kappa,
+                                                     const uint32_t *__restrict__ bad)
+{
+    if (bad && *bad) return;
+    const SegPtrs &p = P[seg];
+    SegState *s = S + seg;
+    P4 *Q = s->cur ? p.p[1] : p.p[0];
+    const int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x;
+    if (i < n) {
+        const int64_t u = p.orig[i];
+        P4 q = Q[i];
+        q.x = xu[3 * u];
+        q.y = xu[3 * u + 1];
+        q.z = xu[3 * u + 2];
+        Q[i] = q;
+#pragma unroll
+        for (int a = 0; a < 3; ++a) {
+            p.m[a][i] = 0.0;
+            p.v[a][i] = 0.0;
+        }
+    }
+    if (i == 0) {
+        s->kappa = kappa;
+        s->t = 0;
+        s->b1t = 1.0;
+        s->b2t = 1.0;
+        seg_bias_terms(*s);
+        s->mk = 0.0;
+        s->vk = 0.0;
+        s->it_rung = 0;
+        s->rung = 0;
+        s->iters = 0;
+        s->flags = F_STALE | F_HOLD;
+    }
+}
+
+void launch_set_state(const SegPtrs *P, SegState *S, int seg, int64_t n, const double *xu,
+                      double kappa, const uint32_t *bad, hipStream_t st)
+{
+    if (n <= 0) return;
+    hipLaunchKernelGGL(k_set_state, dim3((unsigned)((n + kBlock - 1) / kBlock)), dim3(kBlock), 0,
+                       st, P, S, seg, n, xu, kappa, bad);
 }
 
 }  // namespace rcp

@@ -130,7 +130,6 @@ void launch_search_seg(const FrontJob *jobs, int J, int64_t nb, int max_nlev, in
 // *out = longest row (max rp[i+1] - rp[i]); out must be zeroed first.
 void launch_max_degree(int64_t n, const int32_t *rp, uint32_t *out, hipStream_t s);
 void launch_fill_u32(uint32_t *p, int64_t n, uint32_t v, hipStream_t s);
-void launch_fill_f64(double *p, int64_t n, double v, hipStream_t s);
 
 // ---------------------------------------------------------- k_place.hip
 // Random sequential addition in rounds (see k_place.hip).
@@ -249,10 +248,13 @@ void launch_tail(const SegState *S, SegState *So, const double *partials, int ns
                  int64_t nb, hipStream_t s);
 // nblocks and bfirst of every packing from lay (2 int64 per packing, device).
 void launch_set_layout(SegState *S, int nseg, const int64_t *lay, hipStream_t s);
-// Start a schedule on segment seg: copy the table, reset the position in it,
-// set the first rung's parameters from the current kappa.
-void launch_sched_start(SegState *S, int seg, const SchedDev &q, int reset_adam,
-                        int64_t iter_limit, hipStream_t s);
+// Start a schedule on every segment (qs[k], device; nullptr: q0 on the only
+// one): copy the table, reset the position in it, set the first rung's
+// parameters from the current kappa; with reset_adam zero moments too (nmax
+// = largest n); the flags set_flags are set.
+void launch_start(const SegPtrs *P, SegState *S, int nseg, int64_t nmax, const SchedDev &q0,
+                  const SchedDev *qs, int reset_adam, int32_t set_flags, int64_t iter_limit,
+                  hipStream_t s);
 void launch_set_flags(SegState *S, int seg, int32_t clear, int32_t set, hipStream_t s);
 
 // Energy terms of one segment at positions given in user order (xu, n x 3
@@ -286,12 +288,16 @@ void launch_disp(const SegPtrs *P, const SegState *S, int seg, int64_t n, const 
 // mu, vu (n x 3 row-major, device).
 void launch_moments_io(const SegPtrs *P, int seg, int64_t n, double *mu, double *vu, int dir,
                        hipStream_t s);
-// Gather user-order positions xu (n x 3) into the current SoA buffer.
-void launch_set_positions(const SegPtrs *P, SegState *S, int seg, int64_t n, const double *xu,
-                          int cur, hipStream_t s);
 // Scatter the current positions into user order xu (n x 3, device).
-void launch_get_positions(const SegPtrs *P, int seg, int64_t n, double *xu, int cur,
+void launch_get_positions(const SegPtrs *P, const SegState *S, int seg, int64_t n, double *xu,
                           hipStream_t s);
+// Check and wrap n positions in place (k_sort.hip); *bad = 1 when one is
+// outside [-L, 2L), else 0.
+void launch_check_positions(double *x, int64_t n, double L, int bounded, uint32_t *bad,
+                            hipStream_t s);
+// A state handed in, unless bad is given and *bad set (k_sort.hip).
+void launch_set_state(const SegPtrs *P, SegState *S, int seg, int64_t n, const double *xu,
+                      double kappa, const uint32_t *bad, hipStream_t s);
 // Shrink to contact: per-block minima of the pair contact scales in
 // part[0..nblocks), their minimum in part[nblocks].
 void launch_shrink(const SegPtrs *P, const SegState *S, int seg, int64_t n, double *part,

@@ -158,6 +158,7 @@ struct rcp_ctx {
     SegPtrs *d_ptrs = nullptr;
     SegState *d_state = nullptr;    // (and a second set of records, see launch_iterations)
     SegState *h_state = nullptr;    // pinned mirror of d_state
+    SchedDev *d_sched = nullptr, *h_sched = nullptr;   // schedules of a batch (device, pinned)
     WorkItem *d_work = nullptr;
     int nitems = 0;
     int64_t items_cap = 0;
@@ -1246,16 +1247,6 @@ static int to_sched(const rcp_schedule *q, SchedDev &d)
     return RCP_OK;
 }
 
-static int reset_moments(rcp_ctx *c, int k)
-{
-    Seg &s = c->segs[k];
-    for (int a = 0; a < 3; ++a) {
-        launch_fill_f64(s.M[s.set][a], s.n, 0.0, c->stream);
-        launch_fill_f64(s.V[s.set][a], s.n, 0.0, c->stream);
-    }
-    return RCP_OK;
-}
-
 // Volume (area in two dimensions) of packing k's domain: L per plain or
 // flat-walled axis, the disk or ball of diameter L over the round axes.
 static double domain_volume(const rcp_ctx *c, const Seg &s)
@@ -1671,6 +1662,8 @@ static void destroy_ctx(rcp_ctx *c)
     if (c->h_out) (void)hipHostFree(c->h_out);
     if (c->h_layout) (void)hipHostFree(c->h_layout);
     dfree(c->d_layout);
+    dfree(c->d_sched);
+    if (c->h_sched) (void)hipHostFree(c->h_sched);
     for (auto &e : c->kev) (void)hipEventDestroy(e);
     c->kev.clear();
     for (auto *v : {&c->rb_pending, &c->rb_pool})
@@ -1817,6 +1810,14 @@ int rcp_census_init(int dim, int n_prob, const int64_t *n, const double *const *
             break;
         }
         if ((rc = dalloc(&c->d_layout, 2 * (size_t)n_prob)) != RCP_OK) break;
+        if (n_prob > 1) {
+            if ((rc = dalloc(&c->d_sched, n_prob)) != RCP_OK) break;
+            if ((e = hipHostMalloc((void **)&c->h_sched, sizeof(SchedDev) * n_prob, 0)) !=
+                hipSuccess) {
+                rc = fail(RCP_ENOMEM, "hipHostMalloc: %s", hipGetErrorString(e));
+                break;
+            }
+        }
         for (int k = 0; k < n_prob && rc == RCP_OK; ++k)
             rc = seg_setup(c, k, n[k], d0[k], box[k], kappa0[k], seeds[k], init_mode);
         if (rc != RCP_OK) break;
@@ -1922,41 +1923,23 @@ static int set_state3(rcp_ctx *c, int k, const double *x, double kappa, int is_d
     Seg &s = c->segs[k];
     if (!x || !(kappa > 0) || !std::isfinite(kappa)) return fail(RCP_EINVAL, "bad state");
     CHK(dgrow(&c->xtmp, &c->xtmp_cap, 3 * s.n));
-    CHK(pull_state(c));
-    if (is_device) {
-        HIPCHK(hipMemcpyAsync(c->xtmp, x, sizeof(double) * 3 * s.n, hipMemcpyDeviceToDevice,
-                              c->stream));
-    } else {
-        std::vector<double> w(x, x + 3 * s.n);
-        const int32_t bounded = s.walls | s.round;
-        for (size_t q = 0; q < w.size(); ++q) {
-            double &v = w[q];
-            if (!std::isfinite(v) || v < -s.L || v >= 2 * s.L)
-                return fail(RCP_EINVAL, "position outside [-L, 2L)");
-            if ((bounded >> (q % 3)) & 1) continue;   // no wrap across walls
-            if (v < 0) v += s.L;
-            if (v >= s.L) v -= s.L;
-        }
-        HIPCHK(hipMemcpyAsync(c->xtmp, w.data(), sizeof(double) * 3 * s.n,
-                              hipMemcpyHostToDevice, c->stream));
-        HIPCHK(hipStreamSynchronize(c->stream));
+    HIPCHK(hipMemcpyAsync(c->xtmp, x, sizeof(double) * 3 * s.n,
+                          is_device ? hipMemcpyDeviceToDevice : hipMemcpyHostToDevice, c->stream));
+    uint32_t *bad = nullptr;
+    if (!is_device) {
+        // positions from the host are checked and wrapped on the device; one
+        // outside the range leaves the packing as it was
+        bad = c->totals + 2;
+        launch_check_positions(c->xtmp, s.n, s.L, s.walls | s.round, bad, c->stream);
     }
-    launch_set_positions(c->d_ptrs, c->d_state, k, s.n, c->xtmp, s.cur, c->stream);
-    CHK(reset_moments(c, k));
-    SegState st = c->h_state[k];
-    st.kappa = kappa;
-    st.t = 0;
-    st.b1t = 1.0;
-    st.b2t = 1.0;
-    seg_bias_terms(st);
-    st.mk = 0;
-    st.vk = 0;
-    st.it_rung = 0;
-    st.rung = 0;
-    st.iters = 0;
-    st.flags = F_STALE | F_HOLD;
-    HIPCHK(hipMemcpyAsync(c->d_state + k, &st, sizeof st, hipMemcpyHostToDevice, c->stream));
-    HIPCHK(hipStreamSynchronize(c->stream));
+    launch_set_state(c->d_ptrs, c->d_state, k, s.n, c->xtmp, kappa, bad, c->stream);
+    HIPCHK(hipGetLastError());
+    uint32_t *h_bad = (uint32_t *)c->h_out;
+    *h_bad = 0;
+    if (bad)
+        HIPCHK(hipMemcpyAsync(h_bad, bad, sizeof *h_bad, hipMemcpyDeviceToHost, c->stream));
+    CHK(pull_state(c));
+    if (*h_bad) return fail(RCP_EINVAL, "position outside [-L, 2L)");
     s.built = false;
     return RCP_OK;
 }
@@ -2159,22 +2142,23 @@ int rcp_get_state(rcp_ctx *c, int k, double *x, double *kappa, double *diam)
 static int get_state3(rcp_ctx *c, int k, double *x, double *kappa, double *diam)
 {
     CHK(check_k(c, k));
-    CHK(pull_state(c));
     Seg &s = c->segs[k];
     const int64_t n = s.n;
     if (!diam) {
-        // positions scattered into user order on the device, one copy out
+        // positions scattered into user order on the device, one copy out,
+        // one wait for it and the record
         if (x && n > 0) {
             CHK(dgrow(&c->xtmp, &c->xtmp_cap, 3 * n));
-            launch_get_positions(c->d_ptrs, k, n, c->xtmp, s.cur, c->stream);
+            launch_get_positions(c->d_ptrs, c->d_state, k, n, c->xtmp, c->stream);
             HIPCHK(hipGetLastError());
             HIPCHK(hipMemcpyAsync(x, c->xtmp, sizeof(double) * 3 * n, hipMemcpyDeviceToHost,
                                   c->stream));
-            HIPCHK(hipStreamSynchronize(c->stream));
         }
+        CHK(pull_state(c));
         if (kappa) *kappa = c->h_state[k].kappa;
         return RCP_OK;
     }
+    CHK(pull_state(c));
     std::vector<P4> q(n);
     std::vector<int32_t> orig(n);
     HIPCHK(hipMemcpy(orig.data(), s.ORIG[s.set], sizeof(int32_t) * n, hipMemcpyDeviceToHost));
@@ -2397,26 +2381,35 @@ int rcp_energy_grad(rcp_ctx *c, int k, double mu, rcp_energy *e, double *grad_x)
 }
 
 // Load a schedule on every packing and set its first rung; with
-// reset_adam the optimiser starts afresh (moments and step counter zero).
+// reset_adam the optimiser starts afresh (moments and step counter zero),
+// with hold every packing waits for rcp_run_continue.  One launch over all
+// packings; nothing is waited for.
 static int start_schedule(rcp_ctx *c, const rcp_schedule *sched, int per_packing,
-                          int64_t max_iters, bool reset_adam = true)
+                          int64_t max_iters, bool reset_adam = true, bool hold = false)
 {
-    CHK(pull_state(c));
-    std::vector<SchedDev> qs(c->segs.size());
-    for (size_t k = 0; k < c->segs.size(); ++k) CHK(to_sched(per_packing ? sched + k : sched, qs[k]));
+    const int ns = (int)c->segs.size();
+    // (the last start's table may still be on its way)
+    if (ns > 1) HIPCHK(hipStreamSynchronize(c->stream));
+    std::vector<SchedDev> qs(ns);
+    for (int k = 0; k < ns; ++k) CHK(to_sched(per_packing ? sched + k : sched, qs[k]));
     // every packing runs again: packings parked by an earlier run get slots
     bool parked = false;
     for (auto &s : c->segs) {
         parked = parked || s.parked;
         s.parked = false;
+        s.err = 0;
     }
     if (parked) CHK(build_work(c));
-    for (size_t k = 0; k < c->segs.size(); ++k) {
-        if (reset_adam) CHK(reset_moments(c, (int)k));
-        c->segs[k].err = 0;
-        launch_sched_start(c->d_state, (int)k, qs[k], reset_adam ? 1 : 0, max_iters, c->stream);
+    int64_t nmax = 0;
+    for (const auto &s : c->segs) nmax = std::max(nmax, s.n);
+    if (ns > 1) {
+        std::memcpy(c->h_sched, qs.data(), sizeof(SchedDev) * ns);
+        HIPCHK(hipMemcpyAsync(c->d_sched, c->h_sched, sizeof(SchedDev) * ns,
+                              hipMemcpyHostToDevice, c->stream));
     }
-    HIPCHK(hipStreamSynchronize(c->stream));
+    launch_start(c->d_ptrs, c->d_state, ns, nmax, qs[0], ns > 1 ? c->d_sched : nullptr,
+                 reset_adam ? 1 : 0, hold ? F_HOLD : 0, max_iters, c->stream);
+    HIPCHK(hipGetLastError());
     return RCP_OK;
 }
 
@@ -2493,12 +2486,7 @@ __global__ void k_extend(SegState *S, int nseg, int64_t n_more)
 int rcp_run_start(rcp_ctx *c, const rcp_schedule *sched, int per_packing)
 {
     if (!c || !sched) return fail(RCP_EINVAL, "null argument");
-    CHK(start_schedule(c, sched, per_packing, 0));
-    // hold every packing until rcp_run_continue
-    for (size_t k = 0; k < c->segs.size(); ++k)
-        launch_set_flags(c->d_state, (int)k, 0, F_HOLD, c->stream);
-    HIPCHK(hipStreamSynchronize(c->stream));
-    return RCP_OK;
+    return start_schedule(c, sched, per_packing, 0, true, true);
 }
 
 int rcp_run_continue(rcp_ctx *c, int64_t n_iters, int32_t *active)
