@@ -2,21 +2,30 @@
 // the neighbour-list build (Morton ordering, entry sort), of several arrays
 // at once.
 //
-// Sort: 8-bit digits, tiles of 2048 keys (256 threads x 8 rounds).  Per pass:
+// Sort: the fewest passes with digits of at most nine bits, all as narrow as
+// that allows; tiles of 2048 keys (256 threads x 8 rounds).  Per pass:
 // per-tile digit histogram -> per digit, an exclusive scan over the tiles
 // and the digit's total (one block per digit) -> stable scatter, which adds
 // the totals of the smaller digits and ranks each key among equal digits of
-// its tile with wave ballots (a 9-bit match over the digit) and per-wave
-// counts in LDS.
+// its wave's 512 with ballots and a counter row of the wave's own in LDS:
+// no barrier between the rounds.
+// A pass over a few tiles is bound by latency: the scatter of four tiles
+// took 8.5 us with eight-bit digits and four barriers a round, 7.1 now.
+// Nine-bit digits save a pass at 17 and 18, 25 to 27, 33 to 36, ... bits.
+// The keys of a tile go through LDS in digit order, so that a wave's stores
+// are runs of several keys.  The whole build of 1e5 spheres (5.2e5 entries):
+// 244 -> 227 us; of 1.2e5 with 3.9e6 entries: 561 -> 505; of 512: 174 -> 155.
 #include "rcp_kernels.hpp"
 
 namespace rcp {
 
 constexpr int kTile = kBlock * 8;   // 2048 items per tile
+constexpr int kMaxDigits = 512;     // two a thread
+static_assert(kTile == kSortTile && kMaxDigits == kSortDigits && kMaxDigits == 2 * kBlock, "");
 
 // ---------------------------------------------------------------- scan
-// Inclusive scan of one value per thread across the block; returns the
-// exclusive prefix and writes the block total to *total.
+// Scans of one value per thread across the block: the exclusive prefix, and
+// the block total in *total.
 __device__ __forceinline__ uint32_t block_exclusive(uint32_t v, uint32_t *total)
 {
     __shared__ uint32_t ws[kWavesPerBlock];
@@ -39,11 +48,35 @@ __device__ __forceinline__ uint32_t block_exclusive(uint32_t v, uint32_t *total)
     return off + inc - v;
 }
 
+__device__ __forceinline__ uint64_t block_exclusive(uint64_t v)
+{
+    __shared__ uint64_t ws[kWavesPerBlock];
+    const int lane = threadIdx.x & (kWave - 1), w = threadIdx.x / kWave;
+    uint64_t inc = v;
+#pragma unroll
+    for (int o = 1; o < kWave; o <<= 1) {
+        const uint64_t u = __shfl_up(inc, o, kWave);
+        if (lane >= o) inc += u;
+    }
+    if (lane == kWave - 1) ws[w] = inc;
+    __syncthreads();
+    uint64_t off = 0;
+    for (int k = 0; k < w; ++k) off += ws[k];
+    return off + inc - v;
+}
+
+// LDS accesses of the wave's lanes before and after stay in that order.
+__device__ __forceinline__ void wave_sync()
+{
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+}
+
 // ---------------------------------------------------------------- sort
 // Several independent arrays (segments) are sorted by one sequence of
 // launches: every launch covers the tiles of all segments, a block finding
 // its segment by binary search over the segments' first tiles.  Histograms
-// are laid out per segment, digit-major: hist[256 t0 + d nt + t].
+// are laid out per segment, digit-major: hist[D t0 + d nt + t], D digits.
 
 // Segment of tile b: the last segment whose first tile is <= b.
 __device__ __forceinline__ int seg_of_tile(const SortSeg *__restrict__ sg, int nseg, int64_t b)
@@ -58,11 +91,13 @@ __device__ __forceinline__ int seg_of_tile(const SortSeg *__restrict__ sg, int n
 }
 
 __global__ __launch_bounds__(kBlock) void k_radix_hist(const SortSeg *__restrict__ sg, int nseg,
-                                                      int par, int shift,
+                                                      int par, int shift, int bits,
                                                       uint32_t *__restrict__ hist)
 {
-    __shared__ uint32_t cnt[256];
+    __shared__ uint32_t cnt[kMaxDigits];
     cnt[threadIdx.x] = 0;
+    cnt[threadIdx.x + kBlock] = 0;
+    const uint32_t D = 1u << bits;
     const int j = seg_of_tile(sg, nseg, blockIdx.x);
     const int64_t n = sg[j].n, t0 = sg[j].t0, nt = sg[j].nt;
     const int64_t t = (int64_t)blockIdx.x - t0;
@@ -82,21 +117,22 @@ __global__ __launch_bounds__(kBlock) void k_radix_hist(const SortSeg *__restrict
 #pragma unroll
     for (int k = 0; k < 8; ++k) {
         const int64_t i = base + k * kBlock + threadIdx.x;
-        if (i < n) atomicAdd(&cnt[(kk[k] >> shift) & 255u], 1u);
+        if (i < n) atomicAdd(&cnt[(uint32_t)(kk[k] >> shift) & (D - 1u)], 1u);
     }
     __syncthreads();
-    hist[256 * t0 + (int64_t)threadIdx.x * nt + t] = cnt[threadIdx.x];
+    for (uint32_t d = threadIdx.x; d < D; d += kBlock)
+        hist[(int64_t)D * t0 + (int64_t)d * nt + t] = cnt[d];
 }
 
 // Block (j, d): exclusive scan, in place, of digit d's tile counts in
-// segment j (tile order), and the digit's total to totals[256 j + d].
-__global__ __launch_bounds__(kBlock) void k_radix_rowscan(const SortSeg *__restrict__ sg,
+// segment j (tile order), and the digit's total to totals[D j + d].
+__global__ __launch_bounds__(kBlock) void k_radix_rowscan(const SortSeg *__restrict__ sg, int bits,
                                                          uint32_t *__restrict__ hist,
                                                          uint32_t *__restrict__ totals)
 {
-    const int j = (int)(blockIdx.x >> 8), d = (int)(blockIdx.x & 255u);
+    const int j = (int)(blockIdx.x >> bits), d = (int)(blockIdx.x & ((1u << bits) - 1u));
     const int64_t nt = sg[j].nt;
-    uint32_t *row = hist + 256 * sg[j].t0 + (int64_t)d * nt;
+    uint32_t *row = hist + (sg[j].t0 << bits) + (int64_t)d * nt;
     uint32_t carry = 0;
     for (int64_t base = 0; base < nt; base += 4 * kBlock) {
         const int64_t i0 = base + (int64_t)threadIdx.x * 4;
@@ -120,69 +156,111 @@ __global__ __launch_bounds__(kBlock) void k_radix_rowscan(const SortSeg *__restr
 
 template <bool kVals>
 __global__ __launch_bounds__(kBlock) void k_radix_scatter(const SortSeg *__restrict__ sg, int nseg,
-                                                         int par, int shift,
+                                                         int par, int shift, int bits,
                                                          const uint32_t *__restrict__ off,
                                                          const uint32_t *__restrict__ totals)
 {
-    __shared__ uint32_t base[256];
-    __shared__ uint32_t wcnt[kWavesPerBlock][257];
-    const int lane = threadIdx.x & (kWave - 1), w = threadIdx.x / kWave;
+    constexpr int R = kTile / kBlock, kWaveTile = kTile / kWavesPerBlock;
+    __shared__ uint32_t cnt[kWavesPerBlock][kMaxDigits];
+    __shared__ uint32_t delta[kMaxDigits];
+    __shared__ uint64_t sk[kTile];
+    __shared__ uint32_t sv[kVals ? kTile : 1];
+    const int tid = (int)threadIdx.x, lane = tid & (kWave - 1), w = tid / kWave;
     const int j = seg_of_tile(sg, nseg, blockIdx.x);
     const int64_t n = sg[j].n, t0 = sg[j].t0, nt = sg[j].nt;
-    const int64_t t = (int64_t)blockIdx.x - t0;
-    const gptr<const uint64_t> kin = (gptr<const uint64_t>)(par ? sg[j].k[1] : sg[j].k[0]);
+    const int64_t t = (int64_t)blockIdx.x - t0, tile = t * kTile;
+    const int m = (int)(n - tile < kTile ? n - tile : kTile);
+    const gptr<const uint64_t> kin = (gptr<const uint64_t>)(par ? sg[j].k[1] : sg[j].k[0]) + tile;
     const gptr<uint64_t> kout = (gptr<uint64_t>)(par ? sg[j].k[0] : sg[j].k[1]);
-    const gptr<const uint32_t> vin = (gptr<const uint32_t>)(par ? sg[j].v[1] : sg[j].v[0]);
+    const gptr<const uint32_t> vin = (gptr<const uint32_t>)(par ? sg[j].v[1] : sg[j].v[0]) + tile;
     const gptr<uint32_t> vout = (gptr<uint32_t>)(par ? sg[j].v[0] : sg[j].v[1]);
+    const uint32_t D = 1u << bits, mask = D - 1u;
     // the tile's keys (and values) are loaded up front, all in flight
-    // together (clamped indices: a tile holds at least one key)
-    const int64_t tile = t * kTile;
-    uint64_t kk[8];
-    uint32_t vv[8];
+    // together, 512 consecutive ones a wave (clamped indices: a tile holds at
+    // least one key)
+    uint64_t kk[R];
+    uint32_t vv[R], pre[R];
 #pragma unroll
-    for (int r = 0; r < 8; ++r) {
-        const int64_t i = tile + r * kBlock + threadIdx.x;
-        const int64_t ic = i < n ? i : n - 1;
+    for (int r = 0; r < R; ++r) {
+        const int i = w * kWaveTile + r * kWave + lane, ic = i < m ? i : m - 1;
         kk[r] = kin[ic];
         vv[r] = kVals ? vin[ic] : 0u;
     }
-    // first position of digit threadIdx.x: the segment's totals of smaller
-    // digits plus this digit's count in its earlier tiles
-    uint32_t all;
-    const uint32_t dbase = block_exclusive(totals[256 * j + threadIdx.x], &all);
-    base[threadIdx.x] = dbase + off[256 * t0 + (int64_t)threadIdx.x * nt + t];
-    const uint64_t lt = (lane == 0) ? 0ull : (~0ull >> (kWave - lane));
+    // this thread's two digits: totals in the segment, counts in earlier tiles
+    const uint32_t d0 = 2u * (uint32_t)tid;
+    uint32_t tot0 = 0, tot1 = 0, off0 = 0, off1 = 0;
+    if (d0 < D) {
+        tot0 = totals[(uint64_t)j * D + d0];
+        off0 = off[(int64_t)D * t0 + (int64_t)d0 * nt + t];
+        if (d0 + 1 < D) {
+            tot1 = totals[(uint64_t)j * D + d0 + 1];
+            off1 = off[(int64_t)D * t0 + (int64_t)(d0 + 1) * nt + t];
+        }
+    }
+    for (int k = tid; k < kWavesPerBlock * kMaxDigits; k += kBlock) (&cnt[0][0])[k] = 0;
+    __syncthreads();
+    // rank among the equal digits of the wave's keys: the rounds before (the
+    // wave's own counters) and the lanes below
+    const uint64_t lt = (1ull << lane) - 1ull;
 #pragma unroll
-    for (int r = 0; r < 8; ++r) {
-        for (int k = threadIdx.x; k < kWavesPerBlock * 257; k += kBlock)
-            (&wcnt[0][0])[k] = 0;
-        __syncthreads();
-        const int64_t i = tile + r * kBlock + threadIdx.x;
-        const bool valid = i < n;
-        uint64_t key = kk[r];
-        uint32_t val = vv[r];
-        uint32_t d = valid ? (uint32_t)((key >> shift) & 255u) : 256u;
-        uint64_t peers = ~0ull;
-#pragma unroll
-        for (int b = 0; b < 9; ++b) {
-            uint32_t bit = (d >> b) & 1u;
-            uint64_t bal = __ballot(bit);
+    for (int r = 0; r < R; ++r) {
+        const bool valid = w * kWaveTile + r * kWave + lane < m;
+        const uint32_t d = (uint32_t)(kk[r] >> shift) & mask;
+        uint64_t peers = __ballot(valid);
+        for (int b = 0; b < bits; ++b) {
+            const bool bit = (d >> b) & 1u;
+            const uint64_t bal = __ballot(bit);
             peers &= bit ? bal : ~bal;
         }
-        uint32_t rank = __popcll(peers & lt);
-        if (valid && rank == 0) wcnt[w][d] = __popcll(peers);
-        __syncthreads();
-        if (valid) {
-            uint32_t pos = base[d] + rank;
-            for (int k = 0; k < w; ++k) pos += wcnt[k][d];
-            kout[pos] = key;
-            if (kVals) vout[pos] = val;
+        const uint32_t rank = (uint32_t)__popcll(peers & lt);
+        const uint32_t before = cnt[w][d];
+        wave_sync();
+        if (valid && rank == 0) cnt[w][d] = before + (uint32_t)__popcll(peers);
+        wave_sync();
+        pre[r] = before + rank;
+    }
+    __syncthreads();
+    // where each digit's keys begin in the sorted tile (and each wave's among
+    // them), and how far from there they go
+    uint32_t c0[kWavesPerBlock], c1[kWavesPerBlock], n0 = 0, n1 = 0;
+#pragma unroll
+    for (int k = 0; k < kWavesPerBlock; ++k) {
+        c0[k] = n0;
+        c1[k] = n1;
+        n0 += cnt[k][d0];
+        n1 += cnt[k][d0 + 1];
+    }
+    // one scan for both: tile counts above bit 40, segment totals below
+    const uint64_t ex =
+        block_exclusive(((uint64_t)(n0 + n1) << 40) | ((uint64_t)tot0 + tot1));
+    const uint32_t l0 = (uint32_t)(ex >> 40), l1 = l0 + n0, g0 = (uint32_t)ex;
+    delta[d0] = g0 + off0 - l0;
+    delta[d0 + 1] = g0 + tot0 + off1 - l1;
+#pragma unroll
+    for (int k = 0; k < kWavesPerBlock; ++k) {
+        cnt[k][d0] = l0 + c0[k];
+        cnt[k][d0 + 1] = l1 + c1[k];
+    }
+    __syncthreads();
+    // through LDS in digit order, so that lanes write runs
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+        if (w * kWaveTile + r * kWave + lane < m) {
+            const uint32_t p = cnt[w][(uint32_t)(kk[r] >> shift) & mask] + pre[r];
+            sk[p] = kk[r];
+            if (kVals) sv[p] = vv[r];
         }
-        __syncthreads();
-        uint32_t add = 0;
-        for (int k = 0; k < kWavesPerBlock; ++k) add += wcnt[k][threadIdx.x];
-        base[threadIdx.x] += add;
-        __syncthreads();
+    }
+    __syncthreads();
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+        const int i = r * kBlock + tid;
+        if (i < m) {
+            const uint64_t key = sk[i];
+            const uint32_t pos = delta[(uint32_t)(key >> shift) & mask] + (uint32_t)i;
+            kout[pos] = key;
+            if (kVals) vout[pos] = sv[i];
+        }
     }
 }
 
@@ -213,17 +291,21 @@ int radix_sort_segs(const SortSeg *sg, int nseg, int64_t ntiles, int nbits, bool
 {
     if (nseg <= 0 || ntiles <= 0) return 0;
     int par = 0;
-    for (int shift = 0; shift < nbits; shift += 8) {
+    const int passes = sort_passes(nbits);
+    for (int q = 0, shift = 0; q < passes; ++q) {
+        // as even as can be: the last passes take the odd bits
+        const int bits = (nbits - shift) / (passes - q);
         hipLaunchKernelGGL(k_radix_hist, dim3((unsigned)ntiles), dim3(kBlock), 0, s, sg, nseg,
-                           par, shift, hist);
-        hipLaunchKernelGGL(k_radix_rowscan, dim3((unsigned)(256 * nseg)), dim3(kBlock), 0, s, sg,
-                           hist, totals);
+                           par, shift, bits, hist);
+        hipLaunchKernelGGL(k_radix_rowscan, dim3((unsigned)nseg << bits), dim3(kBlock), 0, s, sg,
+                           bits, hist, totals);
         if (vals)
             hipLaunchKernelGGL(k_radix_scatter<true>, dim3((unsigned)ntiles), dim3(kBlock), 0, s,
-                               sg, nseg, par, shift, hist, totals);
+                               sg, nseg, par, shift, bits, hist, totals);
         else
             hipLaunchKernelGGL(k_radix_scatter<false>, dim3((unsigned)ntiles), dim3(kBlock), 0, s,
-                               sg, nseg, par, shift, hist, totals);
+                               sg, nseg, par, shift, bits, hist, totals);
+        shift += bits;
         par ^= 1;
     }
     return par;

@@ -14,10 +14,14 @@ struct SortSeg {
     int64_t n, t0, nt;
 };
 constexpr int64_t kSortTile = 2048;
+constexpr int64_t kSortDigits = 512;   // at most, per pass
+// Passes of a sort on nbits bits (its result is in buffer passes & 1).
+constexpr int sort_passes(int nbits) { return (nbits + 8) / 9; }
 // Stable LSD radix sort of every segment sg[0..nseg) (device memory) on the
 // low nbits of its keys, by one sequence of launches over all ntiles
 // tiles; returns the buffer index (the same for all segments) that holds
-// the result.  hist needs 256 * ntiles entries, totals 256 * nseg.
+// the result.  hist needs kSortDigits * ntiles entries, totals
+// kSortDigits * nseg.
 int radix_sort_segs(const SortSeg *sg, int nseg, int64_t ntiles, int nbits, bool vals,
                     uint32_t *hist, uint32_t *totals, hipStream_t s);
 // Write nseg host descriptors to dst (device) in stream order.

@@ -609,8 +609,8 @@ static int build_grow(rcp_ctx *c, std::vector<BuildJob> &jobs, int nl)
     CHK(dgrow(&c->svB, &c->svB_cap, ntot));
     CHK(dgrow(&c->larena, &c->larena_cap, ltot));
     CHK(dgrow(&c->ltmp, &c->ltmp_cap, ltot));
-    CHK(dgrow(&c->shist, &c->shist_cap, 256 * std::max(tiles, ltiles)));
-    CHK(dgrow(&c->stot, &c->stot_cap, 256 * J));
+    CHK(dgrow(&c->shist, &c->shist_cap, kSortDigits * std::max(tiles, ltiles)));
+    CHK(dgrow(&c->stot, &c->stot_cap, kSortDigits * J));
     CHK(dgrow(&c->d_segs, &c->segs_cap, J));
     CHK(dgrow(&c->bcount, &c->bcount_cap, J));
     if ((int64_t)c->h_segs.size() < J) c->h_segs.resize(J);
@@ -675,7 +675,7 @@ static int build_fronts(rcp_ctx *c, std::vector<BuildJob> &jobs, int nl)
     const int J = (int)jobs.size();
     int nbits = 1;
     for (auto &j : jobs) nbits = std::max(nbits, j.nbits);
-    const int spar = ((nbits + 7) / 8) & 1;   // buffer of the sorted keys (n >= 1 always)
+    const int spar = sort_passes(nbits) & 1;   // buffer of the sorted keys (n >= 1 always)
     int64_t nb = 0, nbt = 0;
     for (int q = 0; q < J; ++q) {
         BuildJob &j = jobs[q];
@@ -773,7 +773,7 @@ static int build_backs(rcp_ctx *c, std::vector<BuildJob> &jobs, const std::vecto
         nbits = std::max(nbits, 2 * jobs[qs[r]].row_bits);
         ltiles += (ms[qs[r]] + kSortTile - 1) / kSortTile;
     }
-    const int spar = ltiles > 0 ? ((nbits + 7) / 8) & 1 : 0;
+    const int spar = ltiles > 0 ? sort_passes(nbits) & 1 : 0;
     const double sk = c->params.skin_s, opg = 1.0 + c->params.skin_g;
     int64_t nbc = 0, nbs = 0, nbr = 0;
     for (int r = 0; r < J; ++r) {
@@ -1374,8 +1374,8 @@ static int place_device(rcp_ctx *c, int k, uint64_t seed, int64_t window, int64_
     CHK(dgrow(&c->skB, &c->skB_cap, n));
     CHK(dgrow(&c->svA, &c->svA_cap, n));
     CHK(dgrow(&c->svB, &c->svB_cap, n));
-    CHK(dgrow(&c->shist, &c->shist_cap, 256 * tiles));
-    CHK(dgrow(&c->stot, &c->stot_cap, 256));
+    CHK(dgrow(&c->shist, &c->shist_cap, kSortDigits * tiles));
+    CHK(dgrow(&c->stot, &c->stot_cap, kSortDigits));
     char *ws = nullptr;
     CHK(dalloc(&ws, off));
     double *d0 = (double *)(ws + o_d0), *x = (double *)(ws + o_x);
