@@ -585,36 +585,56 @@ constexpr int kTabRow = 20;
 
 // Per-wave state of k_search_coop in LDS: the wave's particles, its plane
 // table and owner marks, and its output staging.  Each wave stages its
-// entries; when its staging is full it reserves global space with one
+// pairs; when its staging is full it reserves global space with one
 // atomic and copies them out without waiting for the other waves, and what
 // remains at the end goes out with one reservation for the whole block.
 // Only the wave itself reads and writes these arrays, and the LDS executes
 // a wave's accesses in order, so no block barrier is needed between a
 // write and the reads of other lanes (the compiler keeps a store and a
 // later load of the same array in order, as their addresses may alias).
-constexpr uint32_t kWaveBuf = 256;   // staged entries per wave (2 KB)
+//
+// Reservations are atomics on one counter, which the device takes one by
+// one, 11 ns each: they bounded the search of dense lists (3.9e6 entries in
+// portions of 256: 235 us of a build of 507).  So a pair is staged once, in
+// five bytes, for the two entries it becomes, and a portion is 512 pairs
+// (build 400 us; 428 with 256), the most that leaves four blocks' LDS on a CU.
+constexpr uint32_t kWavePairs = 512;   // staged pairs per wave (2.5 KB)
 
 struct SearchOut {
     const P4 *own;      // LDS, this wave's 64 particles
     int32_t *tab;       // LDS, this wave's 64 rows of kTabRow
     int32_t *mark;      // LDS, this wave's 64 owner marks
-    uint64_t *wbuf;     // LDS, this wave's kWaveBuf staged entries
-    uint64_t *list;
+    uint32_t *pj;       // LDS, this wave's kWavePairs staged partners
+    uint8_t *po;        // LDS, and their owners' lanes
+    uint64_t *list;     // 16-byte aligned, cap even
     unsigned long long *counter;
-    int64_t cap;
+    int64_t cap, wbase;
     int row_bits;
 };
 
-// Copy the wave's n staged entries to the list (called by the whole wave).
+// The wave's n staged pairs to the list from entry g (even) on, each as its
+// two entries with one store (called by the whole wave).
+__device__ __forceinline__ void write_pairs(const SearchOut &out, int lane, unsigned long long g,
+                                            uint32_t n)
+{
+    for (uint32_t k = (uint32_t)lane; k < n; k += kWave) {
+        const int64_t at = (int64_t)(g >> 1) + k;
+        const uint64_t io = (uint64_t)(out.wbase + out.po[k]), jo = out.pj[k];
+        if (2 * at < out.cap)
+            gstore((u64x2 *)out.list, at,
+                   u64x2{(io << out.row_bits) | jo, (jo << out.row_bits) | io});
+    }
+}
+
+// Copy the wave's n staged pairs to the list (called by the whole wave).
 __device__ __forceinline__ void flush_wave(const SearchOut &out, int lane, uint32_t n)
 {
     unsigned long long g = 0;
-    if (lane == 0) g = atomicAdd(out.counter, (unsigned long long)n);
+    if (lane == 0) g = atomicAdd(out.counter, 2ull * n);
     g = (unsigned long long)(uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)g) |
         ((unsigned long long)(uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(g >> 32))
          << 32);
-    for (uint32_t k = (uint32_t)lane; k < n; k += kWave)
-        if ((int64_t)g + k < out.cap) gstore(out.list, (int64_t)g + k, out.wbuf[k]);
+    write_pairs(out, lane, g, n);
     __builtin_amdgcn_wave_barrier();
 }
 
@@ -627,9 +647,10 @@ __device__ __forceinline__ void flush_wave(const SearchOut &out, int lane, uint3
 // position there (the last such lane of a position), and a running maximum
 // over the window gives every candidate its owner.  The owner's table row
 // then gives the run and the sorted index.  Listed pairs are staged at the
-// wave's count wn (the same on every lane).
+// wave's count wn (the same on every lane).  The wave takes round z of every
+// nz rounds.
 __device__ __forceinline__ void test_plane(const BuildArgs &a, const SearchOut &out, int lane,
-                                           uint64_t below, int64_t wbase, const int2 r[9],
+                                           uint64_t below, const int2 r[9], int z, int nz,
                                            uint32_t &wn)
 {
     int32_t cum[9];
@@ -667,7 +688,8 @@ __device__ __forceinline__ void test_plane(const BuildArgs &a, const SearchOut &
     int32_t nxt = __shfl(inc, (lane + 1) & (kWave - 1), kWave);
     if (lane == kWave - 1) nxt = 0x7fffffff;
     __builtin_amdgcn_wave_barrier();
-    for (int32_t r0 = 0; r0 < T; r0 += kWave) {
+    for (int64_t rz = (int64_t)z * kWave; rz < T; rz += (int64_t)nz * kWave) {
+        const int32_t r0 = (int32_t)rz;
         const int32_t q = r0 + lane;
         out.mark[lane] = 0;
         const int32_t P = max(inc - r0, 0), Pn = max(nxt - r0, 0);
@@ -710,16 +732,15 @@ __device__ __forceinline__ void test_plane(const BuildArgs &a, const SearchOut &
         }
         const uint64_t bal = __ballot(hit);
         if (bal == 0ull) continue;
-        const uint32_t cnt = 2u * (uint32_t)__popcll(bal);
-        if (wn + cnt > kWaveBuf) {
+        const uint32_t cnt = (uint32_t)__popcll(bal);
+        if (wn + cnt > kWavePairs) {
             flush_wave(out, lane, wn);
             wn = 0;
         }
         if (hit) {
-            const int64_t io = wbase + o;
-            const uint32_t kk = wn + 2u * (uint32_t)__popcll(bal & below);
-            out.wbuf[kk] = ((uint64_t)io << out.row_bits) | (uint64_t)j;
-            out.wbuf[kk + 1] = ((uint64_t)j << out.row_bits) | (uint64_t)io;
+            const uint32_t kk = wn + (uint32_t)__popcll(bal & below);
+            out.pj[kk] = (uint32_t)j;
+            out.po[kk] = (uint8_t)o;
         }
         wn += cnt;
         __builtin_amdgcn_wave_barrier();
@@ -744,7 +765,8 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4))) voi
     __shared__ P4 own[kBlock];
     __shared__ __align__(16) int32_t tab[kBlock * kTabRow];
     __shared__ int32_t mark[kBlock];
-    __shared__ uint64_t wbuf[kWavesPerBlock * kWaveBuf];
+    __shared__ uint32_t pj[kWavesPerBlock * kWavePairs];
+    __shared__ uint8_t po[kWavesPerBlock * kWavePairs];
     __shared__ uint32_t wcount[kWavesPerBlock];
     __shared__ unsigned long long bbase;
     const int64_t gb =
@@ -754,7 +776,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4))) voi
     const int64_t blk = (int64_t)gb - F.b0;
     // split grids give every packing 3 * (the batch's deepest) levels; the
     // slices past this packing's levels have nothing to do
-    if (gridDim.y > 1 && (int)blockIdx.y / 3 >= a.nlev) return;
+    if ((int)blockIdx.y / 3 >= a.nlev) return;
     const int lane = (int)(threadIdx.x & (kWave - 1));
     const uint64_t below = lane == 0 ? 0ull : (~0ull >> (kWave - lane));
     const int64_t wbase = (int64_t)blk * kBlock + (threadIdx.x & ~(kWave - 1));
@@ -762,7 +784,8 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4))) voi
     const bool valid = i < a.n;
     const int wofs = (int)(threadIdx.x & ~(kWave - 1));
     const SearchOut out{own + wofs, tab + wofs * kTabRow, mark + wofs,
-                        wbuf + (wofs / kWave) * kWaveBuf, F.list, F.counter, F.lcap, F.row_bits};
+                        pj + (wofs / kWave) * kWavePairs, po + (wofs / kWave) * kWavePairs,
+                        F.list, F.counter, F.lcap, wbase, F.row_bits};
     double xi = 0.0, yi = 0.0, zi = 0.0, di = 0.0;
     int li = kMaxLevels;
     if (valid) {
@@ -775,15 +798,17 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4))) voi
     }
     own[threadIdx.x] = P4{xi, yi, zi, di};
     __builtin_amdgcn_wave_barrier();
-    // a grid with gridDim.y > 1 gives each block one level and one plane
-    // (fixed x offset) of the stencil: shorter chains of dependent lookups
-    // for packings too small to fill the GPU otherwise
+    // a grid with gridDim.y > 1 gives each block one plane (fixed x offset)
+    // of the stencil, with gridDim.y > 3 one level as well, and with
+    // gridDim.z > 1 every gridDim.z-th round of its candidates: shorter
+    // chains for packings too small to fill the GPU otherwise
     int Lb = 0, Le = a.nlev, plane = -1;
-    if (gridDim.y > 1) {
+    if (gridDim.y > 1) plane = (int)blockIdx.y % 3;
+    if (gridDim.y > 3) {
         Lb = (int)blockIdx.y / 3;
-        Le = Lb + 1 < a.nlev ? Lb + 1 : a.nlev;
-        plane = (int)blockIdx.y % 3;
+        Le = Lb + 1;
     }
+    const int z = (int)blockIdx.z, nz = (int)gridDim.z;
     uint32_t wn = 0;
     for (int L = Lb; L < Le; ++L) {
         const LevelGrid g = a.lv[L];
@@ -805,7 +830,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4))) voi
 #pragma unroll
                 for (int k = 0; k < 9; ++k) r[k] = above(r[k], i);
             }
-            test_plane(a, out, lane, below, wbase, r, wn);
+            test_plane(a, out, lane, below, r, z, nz, wn);
         }
     }
     // what the waves still hold goes out with one reservation per block
@@ -815,13 +840,12 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4))) voi
     if (threadIdx.x == 0) {
         uint32_t tot = 0;
         for (int k = 0; k < kWavesPerBlock; ++k) tot += wcount[k];
-        bbase = tot ? atomicAdd(F.counter, (unsigned long long)tot) : 0ull;
+        bbase = tot ? atomicAdd(F.counter, 2ull * tot) : 0ull;
     }
     __syncthreads();
     unsigned long long g = bbase;
-    for (int k = 0; k < w; ++k) g += wcount[k];
-    for (uint32_t k = (uint32_t)lane; k < wn; k += kWave)
-        if ((int64_t)g + k < F.lcap) gstore(F.list, (int64_t)g + k, out.wbuf[k]);
+    for (int k = 0; k < w; ++k) g += 2ull * wcount[k];
+    write_pairs(out, lane, g, wn);
 }
 
 void launch_search(const BuildArgs &a, uint64_t *list, unsigned long long *counter, int64_t cap,
@@ -837,9 +861,17 @@ void launch_search_seg(const FrontJob *jobs, int J, int64_t nb, int max_nlev, in
                        int64_t b_base, hipStream_t s)
 {
     if (nb <= 0) return;
-    // fewer than 8 blocks per CU: split the work by level and plane
-    const unsigned ny = nb < 2048 ? 3u * (unsigned)max_nlev : 1u;
-    hipLaunchKernelGGL(k_search_coop, dim3((unsigned)nb, ny), dim3(kBlock), 0, s, jobs, J,
+    // Eight blocks a CU fill the device.  Below that the nine or more steps
+    // (level, plane) a wave takes one after another are split over blocks: by
+    // plane while that gives 1024 blocks, else by level too, and what still
+    // falls short of them by rounds of candidates.  Each block ends with an
+    // atomic on the packing's counter (11 us per thousand), so no further
+    // than that.  Whole builds, us: 512 spheres 158 by level and plane, 110
+    // with rounds split as well; 3e5 spheres 348 by level and plane, 319 by
+    // plane; 1e6 spheres 766 whole, 822 by plane.
+    const unsigned ny = nb >= 2048 ? 1u : (3 * nb >= 1024 ? 3u : 3u * (unsigned)max_nlev);
+    const unsigned nz = (unsigned)std::max<int64_t>(1, std::min<int64_t>(8, 1024 / (nb * ny)));
+    hipLaunchKernelGGL(k_search_coop, dim3((unsigned)nb, ny, nz), dim3(kBlock), 0, s, jobs, J,
                        xcd_remap, b_base);
 }
 

@@ -544,7 +544,9 @@ static int build_plan(rcp_ctx *c, int k, double kappa, int64_t min_entries, Buil
     j.hcap = 64;
     while (j.hcap < 4 * nhashed) j.hcap <<= 1;
     // the expected list length with room to spare
+    // (even: entries are written in pairs)
     j.lcap = std::max<int64_t>({s.list_est + s.list_est / 4, 8 * n, 1024, min_entries});
+    j.lcap += j.lcap & 1;
     return RCP_OK;
 }
 
