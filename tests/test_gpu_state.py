@@ -68,3 +68,28 @@ def test_a_new_schedule_starts_every_packing_afresh(rcp, orc):
         c = run(q, k, slice(k, k + 1))
         q.close()
         assert np.array_equal(a[k][0], c[0][0]) and a[k][1] == c[0][1]
+
+
+@pytest.mark.parametrize("graph_iters,step", [(1, 700), (4, 350), (8, 700), (32, 700), (32, 61)])
+def test_iterations_do_not_depend_on_how_they_are_queued(rcp, orc, graph_iters, step):
+    # several graphs in a row between two looks at the records, over list
+    # builds, against one graph a look and single launches
+    n, L = 300, 7.0
+    d = 0.5 + 0.1 * np.arange(n) / n
+    x = orc.rsa(d, L, 0.5, 5)
+
+    def run(gi, st):
+        p = rcp.Packing(d, L, 1.0, 0, init="none", tuning=rcp.make_tuning(graph_iters=gi))
+        p.set_state(x, 1.2)
+        p.run_start(rcp.schedule_from_rungs([(1e-4, 1e-3, 1e-4, 1.0, 1 << 30)]))
+        for k in range(0, 700, st):
+            p.run_continue(min(st, 700 - k))
+        r = p.get_state() + p.get_optimizer()
+        p.close()
+        return r
+
+    a, b = run(16, 16), run(graph_iters, step)
+    # (the stop test holds before the last one)
+    assert b[4]["iterations"] == a[4]["iterations"] > 600
+    assert np.array_equal(a[0], b[0]) and a[1] == b[1]
+    assert np.array_equal(a[2], b[2]) and np.array_equal(a[3], b[3])
