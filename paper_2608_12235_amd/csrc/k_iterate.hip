@@ -920,14 +920,13 @@ __device__ __forceinline__ double group_sum(double v, int sh)
     return v;
 }
 
-// A block whose items have more entries together than six of their size
+// A block whose items have more entries together than kSplitItems of their size
 // (1536 by default) takes them one after the other with all four waves, each
 // wave every fourth round: rows are not cut, so an item grows past its size
 // only by one long row, and a wave alone would take it at about 2 us per
 // round of 64 (on 1.2e5 spheres around frozen ones, rows of up to 2006: 48
 // us with the split, 72 us without; where dense lists' ordinary items split
 // too, 22 against 15 us on 1e5 spheres).
-constexpr int kSplitItems = 6;
 
 // What a block of the wave kernels must know before its first vector load,
 // read as one batch of scalar loads: left to themselves these reads, each
@@ -1535,24 +1534,23 @@ __device__ __forceinline__ int back_job_of(const BackJob *__restrict__ jobs, int
     return lo;
 }
 
-__global__ __launch_bounds__(kBlock) void k_items_fill_seg(const BackJob *__restrict__ jobs, int J)
-{
-    const BackJob &B = jobs[back_job_of(jobs, J, blockIdx.x, &BackJob::bs0)];
-    const int64_t b = ((int64_t)blockIdx.x - B.bs0) * kBlock + threadIdx.x;
-    if (!B.fill || b >= B.nslots) return;
-    WorkItem w;
-    w.seg = B.seg;
-    w.e0 = w.e1 = B.rp ? B.rp[B.n] : 0;
-    w.split = kSplitItems * B.item_work;
-    w.begin = B.n;
-    w.end = B.n;
-    B.W[b] = w;
-}
-
-__global__ __launch_bounds__(kBlock) void k_items_seg(const BackJob *__restrict__ jobs, int J)
+// The cut of every packing's rows into its slots; the thread of the first row
+// makes the new list the packing's (limits, buffers, flags).
+__global__ __launch_bounds__(kBlock) void k_items_seg(const BackJob *__restrict__ jobs, int J,
+                                                     SegState *__restrict__ S,
+                                                     SegPtrs *__restrict__ P)
 {
     const BackJob &B = jobs[back_job_of(jobs, J, blockIdx.x, &BackJob::br0)];
     const int64_t i = ((int64_t)blockIdx.x - B.br0) * kBlock + threadIdx.x;
+    if (i == 0) {
+        SegState *s = S + B.seg;
+        s->kb = B.kb;
+        s->disp_lim = B.disp_lim;
+        s->kappa_lim = B.kappa_lim;
+        s->cur = B.cur;
+        s->flags &= ~(F_REBUILD | F_STALE);
+        P[B.seg] = B.ptrs;
+    }
     if (!B.fill || i >= B.n) return;
     const int64_t rc = B.row_cost, wk = B.item_work;
     const int64_t hi = rc * i + (int64_t)B.rp[i];
@@ -1568,33 +1566,11 @@ __global__ __launch_bounds__(kBlock) void k_items_seg(const BackJob *__restrict_
     }
 }
 
-__global__ void k_after_seg(const BackJob *__restrict__ jobs, int J, SegState *S, SegPtrs *P)
+void launch_items_seg(const BackJob *jobs, int J, int64_t nbr, SegState *S, SegPtrs *P,
+                      hipStream_t st)
 {
-    const int j = (int)(blockIdx.x * blockDim.x + threadIdx.x);
-    if (j >= J) return;
-    const BackJob &B = jobs[j];
-    SegState *s = S + B.seg;
-    s->kb = B.kb;
-    s->disp_lim = B.disp_lim;
-    s->kappa_lim = B.kappa_lim;
-    s->cur = B.cur;
-    s->flags &= ~(F_REBUILD | F_STALE);
-    P[B.seg] = B.ptrs;
-}
-
-void launch_items_seg(const BackJob *jobs, int J, int64_t nbs, int64_t nbr, hipStream_t st)
-{
-    if (nbs > 0)
-        hipLaunchKernelGGL(k_items_fill_seg, dim3((unsigned)nbs), dim3(kBlock), 0, st, jobs, J);
     if (nbr > 0)
-        hipLaunchKernelGGL(k_items_seg, dim3((unsigned)nbr), dim3(kBlock), 0, st, jobs, J);
-}
-
-void launch_after_seg(const BackJob *jobs, int J, SegState *S, SegPtrs *P, hipStream_t st)
-{
-    if (J > 0)
-        hipLaunchKernelGGL(k_after_seg, dim3((unsigned)((J + kBlock - 1) / kBlock)), dim3(kBlock), 0,
-                           st, jobs, J, S, P);
+        hipLaunchKernelGGL(k_items_seg, dim3((unsigned)nbr), dim3(kBlock), 0, st, jobs, J, S, P);
 }
 
 // Work-table layout of every packing: lay[2k] blocks, lay[2k + 1] first item.

@@ -894,8 +894,19 @@ __device__ __forceinline__ void csr_one(const uint64_t *__restrict__ srt, int64_
 }
 
 // ------------------------------------------- segmented build steps
-__global__ __launch_bounds__(kBlock) void k_keys_seg(const FrontJob *__restrict__ jobs, int J)
+// Blocks [0, nb): keys; the rest: tables and counters cleared.
+__global__ __launch_bounds__(kBlock) void k_keys_seg(const FrontJob *__restrict__ jobs, int J,
+                                                    int64_t nb)
 {
+    if ((int64_t)blockIdx.x >= nb) {
+        const int64_t b = (int64_t)blockIdx.x - nb;
+        const FrontJob &F = jobs[job_of(jobs, J, b, &FrontJob::bt0)];
+        const int64_t i = (b - F.bt0) * kBlock + threadIdx.x;
+        if (i < F.hcap) F.a.hash[i].key = kEmptyKey;
+        if (i < F.nd2) reinterpret_cast<uint32_t *>(F.a.dense)[i] = 0u;
+        if (i == 0) *F.counter = 0ull;
+        return;
+    }
     const FrontJob &F = jobs[job_of(jobs, J, blockIdx.x, &FrontJob::b0)];
     const int64_t i = ((int64_t)blockIdx.x - F.b0) * kBlock + threadIdx.x;
     if (i < F.a.n) key_of(F.a, F.pos0, F.lev0, i, F.keys, F.vals);
@@ -908,62 +919,62 @@ __global__ __launch_bounds__(kBlock) void k_permute_seg(const FrontJob *__restri
     if (k < F.pa.n) permute_one(F.pa, k);
 }
 
-// After the permutation: the other position buffer (the source of the
-// permutation, which the next iteration writes) takes the D0 of the new
-// order, so that iterations need to write only the three coordinates.
-__global__ __launch_bounds__(kBlock) void k_d0_copy_seg(const FrontJob *__restrict__ jobs, int J)
-{
-    const FrontJob &F = jobs[job_of(jobs, J, blockIdx.x, &FrontJob::b0)];
-    const int64_t k = ((int64_t)blockIdx.x - F.b0) * kBlock + threadIdx.x;
-    if (k < F.pa.n) const_cast<P4 *>(F.pa.ps)[k].d = F.pa.pd[k].d;
-}
-
-__global__ __launch_bounds__(kBlock) void k_tables_clear_seg(const FrontJob *__restrict__ jobs,
-                                                            int J)
-{
-    const FrontJob &F = jobs[job_of(jobs, J, blockIdx.x, &FrontJob::bt0)];
-    const int64_t i = ((int64_t)blockIdx.x - F.bt0) * kBlock + threadIdx.x;
-    if (i < F.hcap) F.a.hash[i].key = kEmptyKey;
-    if (i < F.nd2) reinterpret_cast<uint32_t *>(F.a.dense)[i] = 0u;
-    if (i == 0) *F.counter = 0ull;
-}
-
+// The cell tables; and, after the permutation, the other position buffer (its
+// source, which the next iteration writes) takes the D0 of the new order, so
+// that iterations need to write only the three coordinates.
 __global__ __launch_bounds__(kBlock) void k_cells_seg(const FrontJob *__restrict__ jobs, int J)
 {
     const FrontJob &F = jobs[job_of(jobs, J, blockIdx.x, &FrontJob::b0)];
     const int64_t i = ((int64_t)blockIdx.x - F.b0) * kBlock + threadIdx.x;
-    if (i < F.a.n) cells_one(F.a, i);
+    if (i >= F.a.n) return;
+    const_cast<P4 *>(F.pa.ps)[i].d = F.pa.pd[i].d;
+    cells_one(F.a, i);
 }
 
-__global__ __launch_bounds__(kBlock) void k_csr_seg(const BackJob *__restrict__ jobs, int J)
+// Blocks [0, nbc): rows and columns; the rest: work-item slots as empty items
+// behind the last row (the items' cut writes the used ones).
+__global__ __launch_bounds__(kBlock) void k_csr_seg(const BackJob *__restrict__ jobs, int J,
+                                                   int64_t nbc)
 {
+    if ((int64_t)blockIdx.x >= nbc) {
+        const int64_t g = (int64_t)blockIdx.x - nbc;
+        const BackJob &B = jobs[job_of(jobs, J, g, &BackJob::bs0)];
+        const int64_t b = (g - B.bs0) * kBlock + threadIdx.x;
+        if (!B.fill || b >= B.nslots) return;
+        WorkItem w;
+        w.seg = B.seg;
+        w.e0 = w.e1 = (int32_t)B.m;
+        w.split = kSplitItems * B.item_work;
+        w.begin = B.n;
+        w.end = B.n;
+        B.W[b] = w;
+        return;
+    }
     const BackJob &B = jobs[job_of(jobs, J, blockIdx.x, &BackJob::bc0)];
     const int64_t q = ((int64_t)blockIdx.x - B.bc0) * kBlock + threadIdx.x;
     if (q <= B.m) csr_one(B.srt, B.m, B.row_bits, B.n, B.rp, B.col, B.rlo, q);
 }
 
-void launch_keys_seg(const FrontJob *jobs, int J, int64_t nb, hipStream_t s)
+void launch_keys_seg(const FrontJob *jobs, int J, int64_t nb, int64_t nbt, hipStream_t s)
 {
-    if (nb > 0) hipLaunchKernelGGL(k_keys_seg, dim3((unsigned)nb), dim3(kBlock), 0, s, jobs, J);
+    if (nb > 0)
+        hipLaunchKernelGGL(k_keys_seg, dim3((unsigned)(nb + nbt)), dim3(kBlock), 0, s, jobs, J, nb);
 }
 
 void launch_permute_seg(const FrontJob *jobs, int J, int64_t nb, hipStream_t s)
 {
-    if (nb <= 0) return;
-    hipLaunchKernelGGL(k_permute_seg, dim3((unsigned)nb), dim3(kBlock), 0, s, jobs, J);
-    hipLaunchKernelGGL(k_d0_copy_seg, dim3((unsigned)nb), dim3(kBlock), 0, s, jobs, J);
+    if (nb > 0) hipLaunchKernelGGL(k_permute_seg, dim3((unsigned)nb), dim3(kBlock), 0, s, jobs, J);
 }
 
-void launch_tables_seg(const FrontJob *jobs, int J, int64_t nbt, int64_t nb, hipStream_t s)
+void launch_cells_seg(const FrontJob *jobs, int J, int64_t nb, hipStream_t s)
 {
-    if (nbt > 0)
-        hipLaunchKernelGGL(k_tables_clear_seg, dim3((unsigned)nbt), dim3(kBlock), 0, s, jobs, J);
     if (nb > 0) hipLaunchKernelGGL(k_cells_seg, dim3((unsigned)nb), dim3(kBlock), 0, s, jobs, J);
 }
 
-void launch_csr_seg(const BackJob *jobs, int J, int64_t nbc, hipStream_t s)
+void launch_csr_seg(const BackJob *jobs, int J, int64_t nbc, int64_t nbs, hipStream_t s)
 {
-    if (nbc > 0) hipLaunchKernelGGL(k_csr_seg, dim3((unsigned)nbc), dim3(kBlock), 0, s, jobs, J);
+    if (nbc > 0)
+        hipLaunchKernelGGL(k_csr_seg, dim3((unsigned)(nbc + nbs)), dim3(kBlock), 0, s, jobs, J, nbc);
 }
 
 // ------------------------------------------------------- statistics

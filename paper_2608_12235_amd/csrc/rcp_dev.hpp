@@ -71,7 +71,7 @@ struct SegState {
                           // absolute diameter -D0, no step; a cascade stage)
     int32_t nblocks;      // iteration-grid blocks of this segment
     int64_t bfirst;       // first of them (index into the work table)
-    // set at each list build (k_after_seg)
+    // set at each list build (k_items_seg)
     double kb, disp_lim, kappa_lim;
     // host: hard walls (bit a = axis a): flat walls at 0 and L across the
     // axes of `walls`, a round container (disk or ball of diameter L
@@ -97,6 +97,10 @@ __host__ __device__ inline void seg_bias_terms(SegState &s)
     s.ib1n = 1.0 / (1.0 - s.b1t * s.beta1);
     s.ib2n = 1.0 / (1.0 - s.b2t * s.beta2);
 }
+
+// A block whose items hold more than kSplitItems items' worth of entries in
+// all shares them among its waves (WorkItem::split).
+constexpr int kSplitItems = 6;
 
 // One wave of the iteration grid: rows [begin, end) of packing seg.  The
 // four items of a block are consecutive and of one packing.

@@ -108,17 +108,17 @@ struct BackJob {
     int64_t br0;            // first block in the row grid
 };
 // Front steps for all packings of a batch (jobs in device memory): Morton
-// keys (nb = blocks of the per-particle grid), permutation (then the D0 of
-// the new order into the other position buffer), cell tables (nbt = blocks
-// of the clear grid; clears the counters too).
-void launch_keys_seg(const FrontJob *jobs, int J, int64_t nb, hipStream_t s);
+// keys (nb = blocks of the per-particle grid), with cell tables and counters
+// cleared in the same launch (nbt = blocks of the clear grid); permutation;
+// cell tables, with the D0 of the new order into the other position buffer.
+void launch_keys_seg(const FrontJob *jobs, int J, int64_t nb, int64_t nbt, hipStream_t s);
 void launch_permute_seg(const FrontJob *jobs, int J, int64_t nb, hipStream_t s);
-void launch_tables_seg(const FrontJob *jobs, int J, int64_t nbt, int64_t nb, hipStream_t s);
-// Back steps: rows and columns (nbc blocks), work items (nbs slot blocks,
-// nbr row blocks), validity limits and pointer entries.
-void launch_csr_seg(const BackJob *jobs, int J, int64_t nbc, hipStream_t s);
-void launch_items_seg(const BackJob *jobs, int J, int64_t nbs, int64_t nbr, hipStream_t s);
-void launch_after_seg(const BackJob *jobs, int J, SegState *S, SegPtrs *P, hipStream_t s);
+void launch_cells_seg(const FrontJob *jobs, int J, int64_t nb, hipStream_t s);
+// Back steps: rows and columns (nbc blocks) and the work items' empty slots
+// (nbs), then the items, validity limits and pointer entries (nbr row blocks).
+void launch_csr_seg(const BackJob *jobs, int J, int64_t nbc, int64_t nbs, hipStream_t s);
+void launch_items_seg(const BackJob *jobs, int J, int64_t nbr, SegState *S, SegPtrs *P,
+                      hipStream_t s);
 
 // One pass over the particles: every listed pair (i, j) is appended twice
 // to `list` as (row << row_bits) | col, rows and cols in sorted order, in an

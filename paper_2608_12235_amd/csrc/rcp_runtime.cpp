@@ -178,17 +178,15 @@ struct rcp_ctx {
     int64_t ltmp_cap = 0;
     uint32_t *shist = nullptr, *stot = nullptr;
     int64_t shist_cap = 0, stot_cap = 0;
-    SortSeg *d_segs = nullptr;
-    int64_t segs_cap = 0;
-    std::vector<SortSeg> h_segs;
     uint64_t *larena = nullptr;      // list regions of the builds in flight
     int64_t larena_cap = 0;
     HashSlot *harena = nullptr;      // their cell hashes and dense cell tables
     int64_t harena_cap = 0;
     int2 *darena = nullptr;
     int64_t darena_cap = 0;
-    FrontJob *d_fj = nullptr, *h_fj = nullptr;   // batch job tables (device, pinned host)
-    BackJob *d_bj = nullptr, *h_bj = nullptr;
+    // tables of a batch of builds (device, pinned host): the sort's segments,
+    // then the jobs (see job_table)
+    char *d_fj = nullptr, *h_fj = nullptr, *d_bj = nullptr, *h_bj = nullptr;
     int64_t fj_cap = 0, bj_cap = 0, hj_cap = 0;
     unsigned long long *bcount = nullptr;   // their entry counts (device, pinned host)
     int64_t bcount_cap = 0;
@@ -591,8 +589,8 @@ static int build_grow(rcp_ctx *c, std::vector<BuildJob> &jobs, int nl)
     const int64_t J = (int64_t)jobs.size();
     CHK(dgrow(&c->harena, &c->harena_cap, htot));
     CHK(dgrow(&c->darena, &c->darena_cap, std::max<int64_t>(dtot, 1)));
-    CHK(dgrow(&c->d_fj, &c->fj_cap, J));
-    CHK(dgrow(&c->d_bj, &c->bj_cap, J));
+    CHK(dgrow(&c->d_fj, &c->fj_cap, J * (int64_t)(sizeof(SortSeg) + sizeof(FrontJob))));
+    CHK(dgrow(&c->d_bj, &c->bj_cap, J * (int64_t)(sizeof(SortSeg) + sizeof(BackJob))));
     if (J > c->hj_cap) {
         if (c->h_fj) (void)hipHostFree(c->h_fj);
         if (c->h_bj) (void)hipHostFree(c->h_bj);
@@ -600,8 +598,10 @@ static int build_grow(rcp_ctx *c, std::vector<BuildJob> &jobs, int nl)
         c->h_bj = nullptr;
         c->hj_cap = 0;
         const int64_t cap = std::max<int64_t>(16, 2 * J);
-        hipError_t e = hipHostMalloc((void **)&c->h_fj, sizeof(FrontJob) * cap, 0);
-        if (e == hipSuccess) e = hipHostMalloc((void **)&c->h_bj, sizeof(BackJob) * cap, 0);
+        hipError_t e =
+            hipHostMalloc((void **)&c->h_fj, (sizeof(SortSeg) + sizeof(FrontJob)) * cap, 0);
+        if (e == hipSuccess)
+            e = hipHostMalloc((void **)&c->h_bj, (sizeof(SortSeg) + sizeof(BackJob)) * cap, 0);
         if (e != hipSuccess) return fail(RCP_ENOMEM, "hipHostMalloc: %s", hipGetErrorString(e));
         c->hj_cap = cap;
     }
@@ -613,9 +613,7 @@ static int build_grow(rcp_ctx *c, std::vector<BuildJob> &jobs, int nl)
     CHK(dgrow(&c->ltmp, &c->ltmp_cap, ltot));
     CHK(dgrow(&c->shist, &c->shist_cap, kSortDigits * std::max(tiles, ltiles)));
     CHK(dgrow(&c->stot, &c->stot_cap, kSortDigits * J));
-    CHK(dgrow(&c->d_segs, &c->segs_cap, J));
     CHK(dgrow(&c->bcount, &c->bcount_cap, J));
-    if ((int64_t)c->h_segs.size() < J) c->h_segs.resize(J);
     if (J > c->h_bcount_cap) {
         if (c->h_bcount) (void)hipHostFree(c->h_bcount);
         c->h_bcount = nullptr;
@@ -629,21 +627,12 @@ static int build_grow(rcp_ctx *c, std::vector<BuildJob> &jobs, int nl)
     return RCP_OK;
 }
 
-// Sort the segments h_segs[0..J) (host descriptors: t0 and nt are filled
-// in here; they are passed to the device as kernel arguments) on the
-// context's stream; *par receives the buffer index holding the results.
-static int sort_segments(rcp_ctx *c, int J, int nbits, bool vals, int *par)
+// The jobs behind the segments of a batch of J.
+template <class Job>
+static Job *job_table(char *t, int J)
 {
-    int64_t t = 0;
-    for (int q = 0; q < J; ++q) {
-        c->h_segs[q].t0 = t;
-        c->h_segs[q].nt = (c->h_segs[q].n + kSortTile - 1) / kSortTile;
-        t += c->h_segs[q].nt;
-    }
-    launch_put_segs(c->d_segs, c->h_segs.data(), J, c->stream);
-    *par = radix_sort_segs(c->d_segs, J, t, nbits, vals, c->shist, c->stot, c->stream);
-    HIPCHK(hipGetLastError());
-    return RCP_OK;
+    static_assert(alignof(Job) <= 8 && sizeof(SortSeg) % 8 == 0, "jobs follow the segments");
+    return (Job *)(t + sizeof(SortSeg) * J);
 }
 
 // Lanes 1..nl-1 wait for the context's stream.
@@ -668,7 +657,8 @@ static int join_lanes(rcp_ctx *c, int nl)
 // Front half of a batch of builds: Morton keys at the current positions
 // and one segmented sort, the permutation of every per-particle array and
 // the cell tables, each as one launch over all packings (job table
-// jobs -> c->h_fj, copied to the device), then the pair searches, one per
+// jobs -> c->h_fj, copied to the device with the sort's segments), then the
+// pair searches, one per
 // packing on its lane, appending every pair in both directions to each
 // packing's list region (entry count of jobs[q] in bcount[q]).  Leaves the
 // lanes forked.
@@ -678,11 +668,14 @@ static int build_fronts(rcp_ctx *c, std::vector<BuildJob> &jobs, int nl)
     int nbits = 1;
     for (auto &j : jobs) nbits = std::max(nbits, j.nbits);
     const int spar = sort_passes(nbits) & 1;   // buffer of the sorted keys (n >= 1 always)
-    int64_t nb = 0, nbt = 0;
+    SortSeg *segs = (SortSeg *)c->h_fj;
+    FrontJob *fj = job_table<FrontJob>(c->h_fj, J);
+    FrontJob *d_fj = job_table<FrontJob>(c->d_fj, J);
+    int64_t nb = 0, nbt = 0, tiles = 0;
     for (int q = 0; q < J; ++q) {
         BuildJob &j = jobs[q];
         Seg &s = c->segs[j.k];
-        FrontJob &F = c->h_fj[q];
+        FrontJob &F = fj[q];
         const int cur = s.cur, ncur = cur ^ 1, set = s.set, nset = set ^ 1;
         j.a.pos = s.Q[ncur];
         j.a.lev = s.LEV[nset];
@@ -722,23 +715,26 @@ static int build_fronts(rcp_ctx *c, std::vector<BuildJob> &jobs, int nl)
         nb += (s.n + kBlock - 1) / kBlock;
         F.bt0 = nbt;
         nbt += (std::max(F.hcap, F.nd2) + kBlock - 1) / kBlock;
-        SortSeg &g = c->h_segs[q];
+        SortSeg &g = segs[q];
         g.k[0] = c->skA + j.koff;
         g.k[1] = c->skB + j.koff;
         g.v[0] = c->svA + j.koff;
         g.v[1] = c->svB + j.koff;
         g.n = s.n;
+        g.t0 = tiles;
+        g.nt = (g.n + kSortTile - 1) / kSortTile;
+        tiles += g.nt;
         s.set = nset;
         s.cur = ncur;
     }
-    HIPCHK(hipMemcpyAsync(c->d_fj, c->h_fj, sizeof(FrontJob) * J, hipMemcpyHostToDevice,
-                          c->stream));
-    launch_keys_seg(c->d_fj, J, nb, c->stream);
-    int par = 0;
-    CHK(sort_segments(c, J, nbits, true, &par));
+    HIPCHK(hipMemcpyAsync(c->d_fj, c->h_fj, (sizeof(SortSeg) + sizeof(FrontJob)) * J,
+                          hipMemcpyHostToDevice, c->stream));
+    launch_keys_seg(d_fj, J, nb, nbt, c->stream);
+    const int par = radix_sort_segs((const SortSeg *)c->d_fj, J, tiles, nbits, true, c->shist,
+                                    c->stot, c->stream);
     if (par != spar) return fail(RCP_EDEVICE, "internal: key sort parity");
-    launch_permute_seg(c->d_fj, J, nb, c->stream);
-    launch_tables_seg(c->d_fj, J, nbt, nb, c->stream);
+    launch_permute_seg(d_fj, J, nb, c->stream);
+    launch_cells_seg(d_fj, J, nb, c->stream);
     // one search launch per packing, spread over the lanes: each packing's
     // grid is split by level and plane when it is small, which a single
     // launch over a large batch would not be
@@ -748,8 +744,8 @@ static int build_fronts(rcp_ctx *c, std::vector<BuildJob> &jobs, int nl)
         const BuildJob &j = jobs[q];
         hipStream_t st = c->lanes[j.lane].st;
         if (coop)
-            launch_search_seg(c->d_fj + q, 1, (j.a.n + kBlock - 1) / kBlock, j.a.nlev,
-                              c->tuning.xcd_remap, c->h_fj[q].b0, st);
+            launch_search_seg(d_fj + q, 1, (j.a.n + kBlock - 1) / kBlock, j.a.nlev,
+                              c->tuning.xcd_remap, fj[q].b0, st);
         else
             launch_search(j.a, c->larena + j.loff, c->bcount + q, j.lcap, j.row_bits,
                           c->tuning.xcd_remap, st);
@@ -763,7 +759,7 @@ static int build_fronts(rcp_ctx *c, std::vector<BuildJob> &jobs, int nl)
 // row pointers and columns, work items (*relayout when a packing's slots
 // are too few: the caller lays out the work table again) and the validity
 // limits and pointer entries, each as one launch over the batch (job table
-// -> c->h_bj, copied to the device).
+// -> c->h_bj, copied to the device with the sort's segments).
 static int build_backs(rcp_ctx *c, std::vector<BuildJob> &jobs, const std::vector<int> &qs,
                        const std::vector<int64_t> &ms, bool *relayout)
 {
@@ -777,17 +773,23 @@ static int build_backs(rcp_ctx *c, std::vector<BuildJob> &jobs, const std::vecto
     }
     const int spar = ltiles > 0 ? sort_passes(nbits) & 1 : 0;
     const double sk = c->params.skin_s, opg = 1.0 + c->params.skin_g;
-    int64_t nbc = 0, nbs = 0, nbr = 0;
+    SortSeg *segs = (SortSeg *)c->h_bj;
+    BackJob *bj = job_table<BackJob>(c->h_bj, J);
+    BackJob *d_bj = job_table<BackJob>(c->d_bj, J);
+    int64_t nbc = 0, nbs = 0, nbr = 0, tiles = 0;
     for (int r = 0; r < J; ++r) {
         const BuildJob &j = jobs[qs[r]];
         const int64_t m = ms[qs[r]];
         Seg &s = c->segs[j.k];
-        BackJob &B = c->h_bj[r];
-        SortSeg &g = c->h_segs[r];
+        BackJob &B = bj[r];
+        SortSeg &g = segs[r];
         g.k[0] = c->larena + j.loff;
         g.k[1] = c->ltmp + j.loff;
         g.v[0] = g.v[1] = nullptr;
         g.n = m;
+        g.t0 = tiles;
+        g.nt = (m + kSortTile - 1) / kSortTile;
+        tiles += g.nt;
         B.srt = (spar ? c->ltmp : c->larena) + j.loff;
         B.m = m;
         B.n = s.n;
@@ -830,14 +832,13 @@ static int build_backs(rcp_ctx *c, std::vector<BuildJob> &jobs, const std::vecto
         s.rebuilds += 1;
         c->stats.rebuilds += 1;
     }
-    HIPCHK(hipMemcpyAsync(c->d_bj, c->h_bj, sizeof(BackJob) * J, hipMemcpyHostToDevice,
-                          c->stream));
-    int par = 0;
-    CHK(sort_segments(c, J, nbits, false, &par));
+    HIPCHK(hipMemcpyAsync(c->d_bj, c->h_bj, (sizeof(SortSeg) + sizeof(BackJob)) * J,
+                          hipMemcpyHostToDevice, c->stream));
+    const int par = radix_sort_segs((const SortSeg *)c->d_bj, J, tiles, nbits, false, c->shist,
+                                    c->stot, c->stream);
     if (par != spar) return fail(RCP_EDEVICE, "internal: entry sort parity");
-    launch_csr_seg(c->d_bj, J, nbc, c->stream);
-    launch_items_seg(c->d_bj, J, nbs, nbr, c->stream);
-    launch_after_seg(c->d_bj, J, c->d_state, c->d_ptrs, c->stream);
+    launch_csr_seg(d_bj, J, nbc, nbs, c->stream);
+    launch_items_seg(d_bj, J, nbr, c->d_state, c->d_ptrs, c->stream);
     HIPCHK(hipGetLastError());
     return RCP_OK;
 }
@@ -1667,7 +1668,6 @@ static void destroy_ctx(rcp_ctx *c)
     dfree(c->ltmp);
     dfree(c->shist);
     dfree(c->stot);
-    dfree(c->d_segs);
     dfree(c->larena);
     dfree(c->harena);
     dfree(c->darena);
