@@ -76,7 +76,15 @@ __device__ __forceinline__ void wave_sync()
 // Several independent arrays (segments) are sorted by one sequence of
 // launches: every launch covers the tiles of all segments, a block finding
 // its segment by binary search over the segments' first tiles.  Histograms
-// are laid out per segment, digit-major: hist[D t0 + d nt + t], D digits.
+// are laid out per segment, digit-major: hist[D t0 + d nt + t], D digits; or,
+// where no segment has more than kFewTiles, tile by tile: hist[D (t0 + t) + d].
+// Then each scatter block adds the tiles' counts itself and there is no scan
+// in between, and with one tile a segment no histogram either.
+enum { kScanned = 0, kFew = 1, kSingle = 2 };
+// Whole builds, us, scanned / few from 64 tiles on: 512 spheres (1 tile of
+// keys, 4 of entries) 90 / 80, 8784 spheres (5 and 11) 157 / 147; 6e4 spheres
+// (30 and 129) the same, 172.
+constexpr int64_t kFewTiles = 64;
 
 // Segment of tile b: the last segment whose first tile is <= b.
 __device__ __forceinline__ int seg_of_tile(const SortSeg *__restrict__ sg, int nseg, int64_t b)
@@ -91,7 +99,7 @@ __device__ __forceinline__ int seg_of_tile(const SortSeg *__restrict__ sg, int n
 }
 
 __global__ __launch_bounds__(kBlock) void k_radix_hist(const SortSeg *__restrict__ sg, int nseg,
-                                                      int par, int shift, int bits,
+                                                      int par, int shift, int bits, int few,
                                                       uint32_t *__restrict__ hist)
 {
     __shared__ uint32_t cnt[kMaxDigits];
@@ -121,7 +129,7 @@ __global__ __launch_bounds__(kBlock) void k_radix_hist(const SortSeg *__restrict
     }
     __syncthreads();
     for (uint32_t d = threadIdx.x; d < D; d += kBlock)
-        hist[(int64_t)D * t0 + (int64_t)d * nt + t] = cnt[d];
+        hist[(int64_t)D * t0 + (few ? (int64_t)D * t + d : (int64_t)d * nt + t)] = cnt[d];
 }
 
 // Block (j, d): exclusive scan, in place, of digit d's tile counts in
@@ -154,7 +162,7 @@ __global__ __launch_bounds__(kBlock) void k_radix_rowscan(const SortSeg *__restr
     if (threadIdx.x == 0) totals[blockIdx.x] = carry;
 }
 
-template <bool kVals>
+template <bool kVals, int kMode>
 __global__ __launch_bounds__(kBlock) void k_radix_scatter(const SortSeg *__restrict__ sg, int nseg,
                                                          int par, int shift, int bits,
                                                          const uint32_t *__restrict__ off,
@@ -189,7 +197,19 @@ __global__ __launch_bounds__(kBlock) void k_radix_scatter(const SortSeg *__restr
     // this thread's two digits: totals in the segment, counts in earlier tiles
     const uint32_t d0 = 2u * (uint32_t)tid;
     uint32_t tot0 = 0, tot1 = 0, off0 = 0, off1 = 0;
-    if (d0 < D) {
+    if (kMode == kFew && d0 < D) {
+        const uint32_t *c = off + (int64_t)D * t0 + d0;
+        const bool two = d0 + 1 < D;
+#pragma unroll 8
+        for (int64_t q = 0; q < nt; ++q) {
+            const uint32_t a = gload(c, q * D), b = two ? gload(c, q * D + 1) : 0u;
+            tot0 += a;
+            tot1 += b;
+            off0 += q < t ? a : 0u;
+            off1 += q < t ? b : 0u;
+        }
+    }
+    if (kMode == kScanned && d0 < D) {
         tot0 = totals[(uint64_t)j * D + d0];
         off0 = off[(int64_t)D * t0 + (int64_t)d0 * nt + t];
         if (d0 + 1 < D) {
@@ -229,6 +249,10 @@ __global__ __launch_bounds__(kBlock) void k_radix_scatter(const SortSeg *__restr
         c1[k] = n1;
         n0 += cnt[k][d0];
         n1 += cnt[k][d0 + 1];
+    }
+    if (kMode == kSingle) {
+        tot0 = n0;
+        tot1 = n1;
     }
     // one scan for both: tile counts above bit 40, segment totals below
     const uint64_t ex =
@@ -286,25 +310,43 @@ void launch_put_segs(SortSeg *dst, const SortSeg *src, int nseg, hipStream_t s)
     }
 }
 
-int radix_sort_segs(const SortSeg *sg, int nseg, int64_t ntiles, int nbits, bool vals,
-                    uint32_t *hist, uint32_t *totals, hipStream_t s)
+template <bool kVals>
+static void launch_scatter(int mode, int64_t ntiles, hipStream_t s, const SortSeg *sg, int nseg,
+                           int par, int shift, int bits, const uint32_t *hist,
+                           const uint32_t *totals)
+{
+    const dim3 g((unsigned)ntiles), t(kBlock);
+    if (mode == kSingle)
+        hipLaunchKernelGGL((k_radix_scatter<kVals, kSingle>), g, t, 0, s, sg, nseg, par, shift,
+                           bits, hist, totals);
+    else if (mode == kFew)
+        hipLaunchKernelGGL((k_radix_scatter<kVals, kFew>), g, t, 0, s, sg, nseg, par, shift, bits,
+                           hist, totals);
+    else
+        hipLaunchKernelGGL((k_radix_scatter<kVals, kScanned>), g, t, 0, s, sg, nseg, par, shift,
+                           bits, hist, totals);
+}
+
+int radix_sort_segs(const SortSeg *sg, int nseg, int64_t ntiles, int64_t most_tiles, int nbits,
+                    bool vals, uint32_t *hist, uint32_t *totals, hipStream_t s)
 {
     if (nseg <= 0 || ntiles <= 0) return 0;
+    const int mode = most_tiles <= 1 ? kSingle : (most_tiles <= kFewTiles ? kFew : kScanned);
     int par = 0;
     const int passes = sort_passes(nbits);
     for (int q = 0, shift = 0; q < passes; ++q) {
         // as even as can be: the last passes take the odd bits
         const int bits = (nbits - shift) / (passes - q);
-        hipLaunchKernelGGL(k_radix_hist, dim3((unsigned)ntiles), dim3(kBlock), 0, s, sg, nseg,
-                           par, shift, bits, hist);
-        hipLaunchKernelGGL(k_radix_rowscan, dim3((unsigned)nseg << bits), dim3(kBlock), 0, s, sg,
-                           bits, hist, totals);
+        if (mode != kSingle)
+            hipLaunchKernelGGL(k_radix_hist, dim3((unsigned)ntiles), dim3(kBlock), 0, s, sg, nseg,
+                               par, shift, bits, mode == kFew ? 1 : 0, hist);
+        if (mode == kScanned)
+            hipLaunchKernelGGL(k_radix_rowscan, dim3((unsigned)nseg << bits), dim3(kBlock), 0, s,
+                               sg, bits, hist, totals);
         if (vals)
-            hipLaunchKernelGGL(k_radix_scatter<true>, dim3((unsigned)ntiles), dim3(kBlock), 0, s,
-                               sg, nseg, par, shift, bits, hist, totals);
+            launch_scatter<true>(mode, ntiles, s, sg, nseg, par, shift, bits, hist, totals);
         else
-            hipLaunchKernelGGL(k_radix_scatter<false>, dim3((unsigned)ntiles), dim3(kBlock), 0, s,
-                               sg, nseg, par, shift, bits, hist, totals);
+            launch_scatter<false>(mode, ntiles, s, sg, nseg, par, shift, bits, hist, totals);
         shift += bits;
         par ^= 1;
     }

@@ -19,11 +19,11 @@ constexpr int64_t kSortDigits = 512;   // at most, per pass
 constexpr int sort_passes(int nbits) { return (nbits + 8) / 9; }
 // Stable LSD radix sort of every segment sg[0..nseg) (device memory) on the
 // low nbits of its keys, by one sequence of launches over all ntiles
-// tiles; returns the buffer index (the same for all segments) that holds
-// the result.  hist needs kSortDigits * ntiles entries, totals
+// tiles (most_tiles: of the largest segment); returns the buffer index (the
+// same for all segments) that holds the result.  hist needs kSortDigits * ntiles entries, totals
 // kSortDigits * nseg.
-int radix_sort_segs(const SortSeg *sg, int nseg, int64_t ntiles, int nbits, bool vals,
-                    uint32_t *hist, uint32_t *totals, hipStream_t s);
+int radix_sort_segs(const SortSeg *sg, int nseg, int64_t ntiles, int64_t most_tiles, int nbits,
+                    bool vals, uint32_t *hist, uint32_t *totals, hipStream_t s);
 // Write nseg host descriptors to dst (device) in stream order.
 void launch_put_segs(SortSeg *dst, const SortSeg *src, int nseg, hipStream_t s);
 

@@ -671,7 +671,7 @@ static int build_fronts(rcp_ctx *c, std::vector<BuildJob> &jobs, int nl)
     SortSeg *segs = (SortSeg *)c->h_fj;
     FrontJob *fj = job_table<FrontJob>(c->h_fj, J);
     FrontJob *d_fj = job_table<FrontJob>(c->d_fj, J);
-    int64_t nb = 0, nbt = 0, tiles = 0;
+    int64_t nb = 0, nbt = 0, tiles = 0, most = 0;
     for (int q = 0; q < J; ++q) {
         BuildJob &j = jobs[q];
         Seg &s = c->segs[j.k];
@@ -724,13 +724,14 @@ static int build_fronts(rcp_ctx *c, std::vector<BuildJob> &jobs, int nl)
         g.t0 = tiles;
         g.nt = (g.n + kSortTile - 1) / kSortTile;
         tiles += g.nt;
+        most = std::max(most, g.nt);
         s.set = nset;
         s.cur = ncur;
     }
     HIPCHK(hipMemcpyAsync(c->d_fj, c->h_fj, (sizeof(SortSeg) + sizeof(FrontJob)) * J,
                           hipMemcpyHostToDevice, c->stream));
     launch_keys_seg(d_fj, J, nb, nbt, c->stream);
-    const int par = radix_sort_segs((const SortSeg *)c->d_fj, J, tiles, nbits, true, c->shist,
+    const int par = radix_sort_segs((const SortSeg *)c->d_fj, J, tiles, most, nbits, true, c->shist,
                                     c->stot, c->stream);
     if (par != spar) return fail(RCP_EDEVICE, "internal: key sort parity");
     launch_permute_seg(d_fj, J, nb, c->stream);
@@ -776,7 +777,7 @@ static int build_backs(rcp_ctx *c, std::vector<BuildJob> &jobs, const std::vecto
     SortSeg *segs = (SortSeg *)c->h_bj;
     BackJob *bj = job_table<BackJob>(c->h_bj, J);
     BackJob *d_bj = job_table<BackJob>(c->d_bj, J);
-    int64_t nbc = 0, nbs = 0, nbr = 0, tiles = 0;
+    int64_t nbc = 0, nbs = 0, nbr = 0, tiles = 0, most = 0;
     for (int r = 0; r < J; ++r) {
         const BuildJob &j = jobs[qs[r]];
         const int64_t m = ms[qs[r]];
@@ -790,6 +791,7 @@ static int build_backs(rcp_ctx *c, std::vector<BuildJob> &jobs, const std::vecto
         g.t0 = tiles;
         g.nt = (m + kSortTile - 1) / kSortTile;
         tiles += g.nt;
+        most = std::max(most, g.nt);
         B.srt = (spar ? c->ltmp : c->larena) + j.loff;
         B.m = m;
         B.n = s.n;
@@ -834,7 +836,7 @@ static int build_backs(rcp_ctx *c, std::vector<BuildJob> &jobs, const std::vecto
     }
     HIPCHK(hipMemcpyAsync(c->d_bj, c->h_bj, (sizeof(SortSeg) + sizeof(BackJob)) * J,
                           hipMemcpyHostToDevice, c->stream));
-    const int par = radix_sort_segs((const SortSeg *)c->d_bj, J, tiles, nbits, false, c->shist,
+    const int par = radix_sort_segs((const SortSeg *)c->d_bj, J, tiles, most, nbits, false, c->shist,
                                     c->stot, c->stream);
     if (par != spar) return fail(RCP_EDEVICE, "internal: entry sort parity");
     launch_csr_seg(d_bj, J, nbc, nbs, c->stream);
@@ -1426,7 +1428,7 @@ static int place_device(rcp_ctx *c, int k, uint64_t seed, int64_t window, int64_
     g.nt = tiles;
     SortSeg *dseg = (SortSeg *)(ws + o_seg);
     launch_put_segs(dseg, &g, 1, c->stream);
-    const int par = radix_sort_segs(dseg, 1, tiles, 64, true, c->shist, c->stot, c->stream);
+    const int par = radix_sort_segs(dseg, 1, tiles, tiles, 64, true, c->shist, c->stot, c->stream);
     a.ord = (const int32_t *)(par ? c->svB : c->svA);
     // the state comes back once for several rounds (three launches each)
     constexpr int kRounds = 8;

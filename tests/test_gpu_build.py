@@ -60,3 +60,20 @@ def test_pairs_of_a_batch(rcp, orc):
         oi, oj = orc.pairs_brute(x, d, L, 1.0, 0.2, 0.02)
         assert np.array_equal(gi, oi) and np.array_equal(gj, oj)
     p.close()
+
+
+@pytest.mark.parametrize("n", [131072, 131073])   # 64 tiles of keys, and one key more
+def test_pairs_of_sampled_rows_at_the_longest_unscanned_sort(rcp, orc, n):
+    d, L, x = _poly(n, 11)
+    p = rcp.Packing(d, L, 1.0, 0, init="none", params=rcp.make_params(skin_s=0.1, skin_g=0.02))
+    p.set_state(x, 1.0)
+    p.neighbor_build()
+    gi, gj = p.pairs()
+    p.close()
+    rows = np.sort(np.random.default_rng(n).choice(n, 800, replace=False))
+    want = orc.rows_pairs(x, d, L, 1.0, rows, 0.1, 0.02)
+    i, j = np.concatenate([gi, gj]), np.concatenate([gj, gi])
+    order = np.lexsort((j, i))
+    i, j = i[order], j[order]
+    for r, a, b, w in zip(rows, np.searchsorted(i, rows), np.searchsorted(i, rows, "right"), want):
+        assert np.array_equal(j[a:b], w), int(r)
