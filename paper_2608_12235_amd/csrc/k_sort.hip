@@ -81,10 +81,11 @@ __device__ __forceinline__ void wave_sync()
 // Then each scatter block adds the tiles' counts itself and there is no scan
 // in between, and with one tile a segment no histogram either.
 enum { kScanned = 0, kFew = 1, kSingle = 2 };
-// Whole builds, us, scanned / few from 64 tiles on: 512 spheres (1 tile of
-// keys, 4 of entries) 90 / 80, 8784 spheres (5 and 11) 157 / 147; 6e4 spheres
-// (30 and 129) the same, 172.
-constexpr int64_t kFewTiles = 64;
+// Whole builds, us, scanned / not: 512 spheres (1 tile of keys, 4 of
+// entries) 90 / 80, 8784 spheres (5 and 11) 157 / 149; 6e4 spheres (30 of
+// keys) the same, 172.  At 59 tiles a scatter takes 11.7 us instead of 7.3
+// and saves a scan of 2.4 and its launch: no gain.
+constexpr int64_t kFewTiles = 32;
 
 // Segment of tile b: the last segment whose first tile is <= b.
 __device__ __forceinline__ int seg_of_tile(const SortSeg *__restrict__ sg, int nseg, int64_t b)

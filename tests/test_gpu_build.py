@@ -62,7 +62,7 @@ def test_pairs_of_a_batch(rcp, orc):
     p.close()
 
 
-@pytest.mark.parametrize("n", [131072, 131073])   # 64 tiles of keys, and one key more
+@pytest.mark.parametrize("n", [65536, 65537, 131073])   # 32 tiles of keys, one key more
 def test_pairs_of_sampled_rows_at_the_longest_unscanned_sort(rcp, orc, n):
     d, L, x = _poly(n, 11)
     p = rcp.Packing(d, L, 1.0, 0, init="none", params=rcp.make_params(skin_s=0.1, skin_g=0.02))
