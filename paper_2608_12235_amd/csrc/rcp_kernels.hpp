@@ -302,10 +302,11 @@ void launch_check_positions(double *x, int64_t n, double L, int bounded, uint32_
 // A state handed in, unless bad is given and *bad set (k_sort.hip).
 void launch_set_state(const SegPtrs *P, SegState *S, int seg, int64_t n, const double *xu,
                       double kappa, const uint32_t *bad, hipStream_t s);
-// Shrink to contact: per-block minima of the pair contact scales in
-// part[0..nblocks), their minimum in part[nblocks].
+// Shrink to contact: minima of the pair contact scales per block in
+// part[0..shrink_blocks(n)), their minimum in the entry after them.
+int shrink_blocks(int64_t n);
 void launch_shrink(const SegPtrs *P, const SegState *S, int seg, int64_t n, double *part,
-                   int nblocks, hipStream_t s);
+                   hipStream_t s);
 // out[0] = max of part[0..nblocks)
 void launch_max_finish(const double *part, int nblocks, double *out, hipStream_t s);
 

@@ -1306,10 +1306,10 @@ static int shrink_seg(rcp_ctx *c, int k, double *kp_out, double *phi_out)
     }
     if (c->h_state[k].flags & (F_REBUILD | F_STALE)) CHK(rebuild(c, k, c->h_state[k].kappa));
     Seg &s = c->segs[k];
-    const int nb = (int)std::max<int64_t>(1, (s.n + kBlock - 1) / kBlock);
+    const int nb = shrink_blocks(s.n);
     CHK(dgrow(&c->part, &c->part_cap, 4 * (int64_t)nb + 8));
     HIPCHK(hipEventRecord(c->e0, c->stream));
-    launch_shrink(c->d_ptrs, c->d_state, k, s.n, c->part, nb, c->stream);
+    launch_shrink(c->d_ptrs, c->d_state, k, s.n, c->part, c->stream);
     HIPCHK(hipEventRecord(c->e1, c->stream));
     double kmin = 0;
     HIPCHK(hipMemcpyAsync(&kmin, c->part + nb, sizeof kmin, hipMemcpyDeviceToHost, c->stream));

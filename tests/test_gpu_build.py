@@ -77,3 +77,19 @@ def test_pairs_of_sampled_rows_at_the_longest_unscanned_sort(rcp, orc, n):
     i, j = i[order], j[order]
     for r, a, b, w in zip(rows, np.searchsorted(i, rows), np.searchsorted(i, rows, "right"), want):
         assert np.array_equal(j[a:b], w), int(r)
+
+
+@pytest.mark.parametrize("n,skin", [(1, 0.3), (2, 0.3), (31, 0.3), (33, 4.0), (700, 3.0),
+                                    (33000, 0.2)])
+def test_shrink_scale_of_short_and_long_rows(rcp, orc, n, skin):
+    # rows of none to hundreds of pairs, eight lanes a row
+    d, L, x = _poly(n, 3 * n)
+    if n <= 40:   # a cluster in a box that the listing cutoff fits
+        L, x = 30.0 * d.max(), x / L * 3.0 * d.max()
+    p = rcp.Packing(d, L, 1.0, 0, init="none", params=rcp.make_params(skin_s=skin, skin_g=0.02))
+    p.set_state(x, 1.0)
+    p.neighbor_build()
+    kp, _ = p.shrink()
+    p.close()
+    i, j = orc.pairs_brute(x, d, L, 1.0, skin, 0.02)
+    assert kp == orc.shrink(x, d, L, 1.0, i, j)
