@@ -1471,8 +1471,8 @@ __global__ __launch_bounds__(kTailBlock) void k_tail(const SegState *S, SegState
 // [b * wk, (b + 1) * wk), i.e. it begins at the first row with w(i) >= b * wk.
 // Row i is that first row for the items b with w(i - 1) < b * wk <= w(i),
 // so one thread per row writes every boundary exactly once; items past the
-// last row keep begin = end = n from the fill.  With wk <= 256 rc no item
-// holds more than 256 rows.
+// last row keep begin = end = n from the fill.  An item holds at most
+// ceil(wk / rc) rows; the wave kernels need 64 or fewer (item_rows_max).
 __global__ __launch_bounds__(kBlock) void k_items_fill(WorkItem *__restrict__ W, int64_t nslots,
                                                       int seg, const int32_t *__restrict__ rp,
                                                       int64_t n, int item_work)

@@ -1,0 +1,71 @@
+// Host arithmetic of the launches, free of HIP so that it can be compiled and
+// checked on its own: the cut of a packing's rows into work items.
+#pragma once
+#include "rcp.h"
+
+#include <algorithm>
+#include <cstdint>
+
+namespace rcp {
+
+constexpr int kWave = 64;
+constexpr int kBlock = 256;
+constexpr int kWavesPerBlock = kBlock / kWave;
+
+// The cut of the rows into work items, one a wave, four a block (the kernels
+// that take a block's rows together join its four): a row costs row_units
+// plus one per partner, an item holds item_units.  A wave takes a sixth
+// of the tuning's item_work, and a row two thirds of its row_cost: by the
+// defaults (6, 1536) 256 units at 4 a row, so up to 64 rows, about 40 on the
+// dense million-sphere state (2.3 partners a row).  Measured there, on 3e6
+// spheres of size ratio 5e5 and on 1e5 spheres with 5.2 partners, us per
+// launch: 42.2 / 126 / 13.8; with a quarter of both, 384 units at 6, 42.8 /
+// 127 / 16.0, with 256 at 5 46.7 / 130 / 14.3, with 192 at 3 43.1 / 128 /
+// 13.7 (and more partials for the tail).
+//
+// The wave kernels hold a row a lane, so their items have at most 64 rows:
+// item_work <= 256 row_cost gives no more.  With variant bit 5 (512 row_cost)
+// an item may have 128, for the kernel that takes 512 rows a block; `waves`
+// cuts it to 64.
+//
+// A packing of fewer than kFineItems such items is cut finer, down to one
+// round of 64 entries an item: a wave of its own is then free for every
+// round.  512 spheres with 13.6 partners, us per launch: 6.8 against 7.9.
+// The rule looks at the packing alone (a batch must give it the same bits as
+// a context of its own), so the line lies where a census of 16 packings of
+// 2e3 to 3.4e4 spheres does not slow down: 12.7 us with 96 items, 14.1 with
+// 128, 15.7 with 512, although 8784 spheres alone would gain by 512 (7.2
+// against 8.7).
+constexpr int64_t kFineItems = 96;
+
+inline int row_units(const rcp_tuning &t) { return (2 * t.row_cost + 2) / 3; }
+
+// Units of an item at most, whatever the packing.
+inline int item_units_max(const rcp_tuning &t, bool waves)
+{
+    const int64_t wk = std::max(1, t.item_work / 6);
+    return (int)(waves ? std::min<int64_t>(wk, (int64_t)kWave * row_units(t)) : wk);
+}
+
+// Rows of an item at most: row i has the work coordinate row_units i + rp[i],
+// and an item the rows of one stretch of item_units of it.
+inline int item_rows_max(const rcp_tuning &t, bool waves)
+{
+    return (item_units_max(t, waves) + row_units(t) - 1) / row_units(t);
+}
+
+inline int item_units(const rcp_tuning &t, bool waves, int64_t n, int64_t entries)
+{
+    const int64_t fine = (row_units(t) * n + entries) / kFineItems;
+    return (int)std::min<int64_t>(item_units_max(t, waves), std::max<int64_t>(fine, kWave));
+}
+
+// Item slots for n rows and that many entries: enough for all units, plus
+// one, in whole blocks.
+inline int64_t item_slots(const rcp_tuning &t, bool waves, int64_t n, int64_t entries)
+{
+    const int64_t k = (row_units(t) * n + entries) / item_units(t, waves, n, entries) + 2;
+    return (k + kWavesPerBlock - 1) / kWavesPerBlock * kWavesPerBlock;
+}
+
+}  // namespace rcp

@@ -10,11 +10,10 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include "launch_plan.hpp"
+
 namespace rcp {
 
-constexpr int kWave = 64;
-constexpr int kBlock = 256;
-constexpr int kWavesPerBlock = kBlock / kWave;
 constexpr int kMaxRungs = 16;
 constexpr int kMaxLevels = 48;
 

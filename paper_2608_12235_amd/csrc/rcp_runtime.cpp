@@ -161,6 +161,7 @@ struct rcp_ctx {
     SchedDev *d_sched = nullptr, *h_sched = nullptr;   // schedules of a batch (device, pinned)
     WorkItem *d_work = nullptr;
     int nitems = 0;
+    int item_rows = 0;              // rows of an item of d_work at most
     int64_t items_cap = 0;
     double *d_partials = nullptr;   // two sets of items_cap
     uint32_t *totals = nullptr;      // small device counters
@@ -327,46 +328,21 @@ static int scratch_address(double **out)
 constexpr double kXrefErr = 1.7320508075688772 * 0x1p-23;
 
 // ------------------------------------------------------------ work table
-// The cut of the rows into work items, one a wave, four a block (the kernels
-// that take a block's rows together join its four): a row costs row_units
-// plus one per partner, an item holds wave_work units.  A wave takes a sixth
-// of the tuning's item_work, and a row two thirds of its row_cost: by the
-// defaults (6, 1536) 256 units at 4 a row, so up to 64 rows, about 40 on the
-// dense million-sphere state (2.3 partners a row).  Measured there, on 3e6
-// spheres of size ratio 5e5 and on 1e5 spheres with 5.2 partners, us per
-// launch: 42.2 / 126 / 13.8; with a quarter of both, 384 units at 6, 42.8 /
-// 127 / 16.0, with 256 at 5 46.7 / 130 / 14.3, with 192 at 3 43.1 / 128 /
-// 13.7 (and more partials for the tail).  item_work <= 256 row_cost keeps an
-// item within the wave kernel's 64 rows; with variant bit 5 (512 row_cost)
-// they are cut to that when the packings are of a kind that only the wave
-// kernel takes.
-//
-// A packing of fewer than kFineItems such items is cut finer, down to one
-// round of 64 entries an item: a wave of its own is then free for every
-// round.  512 spheres with 13.6 partners, us per launch: 6.8 against 7.9.
-// The rule looks at the packing alone (a batch must give it the same bits as
-// a context of its own), so the line lies where a census of 16 packings of
-// 2e3 to 3.4e4 spheres does not slow down: 12.7 us with 96 items, 14.1 with
-// 128, 15.7 with 512, although 8784 spheres alone would gain by 512 (7.2
-// against 8.7).
-constexpr int64_t kFineItems = 96;
-static int row_units(const rcp_ctx *c) { return (2 * c->tuning.row_cost + 2) / 3; }
+// (the cut itself: see launch_plan.hpp)
+static int row_units(const rcp_ctx *c) { return row_units(c->tuning); }
+
+// Whether only the wave kernels run on this context's packings, whatever the
+// tuning's variant.
+static bool waves_only(const rcp_ctx *c) { return c->any_mixed || c->any_walls || c->dim == 2; }
 
 static int wave_work(const rcp_ctx *c, int64_t n, int64_t entries)
 {
-    int64_t wk = std::max(1, c->tuning.item_work / 6);
-    if (c->any_mixed || c->any_walls || c->dim == 2)
-        wk = std::min<int64_t>(wk, (int64_t)kWave * row_units(c));
-    const int64_t fine = (row_units(c) * n + entries) / kFineItems;
-    return (int)std::min(wk, std::max<int64_t>(fine, kWave));
+    return item_units(c->tuning, waves_only(c), n, entries);
 }
 
-// Work-item slots for packing k: enough for row_units * n + slot_entries
-// units of wave_work each, plus one, in whole blocks.
 static int64_t slots_for(const rcp_ctx *c, int64_t n, int64_t entries)
 {
-    const int64_t k = (row_units(c) * n + entries) / wave_work(c, n, entries) + 2;
-    return (k + kWavesPerBlock - 1) / kWavesPerBlock * kWavesPerBlock;
+    return item_slots(c->tuning, waves_only(c), n, entries);
 }
 
 // Cut the rows of a built packing into work items (device kernel on its
@@ -404,6 +380,7 @@ static int build_work(rcp_ctx *c)
         c->items_cap = total;
     }
     c->nitems = (int)total;
+    c->item_rows = item_rows_max(c->tuning, waves_only(c));
     const int ns = (int)c->segs.size();
     for (int k = 0; k < ns; ++k) {
         c->h_layout[2 * k] = c->segs[k].blocks;
@@ -1014,6 +991,14 @@ static bool tail_ahead(const rcp_ctx *c)
     return c->nitems <= max_pre_blocks();
 }
 
+// The wave kernels take no item of more rows than a wave has lanes.
+static int check_items(const rcp_ctx *c, int flags)
+{
+    if (iterate_takes_waves(flags) && c->item_rows > kWave)
+        return fail(RCP_EDEVICE, "internal: work items of %d rows for a wave kernel", c->item_rows);
+    return RCP_OK;
+}
+
 // K iterations: gradient + Adam kernel and tail kernel each, bracketed by
 // the slot's three events when the slot is timed.  With the tail ahead,
 // records and partials go back and forth between two sets and only the last
@@ -1022,6 +1007,7 @@ static int launch_iterations(rcp_ctx *c, int K)
 {
     const bool fused = tail_fused(c), ahead = tail_ahead(c);
     const int flags = iterate_flags(c) | (fused ? 2 : 0), ns = (int)c->segs.size();
+    CHK(check_items(c, flags));
     SegState *S[2] = {c->d_state, c->d_state + ns};
     double *part[2] = {c->d_partials, c->d_partials + 4 * c->items_cap};
     for (int slot = 0; slot < K; ++slot) {
@@ -1735,7 +1721,7 @@ void rcp_tuning_default(rcp_tuning *t)
     // cooperative pair search; whole 32-byte records written (measured at
     // least as fast as writing the three coordinates alone)
     t->variant = 64 | 128;
-    // work items: see wave_work
+    // work items: see launch_plan.hpp
     t->row_cost = 6;
     t->item_work = 1536;
     t->time_kernels = 0;
@@ -2352,14 +2338,16 @@ static int eval_current(rcp_ctx *c, int k, const P4 *q, double kappa, double mu,
                         double *E, double *gk, hipStream_t st)
 {
     Seg &s = c->segs[k];
-    // the packing's items in the work table; a finished packing has given
-    // them up, and its rows are cut here
+    // the packing's items in the work table; its rows are cut here when it is
+    // finished and has given them up, or when the table is cut for a kernel
+    // that takes more rows an item than a wave has lanes
     const WorkItem *w = c->d_work + s.first_item * kWavesPerBlock;
     int nb = s.blocks;
-    if (s.parked) {
-        const int64_t slots = slots_for(c, s.n, s.nnz);
+    if (s.parked || c->item_rows > kWave) {
+        const int64_t slots = item_slots(c->tuning, true, s.n, s.nnz);
         CHK(dgrow(&c->eitems, &c->eitems_cap, slots));
-        launch_items(s.rp, s.n, k, row_units(c), wave_work(c, s.n, s.nnz), c->eitems, slots, st);
+        launch_items(s.rp, s.n, k, row_units(c), item_units(c->tuning, true, s.n, s.nnz), c->eitems,
+                     slots, st);
         w = c->eitems;
         nb = (int)(slots / kWavesPerBlock);
     }
@@ -2710,6 +2698,7 @@ int rcp_time_iterations(rcp_ctx *c, int64_t n_iters, double *iterate_us, double 
 {
     if (!c || n_iters < 1) return fail(RCP_EINVAL, "bad arguments");
     const int ns = (int)c->segs.size();
+    CHK(check_items(c, iterate_flags(c)));
     hipLaunchKernelGGL(k_extend, dim3((ns + 63) / 64), dim3(64), 0, c->stream, c->d_state, ns,
                        n_iters);
     constexpr int kBatch = 32;

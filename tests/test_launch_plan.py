@@ -1,0 +1,79 @@
+"""The host arithmetic of the launches (csrc/launch_plan.hpp), compiled on its
+own with the host compiler: the cut of the rows into work items."""
+import ctypes as C
+import os
+import subprocess
+
+import numpy as np
+import pytest
+
+from paper_2608_12235_amd._lib import Tuning
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+CSRC = os.path.join(ROOT, "paper_2608_12235_amd", "csrc")
+
+SOURCE = """
+#include "launch_plan.hpp"
+using namespace rcp;
+extern "C" {
+int units_row(const rcp_tuning *t) { return row_units(*t); }
+int units_item(const rcp_tuning *t, int waves, int64_t n, int64_t e) { return item_units(*t, waves, n, e); }
+int rows_max(const rcp_tuning *t, int waves) { return item_rows_max(*t, waves); }
+int64_t slots(const rcp_tuning *t, int waves, int64_t n, int64_t e) { return item_slots(*t, waves, n, e); }
+}
+"""
+
+
+@pytest.fixture(scope="module")
+def plan(tmp_path_factory):
+    d = tmp_path_factory.mktemp("plan")
+    src, lib = str(d / "plan.cpp"), str(d / "plan.so")
+    with open(src, "w") as f:
+        f.write(SOURCE)
+    subprocess.run(["g++", "-std=c++17", "-O1", "-Wall", "-Werror", "-shared", "-fPIC", "-I", CSRC,
+                    "-I", os.path.join(ROOT, "include"), src, "-o", lib], check=True)
+    L = C.CDLL(lib)
+    L.slots.restype = C.c_int64
+    L.slots.argtypes = L.units_item.argtypes = [C.c_void_p, C.c_int, C.c_int64, C.c_int64]
+    return L
+
+
+def _tuning(**kw):
+    t = Tuning()
+    t.row_cost, t.item_work, t.variant = 6, 1536, 192
+    for k, v in kw.items():
+        setattr(t, k, v)
+    return t
+
+
+def _items(plan, t, waves, degrees):
+    """Rows of every item of the cut, and the slots there are for them."""
+    n, m = len(degrees), int(np.sum(degrees))
+    rp = np.concatenate([[0], np.cumsum(degrees)])[:-1]
+    w = (plan.units_row(C.byref(t)) * np.arange(n) + rp) // plan.units_item(C.byref(t), waves, n, m)
+    return np.bincount(w), plan.slots(C.byref(t), waves, n, m)
+
+
+@pytest.mark.parametrize("row_cost,item_work,variant", [
+    (6, 1536, 192), (6, 3072, 224), (1, 512, 32), (1, 1, 192), (4, 1024, 192), (4, 2048, 32),
+    (65536, 65536 * 512, 32), (7, 3583, 32), (64, 16384, 0)])
+@pytest.mark.parametrize("n", [1, 64, 2000, 6239, 30011])
+def test_items_fit_a_wave_and_the_table(plan, row_cost, item_work, variant, n):
+    t = _tuning(row_cost=row_cost, item_work=item_work, variant=variant)
+    rng = np.random.default_rng(n)
+    for deg in (np.zeros(n, int), np.ones(n, int), rng.integers(0, 3, n), rng.integers(0, 40, n)):
+        for waves in (1, 0):
+            rows, slots = _items(plan, t, waves, deg)
+            assert len(rows) <= slots and slots % 4 == 0
+            assert rows.max() <= plan.rows_max(C.byref(t), waves)
+            assert rows.max() <= (64 if waves or not variant & 32 else 128)
+
+
+def test_wide_items_have_more_rows_than_lanes(plan):
+    # sparse rows at 6 / 3072: the cut for the 512-row kernel, which a kernel
+    # with a row a lane must not be given
+    t = _tuning(row_cost=6, item_work=3072, variant=224)
+    rows, _ = _items(plan, t, 0, np.zeros(20000, int))
+    assert rows.max() == 128 and plan.rows_max(C.byref(t), 0) == 128
+    rows, _ = _items(plan, t, 1, np.zeros(20000, int))
+    assert rows.max() == 64 and plan.rows_max(C.byref(t), 1) == 64
