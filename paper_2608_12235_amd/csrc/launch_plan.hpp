@@ -1,5 +1,6 @@
 // Host arithmetic of the launches, free of HIP so that it can be compiled and
-// checked on its own: the cut of a packing's rows into work items.
+// checked on its own: the cut of a packing's rows into work items, and what
+// runs an iteration's tail.
 #pragma once
 #include "rcp.h"
 
@@ -66,6 +67,15 @@ inline int64_t item_slots(const rcp_tuning &t, bool waves, int64_t n, int64_t en
 {
     const int64_t k = (row_units(t) * n + entries) / item_units(t, waves, n, entries) + 2;
     return (k + kWavesPerBlock - 1) / kWavesPerBlock * kWavesPerBlock;
+}
+
+// Whether the gradient kernel runs the tail itself: only the block-per-item
+// kernels have that form, not the wave kernels (`waves`: nothing else runs,
+// whatever the tuning), the persistent one (bit 3) or the one of 512 rows a
+// block (bit 5).
+inline bool fuses_tail(const rcp_tuning &t, bool waves)
+{
+    return t.fused_tail && !waves && !(t.variant & (8 | 32));
 }
 
 }  // namespace rcp

@@ -973,13 +973,7 @@ static int iterate_flags(const rcp_ctx *c)
            ((c->tuning.variant & 63) << 8);
 }
 
-// The tail runs inside the gradient kernel only when asked for and when no
-// packing has frozen spheres or walls and the packings are 3-D (the other
-// kernels have no fused tail).
-static bool tail_fused(const rcp_ctx *c)
-{
-    return c->tuning.fused_tail && !c->any_mixed && !c->any_walls && c->dim == 3;
-}
+static bool tail_fused(const rcp_ctx *c) { return fuses_tail(c->tuning, waves_only(c)); }
 
 // Whether the tail of an iteration runs at the start of the next one's
 // kernel: the wave kernel, no more blocks in all than that form takes (see

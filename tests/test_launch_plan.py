@@ -1,5 +1,6 @@
 """The host arithmetic of the launches (csrc/launch_plan.hpp), compiled on its
-own with the host compiler: the cut of the rows into work items."""
+own with the host compiler: the cut of the rows into work items, and what runs
+an iteration's tail."""
 import ctypes as C
 import os
 import subprocess
@@ -20,6 +21,7 @@ int units_row(const rcp_tuning *t) { return row_units(*t); }
 int units_item(const rcp_tuning *t, int waves, int64_t n, int64_t e) { return item_units(*t, waves, n, e); }
 int rows_max(const rcp_tuning *t, int waves) { return item_rows_max(*t, waves); }
 int64_t slots(const rcp_tuning *t, int waves, int64_t n, int64_t e) { return item_slots(*t, waves, n, e); }
+int fused(const rcp_tuning *t, int waves) { return fuses_tail(*t, waves); }
 }
 """
 
@@ -77,3 +79,15 @@ def test_wide_items_have_more_rows_than_lanes(plan):
     assert rows.max() == 128 and plan.rows_max(C.byref(t), 0) == 128
     rows, _ = _items(plan, t, 1, np.zeros(20000, int))
     assert rows.max() == 64 and plan.rows_max(C.byref(t), 1) == 64
+
+
+def test_every_iteration_has_a_tail(plan):
+    # a gradient kernel without the fused form must be followed by the tail's
+    # own launch: bits 3 and 5 select such kernels, and so do walls, frozen
+    # spheres and two dimensions
+    for variant in range(256):
+        t = _tuning(variant=variant, fused_tail=1)
+        assert plan.fused(C.byref(t), 0) == (0 if variant & 8 or variant & 32 else 1), variant
+        assert plan.fused(C.byref(t), 1) == 0
+        t.fused_tail = 0
+        assert plan.fused(C.byref(t), 0) == 0
