@@ -1376,7 +1376,16 @@ static void launch_variant(const SegPtrs *P, SegState *S, const WorkItem *W, dou
     // partner indices staged in LDS; bit 3: persistent blocks (bits 1, 2 and
     // the fused tail do not apply to it); bit 4: seven waves per SIMD asked
     // of the compiler; bit 5: items of up to 512 rows (bits 1-4 and the
-    // fused tail do not apply)
+    // fused tail do not apply; no other kernel takes that many)
+    if (variant & 32) {
+        if (variant & 1)
+            hipLaunchKernelGGL(k_iterate512<4>, dim3(nitems), dim3(kBlock), 0, st, P, S, W,
+                               partials, f);
+        else
+            hipLaunchKernelGGL(k_iterate512<2>, dim3(nitems), dim3(kBlock), 0, st, P, S, W,
+                               partials, f);
+        return;
+    }
     if (variant & 8) {
         const int grid = std::min(nitems, kPersistBlocks);
         if (variant & 1)
@@ -1385,15 +1394,6 @@ static void launch_variant(const SegPtrs *P, SegState *S, const WorkItem *W, dou
         else
             hipLaunchKernelGGL(k_iterate_persist<2>, dim3(grid), dim3(kBlock), 0, st, P, S, W,
                                partials, nitems, f);
-        return;
-    }
-    if (variant & 32) {
-        if (variant & 1)
-            hipLaunchKernelGGL(k_iterate512<4>, dim3(nitems), dim3(kBlock), 0, st, P, S, W,
-                               partials, f);
-        else
-            hipLaunchKernelGGL(k_iterate512<2>, dim3(nitems), dim3(kBlock), 0, st, P, S, W,
-                               partials, f);
         return;
     }
     if (variant & 16) launch_basic<kF, 7>(P, S, W, partials, nitems, f, variant, st);
