@@ -202,6 +202,10 @@ struct rcp_ctx {
     int64_t qtmp_cap = 0;
     WorkItem *eitems = nullptr;      // work items of an evaluation (see eval_current)
     int64_t eitems_cap = 0;
+    // the last evaluation on a caller's stream (rcp_energy_dev and its
+    // adjoint), which may still be reading part, out, qtmp, eitems and the list
+    hipEvent_t ev_dev = nullptr;
+    bool dev_busy = false;
     double *h_out = nullptr;         // pinned small results
     // iteration graphs by length (see graph_len); graph_valid = false
     // drops them all before the next launch
@@ -275,8 +279,29 @@ static void flush_rebuild_times(rcp_ctx *c)
     c->rb_pending.clear();
 }
 
+// Work queued on st from here on comes after the last evaluation on a caller's
+// stream.  Once the context's own stream waits for it nothing else need: calls
+// on other streams wait for that one.
+static int after_dev(rcp_ctx *c, hipStream_t st)
+{
+    if (!c->dev_busy) return RCP_OK;
+    HIPCHK(hipStreamWaitEvent(st, c->ev_dev, 0));
+    if (st == c->stream) c->dev_busy = false;
+    return RCP_OK;
+}
+
+// An evaluation has been queued on st.
+static int mark_dev(rcp_ctx *c, hipStream_t st)
+{
+    if (st == c->stream) return RCP_OK;
+    HIPCHK(hipEventRecord(c->ev_dev, st));
+    c->dev_busy = true;
+    return RCP_OK;
+}
+
 static int pull_state(rcp_ctx *c)
 {
+    CHK(after_dev(c, c->stream));
     HIPCHK(hipMemcpyAsync(c->h_state, c->d_state, sizeof(SegState) * c->segs.size(),
                           hipMemcpyDeviceToHost, c->stream));
     HIPCHK(hipStreamSynchronize(c->stream));
@@ -1616,6 +1641,7 @@ static void destroy_ctx(rcp_ctx *c)
 {
     if (!c) return;
     if (c->stream) (void)hipStreamSynchronize(c->stream);
+    if (c->dev_busy) (void)hipEventSynchronize(c->ev_dev);
     for (auto &g : c->graphs) (void)hipGraphExecDestroy(g.second);
     for (auto &s : c->segs) {
         for (int b = 0; b < 2; ++b) {
@@ -1642,6 +1668,7 @@ static void destroy_ctx(rcp_ctx *c)
     }
     c->lanes.clear();
     if (c->fork_ev) (void)hipEventDestroy(c->fork_ev);
+    if (c->ev_dev) (void)hipEventDestroy(c->ev_dev);
     dfree(c->totals);
     dfree(c->skA);
     dfree(c->skB);
@@ -1797,6 +1824,12 @@ int rcp_census_init(int dim, int n_prob, const int64_t *n, const double *const *
             rc = fail(RCP_EDEVICE, "hipEventCreate: %s", hipGetErrorString(e));
             break;
         }
+        // (it only keeps later writes behind reads: no fence is needed)
+        if ((e = hipEventCreateWithFlags(&c->ev_dev, hipEventDisableTiming |
+                                                         hipEventDisableSystemFence)) != hipSuccess) {
+            rc = fail(RCP_EDEVICE, "hipEventCreate: %s", hipGetErrorString(e));
+            break;
+        }
         if ((rc = scratch_address(&c->scratch)) != RCP_OK) break;
         if ((rc = dalloc(&c->d_ptrs, n_prob)) != RCP_OK) break;
         if ((rc = dalloc(&c->d_state, 2 * (size_t)n_prob)) != RCP_OK) break;
@@ -1884,6 +1917,7 @@ int rcp_set_tuning(rcp_ctx *c, const rcp_tuning *t)
         (int64_t)t->item_work > max_rows * t->row_cost)
         return fail(RCP_EINVAL, "bad tuning values");
     if (t->time_kernels < 0 || t->time_kernels > 2) return fail(RCP_EINVAL, "bad tuning values");
+    CHK(after_dev(c, c->stream));
     const bool relayout = t->row_cost != c->tuning.row_cost || t->item_work != c->tuning.item_work;
     c->tuning = *t;
     c->graph_valid = false;
@@ -1928,6 +1962,7 @@ static int set_state3(rcp_ctx *c, int k, const double *x, double kappa, int is_d
     CHK(check_k(c, k));
     Seg &s = c->segs[k];
     if (!x || !(kappa > 0) || !std::isfinite(kappa)) return fail(RCP_EINVAL, "bad state");
+    CHK(after_dev(c, c->stream));
     CHK(dgrow(&c->xtmp, &c->xtmp_cap, 3 * s.n));
     HIPCHK(hipMemcpyAsync(c->xtmp, x, sizeof(double) * 3 * s.n,
                           is_device ? hipMemcpyDeviceToDevice : hipMemcpyHostToDevice, c->stream));
@@ -2396,6 +2431,7 @@ static int start_schedule(rcp_ctx *c, const rcp_schedule *sched, int per_packing
                           int64_t max_iters, bool reset_adam = true, bool hold = false)
 {
     const int ns = (int)c->segs.size();
+    CHK(after_dev(c, c->stream));
     // (the last start's table may still be on its way)
     if (ns > 1) HIPCHK(hipStreamSynchronize(c->stream));
     std::vector<SchedDev> qs(ns);
@@ -2502,6 +2538,7 @@ int rcp_run_continue(rcp_ctx *c, int64_t n_iters, int32_t *active)
     if (!c) return fail(RCP_EINVAL, "null context");
     if (n_iters < 0) return fail(RCP_EINVAL, "n_iters < 0");
     const int ns = (int)c->segs.size();
+    CHK(after_dev(c, c->stream));
     hipLaunchKernelGGL(k_extend, dim3((ns + 63) / 64), dim3(64), 0, c->stream, c->d_state, ns,
                        n_iters);
     // run_loop returns right after reading every record back (nothing is
@@ -2588,6 +2625,7 @@ static int ensure_valid_at(rcp_ctx *c, const double *x_dev, double kappa, hipStr
                            const P4 **q)
 {
     if (st != c->stream) HIPCHK(hipStreamSynchronize(c->stream));
+    CHK(after_dev(c, st));
     Seg &s = c->segs[0];
     SegState &h = c->h_state[0];
     *q = nullptr;
@@ -2629,7 +2667,7 @@ int rcp_energy_dev(rcp_ctx *c, const double *x_dev, double kappa, double mu, dou
     CHK(ensure_valid_at(c, x_dev, kappa, st, &q));
     CHK(eval_current(c, 0, q, kappa, mu, nullptr, E_dev, nullptr, st));
     HIPCHK(hipGetLastError());
-    return RCP_OK;
+    return mark_dev(c, st);
 }
 
 int rcp_adjoint_dev(rcp_ctx *c, const double *x_dev, double kappa, double mu, double *gx_dev,
@@ -2642,7 +2680,7 @@ int rcp_adjoint_dev(rcp_ctx *c, const double *x_dev, double kappa, double mu, do
     CHK(ensure_valid_at(c, x_dev, kappa, st, &q));
     CHK(eval_current(c, 0, q, kappa, mu, gx_dev, nullptr, gk_dev, st));
     HIPCHK(hipGetLastError());
-    return RCP_OK;
+    return mark_dev(c, st);
 }
 
 int rcp_energy_dev_static(rcp_ctx *c, const double *x_dev, double kappa, double mu,
@@ -2693,6 +2731,7 @@ int rcp_time_iterations(rcp_ctx *c, int64_t n_iters, double *iterate_us, double 
     if (!c || n_iters < 1) return fail(RCP_EINVAL, "bad arguments");
     const int ns = (int)c->segs.size();
     CHK(check_items(c, iterate_flags(c)));
+    CHK(after_dev(c, c->stream));
     hipLaunchKernelGGL(k_extend, dim3((ns + 63) / 64), dim3(64), 0, c->stream, c->d_state, ns,
                        n_iters);
     constexpr int kBatch = 32;
