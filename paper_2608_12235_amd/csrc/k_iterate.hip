@@ -1490,16 +1490,21 @@ __global__ __launch_bounds__(kBlock) void k_items_fill(WorkItem *__restrict__ W,
 
 __global__ __launch_bounds__(kBlock) void k_items(const int32_t *__restrict__ rp, int64_t n,
                                                  int64_t rc, int64_t wk,
-                                                 WorkItem *__restrict__ W, int64_t nslots)
+                                                 WorkItem *__restrict__ W, int64_t nslots,
+                                                 int64_t first)
 {
     const int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x;
     if (i >= n) return;
-    const int64_t hi = rc * i + (int64_t)rp[i];
-    const int64_t bl = i == 0 ? 0 : (rc * (i - 1) + (int64_t)rp[i - 1]) / wk + 1;
-    const int64_t bh = min(hi / wk, nslots - 1);
-    for (int64_t b = bl; b <= bh; ++b) {
-        W[b].begin = i;
-        W[b].e0 = rp[i];
+    const int64_t hi = (rc * i + (int64_t)rp[i]) / wk - first;
+    const int64_t lo = (i == 0 ? 0 : (rc * (i - 1) + (int64_t)rp[i - 1]) / wk + 1) - first;
+    // (items [0, nslots) of those from `first` on; the item behind them ends
+    // the last)
+    const int64_t bh = min(hi, nslots);
+    for (int64_t b = max(lo, (int64_t)0); b <= bh; ++b) {
+        if (b < nslots) {
+            W[b].begin = i;
+            W[b].e0 = rp[i];
+        }
         if (b > 0) {
             W[b - 1].end = i;
             W[b - 1].e1 = rp[i];
@@ -1508,7 +1513,7 @@ __global__ __launch_bounds__(kBlock) void k_items(const int32_t *__restrict__ rp
 }
 
 void launch_items(const int32_t *rp, int64_t n, int seg, int row_cost, int item_work,
-                  WorkItem *W, int64_t nslots, hipStream_t st)
+                  WorkItem *W, int64_t nslots, hipStream_t st, int64_t first)
 {
     if (nslots <= 0) return;
     const unsigned gf = (unsigned)((nslots + kBlock - 1) / kBlock);
@@ -1517,7 +1522,7 @@ void launch_items(const int32_t *rp, int64_t n, int seg, int row_cost, int item_
     if (!rp || n <= 0) return;
     const unsigned gi = (unsigned)((n + kBlock - 1) / kBlock);
     hipLaunchKernelGGL(k_items, dim3(gi), dim3(kBlock), 0, st, rp, n, (int64_t)row_cost,
-                       (int64_t)item_work, W, nslots);
+                       (int64_t)item_work, W, nslots, first);
 }
 
 // Segmented forms for a batch of list builds: block b of a grid belongs
@@ -1659,87 +1664,9 @@ void launch_set_flags(SegState *S, int seg, int32_t clear, int32_t set, hipStrea
 }
 
 // ------------------------------------------------------- evaluation
-// Thread per row over the whole list, positions from the user-order array xu
-// gathered through orig: the form that needs no memory but the partials (for
-// callers that cannot allocate).  Partials per block: E_ov, S, max delta,
-// overlapping pairs (and wall contacts, with walls).
-__global__ __launch_bounds__(kBlock) void k_eval(const SegPtrs *__restrict__ P,
-                                                const SegState *__restrict__ S, int seg,
-                                                int64_t n, const double *__restrict__ xu,
-                                                double kappa, double *__restrict__ part)
-{
-    const SegState *s = S + seg;
-    const IterPtrs p = select_ptrs(P, seg, s->cur);
-    const int32_t *orig = P[seg].orig;
-    const double L = s->L, iL = 1.0 / L;
-    const int32_t bounded = s->walls | s->round;
-    const double iLa[3] = {(bounded & 1) ? 0.0 : iL, (bounded & 2) ? 0.0 : iL,
-                           (bounded & 4) ? 0.0 : iL};
-    const int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x;
-    double be = 0, bs = 0, bm = 0, bn = 0;
-    if (i < n) {
-        // position from the user-order array, D0 from the list
-        auto pos = [&](int64_t k) -> P4 {
-            P4 q = p.q[k];
-            const int64_t u = orig[k];
-            q.x = xu[3 * u];
-            q.y = xu[3 * u + 1];
-            q.z = xu[3 * u + 2];
-            return q;
-        };
-        const P4 qi = pos(i);
-        Acc a = {0, 0, 0, 0, 0, 0, 0};
-        if (s->mixed)
-            for (int32_t q = p.rp[i]; q < p.rp[i + 1]; ++q)
-                pair_term<true, true>(a, qi, pos(p.col[q]), kappa, L, iLa);
-        else
-            for (int32_t q = p.rp[i]; q < p.rp[i + 1]; ++q)
-                pair_term(a, qi, pos(p.col[q]), kappa, L, iLa);
-        if (bounded) {
-            WallAcc w = {{0.0, 0.0, 0.0}, 0.0, 0.0, 0.0, 0.0};
-            const double px[3] = {qi.x, qi.y, qi.z};
-            wall_terms(px, kappa * qi.d, L, s->walls, s->round, w);
-            a.e += w.e;
-            a.s += w.s;
-            a.m = fmax(a.m, w.m);
-            a.c += w.c;
-        }
-        be = a.e;
-        bs = a.s;
-        bm = a.m;
-        bn = a.c;
-    }
-    be = wave_sum(be);
-    bs = wave_sum(bs);
-    bm = wave_max(bm);
-    bn = wave_sum(bn);
-    __shared__ double red[kWavesPerBlock][4];
-    const int lane = threadIdx.x & (kWave - 1), wv = threadIdx.x / kWave;
-    if (lane == 0) {
-        red[wv][0] = be;
-        red[wv][1] = bs;
-        red[wv][2] = bm;
-        red[wv][3] = bn;
-    }
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        double e = 0, sd = 0, m = 0, c = 0;
-        for (int k = 0; k < kWavesPerBlock; ++k) {
-            e += red[k][0];
-            sd += red[k][1];
-            m = fmax(m, red[k][2]);
-            c += red[k][3];
-        }
-        double *o = part + 4 * (int64_t)blockIdx.x;
-        o[0] = e;
-        o[1] = sd;
-        o[2] = m;
-        o[3] = c;
-    }
-}
-
-// The same terms by a wave per work item (W, four a block), over the
-// positions Q in list order (nullptr: the current buffer).  On 1e6 spheres
+// By a wave per work item (W, four a block), over the positions Q in list
+// order (nullptr: the current buffer); partials per block: E_ov, S, max delta,
+// overlapping pairs (and wall contacts, with walls).  On 1e6 spheres
 // with 2.3 partners a row, gradient out, 35 us against 453 for a thread
 // per row gathering every partner through orig; both are bound by scattered
 // accesses, here only those of the gradient's user order.
@@ -1852,19 +1779,17 @@ void launch_gather_disp(const SegPtrs *P, const SegState *S, int seg, int64_t n,
                        part);
 }
 
-void launch_eval(const SegPtrs *P, const SegState *S, int seg, int64_t n, const double *xu,
-                 double kappa, double *part, int nblocks, hipStream_t st)
-{
-    hipLaunchKernelGGL(k_eval, dim3(nblocks), dim3(kBlock), 0, st, P, S, seg, n, xu, kappa, part);
-}
-
-constexpr int kFinishBlock = 1024;
+constexpr int kFinishBlock = kFinishThreads;
 
 // One block (one wave took 18 us over the 3907 partials of 1e6 spheres,
 // 4.4 us now): each thread's partials eight in flight, then waves and their
-// sums by DPP, in a fixed order.
+// sums by DPP, in a fixed order.  Partials that come in portions (multiples of
+// kFinishBlock) leave the threads' sums in `next` and take them up from `prev`:
+// the same additions in the same order.
 __global__ __launch_bounds__(kFinishBlock) void k_eval_finish(const double *__restrict__ part,
-                                                             int nblocks, double kappa, double mu,
+                                                             int nblocks,
+                                                             const Part4 *prev, Part4 *next,
+                                                             double kappa, double mu,
                                                              const SegState *__restrict__ S,
                                                              int seg, double *__restrict__ out,
                                                              double *__restrict__ E,
@@ -1873,6 +1798,7 @@ __global__ __launch_bounds__(kFinishBlock) void k_eval_finish(const double *__re
     constexpr int kT = kFinishBlock, kW = kT / kWave;
     const Part4 *P = reinterpret_cast<const Part4 *>(part);
     Part4 t = {0, 0, 0, 0};
+    if (prev) t = prev[threadIdx.x];
     for (int b = threadIdx.x; b < nblocks; b += 8 * kT) {
         Part4 p[8];
 #pragma unroll
@@ -1884,6 +1810,10 @@ __global__ __launch_bounds__(kFinishBlock) void k_eval_finish(const double *__re
             t.m = fmax(t.m, p[k].m);
             t.d += p[k].d;
         }
+    }
+    if (next) {
+        next[threadIdx.x] = t;
+        return;
     }
     __shared__ Part4 red[kW];
     const int lane = threadIdx.x & (kWave - 1), wv = threadIdx.x / kWave;
@@ -1912,44 +1842,11 @@ __global__ __launch_bounds__(kFinishBlock) void k_eval_finish(const double *__re
 
 void launch_eval_finish(const double *part, int nblocks, double kappa, double mu,
                         const SegState *S, int seg, double *out, double *E, double *gk,
-                        hipStream_t st)
+                        hipStream_t st, const double *prev, double *next)
 {
-    hipLaunchKernelGGL(k_eval_finish, dim3(1), dim3(kFinishBlock), 0, st, part, nblocks, kappa, mu,
-                       S, seg, out, E, gk);
-}
-
-__global__ __launch_bounds__(kBlock) void k_disp(const SegPtrs *__restrict__ P,
-                                                const SegState *__restrict__ S, int seg,
-                                                int64_t n, const double *__restrict__ xu,
-                                                double *__restrict__ part)
-{
-    const SegPtrs p = P[seg];
-    const double L = S[seg].L, hL = S[seg].hL;
-    const int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x;
-    double d2 = 0;
-    if (i < n) {
-        const int64_t u = p.orig[i];
-#pragma unroll
-        for (int a = 0; a < 3; ++a) {
-            const double dd = min_image(xu[3 * u + a] - (double)p.xref[a][i], L, hL);
-            d2 += dd * dd;
-        }
-    }
-    d2 = wave_max(d2);
-    __shared__ double red[kWavesPerBlock];
-    if ((threadIdx.x & (kWave - 1)) == 0) red[threadIdx.x / kWave] = d2;
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        double m = 0;
-        for (int k = 0; k < kWavesPerBlock; ++k) m = fmax(m, red[k]);
-        part[blockIdx.x] = m;
-    }
-}
-
-void launch_disp(const SegPtrs *P, const SegState *S, int seg, int64_t n, const double *xu,
-                 double *part, int nblocks, hipStream_t st)
-{
-    hipLaunchKernelGGL(k_disp, dim3(nblocks), dim3(kBlock), 0, st, P, S, seg, n, xu, part);
+    hipLaunchKernelGGL(k_eval_finish, dim3(1), dim3(kFinishBlock), 0, st, part, nblocks,
+                       reinterpret_cast<const Part4 *>(prev), reinterpret_cast<Part4 *>(next),
+                       kappa, mu, S, seg, out, E, gk);
 }
 
 __global__ __launch_bounds__(kBlock) void k_set_frozen(const SegPtrs *__restrict__ P, int seg,

@@ -230,9 +230,9 @@ void launch_place_round(const PlaceArgs &a, hipStream_t st);
 // bit 3: one packing (number 0).
 // Work items of packing seg (nslots slots at W, four a block): rows are cut
 // so that an item covers item_work units of row_cost * row + row pointer; rp
-// == nullptr leaves every slot empty.
+// == nullptr leaves every slot empty.  W[0] is item `first` of the cut.
 void launch_items(const int32_t *rp, int64_t n, int seg, int row_cost, int item_work,
-                  WorkItem *W, int64_t nslots, hipStream_t st);
+                  WorkItem *W, int64_t nslots, hipStream_t st, int64_t first = 0);
 void launch_iterate(const SegPtrs *P, SegState *S, const WorkItem *W, double *partials,
                     int nitems, int flags, hipStream_t s);
 // Whether launch_iterate runs the wave kernel for these flags, and the most
@@ -261,33 +261,29 @@ void launch_start(const SegPtrs *P, SegState *S, int nseg, int64_t nmax, const S
                   hipStream_t s);
 void launch_set_flags(SegState *S, int seg, int32_t clear, int32_t set, hipStream_t s);
 
-// Energy terms of one segment at positions given in user order (xu, n x 3
-// row-major, device): per-block partials E_ov, S_drd, max delta, n_overlap.
-void launch_eval(const SegPtrs *P, const SegState *S, int seg, int64_t n, const double *xu,
-                 double kappa, double *part, int nblocks, hipStream_t s);
-// Final reduction of launch_eval partials into out[0..5]: E_ov, E_growth,
-// gk_ov, gk_growth, max delta, n_overlap (mu and sum D0 given).
-// (E, gk: where not null, E[0..1] = total energy and max delta, gk[0] = total
-// dE/dkappa).
-void launch_eval_finish(const double *part, int nblocks, double kappa, double mu,
-                        const SegState *S, int seg, double *out, double *E, double *gk,
-                        hipStream_t s);
 struct EvalOut {
-    double *part;     // the partials of launch_eval
+    double *part;     // per-block partials: E_ov, S_drd, max delta, n_overlap
     double *gu;       // dE/dx in user order (n x 3) or nullptr
 };
-// The terms of launch_eval by work items (nblocks blocks of four at W), over
-// the positions Q in list order (nullptr: the current buffer); flags bits 4
-// and 5 as in launch_iterate.
+// Energy terms and gradient of one segment by work items (nblocks blocks of
+// four at W), over the positions Q in list order (nullptr: the current
+// buffer); flags bits 4 and 5 as in launch_iterate.
 void launch_eval_wave(const SegPtrs *P, const SegState *S, int seg, const WorkItem *W, const P4 *Q,
                       double kappa, int flags, const EvalOut &o, int nblocks, hipStream_t s);
+// Final reduction of its partials into out[0..5]: E_ov, E_growth, gk_ov,
+// gk_growth, max delta, n_overlap (mu and sum D0 given).
+// (E, gk: where not null, E[0..1] = total energy and max delta, gk[0] = total
+// dE/dkappa).  prev, next: where not null, 4 kFinishThreads doubles in which
+// one portion of the partials (a multiple of kFinishThreads) leaves its sums
+// for the next, which the last makes the results of.
+constexpr int kFinishThreads = 1024;
+void launch_eval_finish(const double *part, int nblocks, double kappa, double mu,
+                        const SegState *S, int seg, double *out, double *E, double *gk,
+                        hipStream_t s, const double *prev = nullptr, double *next = nullptr);
 // Positions xu (user order, n x 3) into Q (list order, the current records'
 // D0), and per block the largest displacement^2 against the list's xref.
 void launch_gather_disp(const SegPtrs *P, const SegState *S, int seg, int64_t n, const double *xu,
                         P4 *Q, double *part, int nblocks, hipStream_t s);
-// Max displacement^2 of xu (user order, n x 3) against the list's xref.
-void launch_disp(const SegPtrs *P, const SegState *S, int seg, int64_t n, const double *xu,
-                 double *part, int nblocks, hipStream_t s);
 // Adam moments of segment seg to (dir 0) or from (dir 1) user-order arrays
 // mu, vu (n x 3 row-major, device).
 void launch_moments_io(const SegPtrs *P, int seg, int64_t n, double *mu, double *vu, int dir,

@@ -324,7 +324,15 @@ static int put_field(rcp_ctx *c, int k, size_t offset, const T &v)
 // Block partials and small results of rcp_energy_dev_static: a device array
 // of this module, one copy per GPU, held until the process ends.  Its name
 // is a host-side stand-in; the device address is looked up once per GPU.
+// The evaluation's partials come in portions of kScratchPart blocks, the sums
+// so far behind them; where the work items too have to be cut there, of
+// kScratchCut, the items behind the partials.
 constexpr int64_t kScratchBlocks = (int64_t)1 << 16;        // n <= 2^24 spheres
+constexpr int64_t kScratchPart = kScratchBlocks - kFinishThreads;
+constexpr int64_t kScratchCut = 12 * kFinishThreads;
+static_assert(kScratchPart % kFinishThreads == 0 && kScratchCut % kFinishThreads == 0, "portions");
+static_assert(kScratchCut * (32 + kWavesPerBlock * (int64_t)sizeof(WorkItem)) <= 32 * kScratchPart,
+              "partials and items of a portion");
 constexpr int64_t kScratchWords = 4 * kScratchBlocks + 64;  // 2 MiB + results
 static __device__ __align__(256) double scratch[kScratchWords];
 
@@ -2360,6 +2368,13 @@ int rcp_get_pairs(rcp_ctx *c, int k, int32_t *pi, int32_t *pj, int64_t cap, int6
     return RCP_OK;
 }
 
+// Whether an evaluation of the packing cuts work items of its own: when it is
+// finished and has given up those in the work table, and when the table is
+// cut for a kernel that takes more rows an item than a wave has lanes.
+static bool own_items(const rcp_ctx *c, const Seg &s) { return s.parked || c->item_rows > kWave; }
+
+static int eval_flags(const Seg &s) { return (s.mixed ? 16 : 0) | ((s.walls | s.round) ? 32 : 0); }
+
 // Energy terms of packing k (its list built) at kappa into c->out, at the
 // positions q in list order or (nullptr) its current ones; the gradient to gu
 // (user order, n x 3) where given; E, gk as in launch_eval_finish.
@@ -2367,12 +2382,9 @@ static int eval_current(rcp_ctx *c, int k, const P4 *q, double kappa, double mu,
                         double *E, double *gk, hipStream_t st)
 {
     Seg &s = c->segs[k];
-    // the packing's items in the work table; its rows are cut here when it is
-    // finished and has given them up, or when the table is cut for a kernel
-    // that takes more rows an item than a wave has lanes
     const WorkItem *w = c->d_work + s.first_item * kWavesPerBlock;
     int nb = s.blocks;
-    if (s.parked || c->item_rows > kWave) {
+    if (own_items(c, s)) {
         const int64_t slots = item_slots(c->tuning, true, s.n, s.nnz);
         CHK(dgrow(&c->eitems, &c->eitems_cap, slots));
         launch_items(s.rp, s.n, k, row_units(c), item_units(c->tuning, true, s.n, s.nnz), c->eitems,
@@ -2384,8 +2396,7 @@ static int eval_current(rcp_ctx *c, int k, const P4 *q, double kappa, double mu,
     EvalOut o;
     o.part = c->part;
     o.gu = gu_dev;
-    const int flags = (s.mixed ? 16 : 0) | ((s.walls | s.round) ? 32 : 0);
-    launch_eval_wave(c->d_ptrs, c->d_state, k, w, q, kappa, flags, o, nb, st);
+    launch_eval_wave(c->d_ptrs, c->d_state, k, w, q, kappa, eval_flags(s), o, nb, st);
     launch_eval_finish(c->part, nb, kappa, mu, c->d_state, k, c->out, E, gk, st);
     return RCP_OK;
 }
@@ -2700,6 +2711,7 @@ int rcp_energy_dev_static(rcp_ctx *c, const double *x_dev, double kappa, double 
     if (!c->scratch) return fail(RCP_ESTATE, "no scratch address for this context");
     hipStream_t st = (hipStream_t)stream;   // NULL: the null stream
     if (st != c->stream) HIPCHK(hipStreamSynchronize(c->stream));
+    CHK(after_dev(c, st));
     // the context's record, read without touching any growable host list
     HIPCHK(hipMemcpyAsync(c->h_state, c->d_state, sizeof(SegState) * c->segs.size(),
                           hipMemcpyDeviceToHost, c->stream));
@@ -2708,8 +2720,11 @@ int rcp_energy_dev_static(rcp_ctx *c, const double *x_dev, double kappa, double 
     if (!s.built || (h.flags & (F_REBUILD | F_STALE)))
         return fail(RCP_ESTATE, "rcp_energy_dev_static: packing 0 has no valid neighbour list");
     double *part = c->scratch, *res = c->scratch + 4 * kScratchBlocks;
+    // the positions in list order go to the packing's other buffer, which its
+    // next step overwrites (the records' D0 there are the same)
+    P4 *q = s.Q[h.cur ^ 1];
     // the validity test of the iteration tail at (x_dev, kappa)
-    launch_disp(c->d_ptrs, c->d_state, 0, s.n, x_dev, part, (int)nb, st);
+    launch_gather_disp(c->d_ptrs, c->d_state, 0, s.n, x_dev, q, part, (int)nb, st);
     launch_max_finish(part, (int)nb, res, st);
     HIPCHK(hipMemcpyAsync(c->h_out, res, sizeof(double), hipMemcpyDeviceToHost, st));
     HIPCHK(hipStreamSynchronize(st));
@@ -2719,10 +2734,26 @@ int rcp_energy_dev_static(rcp_ctx *c, const double *x_dev, double kappa, double 
         return fail(RCP_ESTATE,
                     "rcp_energy_dev_static: the neighbour list is not valid at these positions "
                     "and kappa (rebuild it with rcp_neighbor_build or rcp_energy_dev)");
-    launch_eval(c->d_ptrs, c->d_state, 0, s.n, x_dev, kappa, part, (int)nb, st);
-    launch_eval_finish(part, (int)nb, kappa, mu, c->d_state, 0, res + 8, E_dev, nullptr, st);
+    // by the items that eval_current takes, in the same order
+    const bool cut = own_items(c, s);
+    const int64_t blocks = cut ? item_slots(c->tuning, true, s.n, s.nnz) / kWavesPerBlock : s.blocks;
+    const int64_t step = cut ? kScratchCut : kScratchPart;
+    WorkItem *items = reinterpret_cast<WorkItem *>(part + 4 * kScratchCut);
+    double *sums = part + 4 * kScratchPart;
+    const EvalOut o = {part, nullptr};
+    for (int64_t b = 0; b < blocks; b += step) {
+        const int64_t m = std::min(step, blocks - b), first = b * kWavesPerBlock;
+        if (cut)
+            launch_items(s.rp, s.n, 0, row_units(c), item_units(c->tuning, true, s.n, s.nnz), items,
+                         m * kWavesPerBlock, st, first);
+        launch_eval_wave(c->d_ptrs, c->d_state, 0,
+                         cut ? items : c->d_work + s.first_item * kWavesPerBlock + first, q, kappa,
+                         eval_flags(s), o, (int)m, st);
+        launch_eval_finish(part, (int)m, kappa, mu, c->d_state, 0, res + 8, E_dev, nullptr, st,
+                           b > 0 ? sums : nullptr, b + m < blocks ? sums : nullptr);
+    }
     HIPCHK(hipGetLastError());
-    return RCP_OK;
+    return mark_dev(c, st);
 }
 
 int rcp_time_iterations(rcp_ctx *c, int64_t n_iters, double *iterate_us, double *tail_us,
