@@ -395,8 +395,11 @@ static int build_work(rcp_ctx *c)
     int64_t total = 0;
     for (size_t k = 0; k < c->segs.size(); ++k) {
         Seg &s = c->segs[k];
+        // room for slot_entries, and for the list there is: under the cut it
+        // was laid out for, a table may hold a few entries more than that
+        const int64_t entries = s.built ? std::max(s.slot_entries, s.nnz) : s.slot_entries;
         // a finished packing gets no slots (its blocks would only exit)
-        const int64_t nb = s.parked ? 0 : slots_for(c, s.n, s.slot_entries) / kWavesPerBlock;
+        const int64_t nb = s.parked ? 0 : slots_for(c, s.n, entries) / kWavesPerBlock;
         if (nb > (int64_t)INT32_MAX / 4 || total + nb > (int64_t)INT32_MAX / 4)
             return fail(RCP_ENOMEM, "work table too large");
         s.blocks = (int)nb;

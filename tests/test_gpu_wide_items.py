@@ -91,3 +91,20 @@ def test_steps_of_wide_items(rcp, orc, variant):
     d = np.minimum(d, L - d)
     assert d.max() <= 1e-9 * ex * steps + 4e-16 * L, d.max()
     assert kg == pytest.approx(st.kappa[0], rel=1e-12)
+
+
+def test_a_new_cut_of_a_built_list_has_items_for_every_row(rcp, orc):
+    # 2000 spheres: the table is laid out for 16000 entries, and with the
+    # default cut it holds this list of a few more; a cut of one unit an item
+    # needs an item for each of them
+    rng = np.random.default_rng(7)
+    d0 = 0.7 + 0.6 * rng.random(2000)
+    L = float((np.pi / 6 * np.sum(d0 ** 3) / 0.4) ** (1 / 3))
+    x = rng.random((2000, 3)) * L
+    p = rcp.Packing(d0, L, 1.0, 0, init="none", params=rcp.make_params(skin_s=0.28, skin_g=0.02))
+    p.set_state(x, 1.0)
+    assert 16000 + 500 < 2 * p.neighbor_build() < 16000 + 1300
+    p.set_tuning(rcp.make_tuning(row_cost=1, item_work=1))
+    _check(orc, x, d0, L, 1.0, 0.3, p.energy_grad(mu=0.3))
+    assert p.stats()["rebuilds"] == 1
+    p.close()
