@@ -1320,16 +1320,16 @@ static void launch_wave(const SegPtrs *P, const SegState *S, SegState *So, const
 #define RCP_WAVE(mixed, walls, dim)                                                            \
     hipLaunchKernelGGL((k_iterate_wave<mixed, walls, dim, kPre>), g, t, 0, st, P, S, So, W, pin, \
                        partials, f)
-    if (flags & 64) {
-        if (flags & 32) RCP_WAVE(false, true, 2);
-        else if (flags & 16) RCP_WAVE(true, false, 2);
-        else RCP_WAVE(false, false, 2);
-    } else if (flags & 32)
-        RCP_WAVE(false, true, 3);
-    else if (flags & 16)
-        RCP_WAVE(true, false, 3);
-    else
-        RCP_WAVE(false, false, 3);
+    switch ((flags >> 4) & 7) {   // mixed, walls, two dimensions
+    case 0: RCP_WAVE(false, false, 3); break;
+    case 1: RCP_WAVE(true, false, 3); break;
+    case 2: RCP_WAVE(false, true, 3); break;
+    case 3: RCP_WAVE(true, true, 3); break;
+    case 4: RCP_WAVE(false, false, 2); break;
+    case 5: RCP_WAVE(true, false, 2); break;
+    case 6: RCP_WAVE(false, true, 2); break;
+    default: RCP_WAVE(true, true, 2); break;
+    }
 #undef RCP_WAVE
 }
 
@@ -1407,7 +1407,7 @@ void launch_iterate(const SegPtrs *P, SegState *S, const WorkItem *W, double *pa
     // records written; bit 3: one packing; bit 4: some packing has frozen
     // spheres (then the wave kernel with the mixed pair terms runs, whatever
     // the variant); bit 5: some packing has walls (then the wave kernel with
-    // the wall terms runs, whatever the variant; never together with bit 4);
+    // the wall terms runs, whatever the variant; no packing has both);
     // bit 6: two dimensions (the wave kernel for two coordinates, whatever
     // the variant); bits 8-13: kernel variant (see launch_variant; the wave
     // kernel when none of them is set and the tail is not fused)
