@@ -1,10 +1,11 @@
 // Host arithmetic of the launches, free of HIP so that it can be compiled and
-// checked on its own: the cut of a packing's rows into work items, and what
-// runs an iteration's tail.
+// checked on its own: the cut of a packing's rows into work items, what runs an
+// iteration's tail, and how many iterations are launched in a row.
 #pragma once
 #include "rcp.h"
 
 #include <algorithm>
+#include <cmath>
 #include <cstdint>
 
 namespace rcp {
@@ -76,6 +77,42 @@ inline int64_t item_slots(const rcp_tuning &t, bool waves, int64_t n, int64_t en
 inline bool fuses_tail(const rcp_tuning &t, bool waves)
 {
     return t.fused_tail && !waves && !(t.variant & (8 | 32));
+}
+
+// Where a running packing stands, for the launches ahead of it.
+struct RunAhead {
+    int64_t iters;               // its iteration count
+    int64_t since_it, interval;  // that at the last list build, or where the
+                                 // schedule began after it; and between the
+                                 // last two in the schedule (0: not known)
+    double max_disp2, disp_lim;  // displacement^2 since the build, and its limit
+    int64_t to_limit, to_end;    // iterations before a limit, and in the schedule
+};
+
+// Iterations to launch before the host next looks at the records, from one
+// packing's side (see launch_span); K: one graph.
+inline int64_t iterations_ahead(const RunAhead &p, int64_t K)
+{
+    const int64_t since = std::max<int64_t>(0, p.iters - p.since_it);
+    int64_t r = K;
+    if (p.interval > 0) {
+        r = p.interval - since;
+    } else if (since > 0 && p.max_disp2 > 0.0 && p.disp_lim > 0.0) {
+        const double d = std::sqrt(p.max_disp2);
+        const double est = d < p.disp_lim ? (double)since * (p.disp_lim / d - 1.0) : 0.0;
+        const int64_t cap = std::max<int64_t>(K, 2 * since);
+        r = est < (double)cap ? (int64_t)est : cap;
+    }
+    return std::min({r, p.to_limit, p.to_end});
+}
+
+// Iterations of a schedule from `done` of rung `rung` on (no more than 2^62).
+inline int64_t schedule_left(const int64_t *budget, int n_rungs, int rung, int64_t done)
+{
+    constexpr int64_t most = (int64_t)1 << 62;
+    int64_t left = 0;
+    for (int r = rung; r < n_rungs; ++r) left = budget[r] < most - left ? left + budget[r] : most;
+    return std::max<int64_t>(0, left - done);
 }
 
 }  // namespace rcp

@@ -131,9 +131,17 @@ struct Seg {
     // hard walls (rcp_set_boundary): flat walls across the axes of `walls`,
     // a round container over the axes of `round`
     int32_t walls = 0, round = 0;
-    // iteration count at the last list build and the length of the last
-    // interval between builds (0: not yet known), for the graph length
-    int64_t it_build = -1, interval = 0;
+    // for the graph length: iteration count where the running schedule (or
+    // what was restored of it) began and at the last list build since (-1:
+    // none yet), and the length of the last interval between builds (0: not
+    // yet known).  Nothing of an earlier run plans a later one.
+    int64_t it_begin = 0, it_build = -1, interval = 0;
+    void begin_count(int64_t it)
+    {
+        it_begin = it;
+        it_build = -1;
+        interval = 0;
+    }
 };
 
 // A stream for the pair searches of a batch of list builds.
@@ -1138,9 +1146,9 @@ static bool seg_done(int32_t f)
 // before its next build: its last interval between builds less the iterations
 // since, or before a second build the displacement allowance left at the
 // displacement rate so far (and no more than the iterations left before any
-// limit); at least kMinGraph.  Beyond K, one graph, it is what every
-// packing has left, and where no interval is known yet at most twice
-// the iterations since the build: a look costs the device 28 us, an
+// limit or in the schedule); at least kMinGraph.  Beyond K, one graph, it is
+// what every packing has left, and where no interval is known yet at most
+// twice the iterations since the build: a look costs the device 28 us, an
 // iteration that idles 2 us.  Results do not depend on it, only how many
 // launches idle.  us per iteration of a settling packing of 512 spheres:
 // 8.0 with a look after every graph of 32, 7.4; of 8784 spheres 11.0, 10.6;
@@ -1153,17 +1161,10 @@ static int64_t launch_span(const rcp_ctx *c, int K)
         const SegState &h = c->h_state[k];
         if (seg_done(h.flags)) continue;
         const Seg &s = c->segs[k];
-        const int64_t since = s.it_build >= 0 ? h.iters - s.it_build : 0;
-        int64_t r = K;
-        if (s.interval > 0 && s.it_build >= 0) {
-            r = s.interval - since;
-        } else if (since > 0 && h.max_disp2 > 0.0 && h.disp_lim > 0.0) {
-            const double d = std::sqrt(h.max_disp2);
-            const double est = d < h.disp_lim ? (double)since * (h.disp_lim / d - 1.0) : 0.0;
-            const int64_t cap = std::max<int64_t>(K, 2 * since);
-            r = est < (double)cap ? (int64_t)est : cap;
-        }
-        if (h.iter_limit > 0) r = std::min<int64_t>(r, h.iter_limit - h.iters);
+        const RunAhead p = {h.iters, std::max(s.it_begin, s.it_build), s.interval, h.max_disp2, h.disp_lim,
+                            h.iter_limit > 0 ? h.iter_limit - h.iters : INT64_MAX,
+                            schedule_left(h.sched.budget, h.sched.n_rungs, h.rung, h.it_rung)};
+        const int64_t r = iterations_ahead(p, K);
         most = std::max(most, r);
         least = std::min(least, r);
     }
@@ -1993,6 +1994,7 @@ static int set_state3(rcp_ctx *c, int k, const double *x, double kappa, int is_d
     CHK(pull_state(c));
     if (*h_bad) return fail(RCP_EINVAL, "position outside [-L, 2L)");
     s.built = false;
+    s.begin_count(0);
     return RCP_OK;
 }
 
@@ -2273,7 +2275,7 @@ int rcp_set_optimizer(rcp_ctx *c, int k, const double *m, const double *v,
         !std::isfinite(o->mu) || !(o->eta_x >= 0) || !std::isfinite(o->eta_x) ||
         !(o->eta_k >= 0) || !std::isfinite(o->eta_k))
         return fail(RCP_EINVAL, "rcp_optimizer: bad value");
-    const Seg &s = c->segs[k];
+    Seg &s = c->segs[k];
     const int64_t n3 = 3 * s.n, nd = (int64_t)c->dim * s.n;
     for (int64_t q = 0; m && q < nd; ++q)
         if (!std::isfinite(m[q])) return fail(RCP_EINVAL, "first moment %lld is not finite", (long long)q);
@@ -2324,6 +2326,7 @@ int rcp_set_optimizer(rcp_ctx *c, int k, const double *m, const double *v,
     HIPCHK(hipMemcpyAsync(c->d_state + k, &st, sizeof st, hipMemcpyHostToDevice, c->stream));
     HIPCHK(hipStreamSynchronize(c->stream));
     c->h_state[k] = st;
+    s.begin_count(st.iters);
     return RCP_OK;
 }
 
@@ -2456,6 +2459,7 @@ static int start_schedule(rcp_ctx *c, const rcp_schedule *sched, int per_packing
         parked = parked || s.parked;
         s.parked = false;
         s.err = 0;
+        s.begin_count(0);
     }
     if (parked) CHK(build_work(c));
     int64_t nmax = 0;

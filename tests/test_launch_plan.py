@@ -1,6 +1,6 @@
 """The host arithmetic of the launches (csrc/launch_plan.hpp), compiled on its
-own with the host compiler: the cut of the rows into work items, and what runs
-an iteration's tail."""
+own with the host compiler: the cut of the rows into work items, what runs an
+iteration's tail, and how many iterations are launched in a row."""
 import ctypes as C
 import os
 import subprocess
@@ -21,6 +21,12 @@ int units_row(const rcp_tuning *t) { return row_units(*t); }
 int units_item(const rcp_tuning *t, int waves, int64_t n, int64_t e) { return item_units(*t, waves, n, e); }
 int rows_max(const rcp_tuning *t, int waves) { return item_rows_max(*t, waves); }
 int64_t slots(const rcp_tuning *t, int waves, int64_t n, int64_t e) { return item_slots(*t, waves, n, e); }
+int64_t ahead(int64_t iters, int64_t since_it, int64_t interval, double disp2, double lim,
+              int64_t to_limit, int64_t to_end, int64_t K)
+{
+    return iterations_ahead({iters, since_it, interval, disp2, lim, to_limit, to_end}, K);
+}
+int64_t left(const int64_t *budget, int n, int rung, int64_t done) { return schedule_left(budget, n, rung, done); }
 int fused(const rcp_tuning *t, int waves) { return fuses_tail(*t, waves); }
 }
 """
@@ -35,7 +41,10 @@ def plan(tmp_path_factory):
     subprocess.run(["g++", "-std=c++17", "-O1", "-Wall", "-Werror", "-shared", "-fPIC", "-I", CSRC,
                     "-I", os.path.join(ROOT, "include"), src, "-o", lib], check=True)
     L = C.CDLL(lib)
-    L.slots.restype = C.c_int64
+    L.slots.restype = L.ahead.restype = L.left.restype = C.c_int64
+    i64 = C.c_int64
+    L.ahead.argtypes = [i64, i64, i64, C.c_double, C.c_double, i64, i64, i64]
+    L.left.argtypes = [C.POINTER(i64), C.c_int, C.c_int, i64]
     L.slots.argtypes = L.units_item.argtypes = [C.c_void_p, C.c_int, C.c_int64, C.c_int64]
     return L
 
@@ -91,3 +100,27 @@ def test_every_iteration_has_a_tail(plan):
         assert plan.fused(C.byref(t), 1) == 0
         t.fused_tail = 0
         assert plan.fused(C.byref(t), 0) == 0
+
+
+def test_launches_end_with_the_schedule(plan):
+    # a known interval of 400, fresh list: what is left of it, unless a limit
+    # or the schedule's end comes first
+    far = 1 << 62
+    assert plan.ahead(1000, 1000, 400, 0.0, 1.0, far, far, 32) == 400
+    assert plan.ahead(1150, 1000, 400, 0.0, 1.0, far, far, 32) == 250
+    assert plan.ahead(1150, 1000, 400, 0.0, 1.0, 100, far, 32) == 100
+    assert plan.ahead(0, 0, 400, 0.0, 1.0, far, 1, 32) == 1
+    assert plan.ahead(0, 0, 0, 0.0, 1.0, far, 5, 32) == 5
+    # a build that the schedule's count knows nothing of adds nothing
+    assert plan.ahead(0, 900, 400, 0.0, 1.0, far, far, 32) == 400
+    # no interval yet: the displacement so far, at most twice as many again
+    assert plan.ahead(40, 0, 0, 0.25, 1.0, far, far, 32) == 40
+    assert plan.ahead(40, 0, 0, 1e-6, 1.0, far, far, 32) == 80
+    assert plan.ahead(40, 0, 0, 4.0, 1.0, far, far, 32) == 0
+
+
+def test_what_is_left_of_a_schedule(plan):
+    b = (C.c_int64 * 4)(10, 20, 1 << 62, 1 << 62)
+    assert plan.left(b, 1, 0, 0) == 10 and plan.left(b, 2, 0, 3) == 27 and plan.left(b, 2, 1, 3) == 17
+    assert plan.left(b, 1, 0, 25) == 0 and plan.left(b, 0, 0, 0) == 0
+    assert plan.left(b, 4, 0, 7) == (1 << 62) - 7 == plan.left(b, 4, 2, 7)
