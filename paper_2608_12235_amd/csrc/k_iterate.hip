@@ -79,7 +79,7 @@ __device__ __forceinline__ double fast_rsq(double x)
 
 // Squared distances below this use the IEEE root (the estimates lose range
 // near the bottom of the exponent range).
-constexpr double kTinyR2 = 1e-200;
+constexpr double kTinyR2 = 1e-200, kTinyV = 1e-200;
 // Overlaps shallower than this take the definition's own rounding (below).
 constexpr double kShallow = 0x1p-10;
 // Pairs with r^2 below d^2 (1 + 2^-50) are examined: every pair whose
@@ -159,30 +159,6 @@ __device__ __forceinline__ void pair_term(Acc &a, const P4 &qi, const P4 &qj, do
     }
 }
 
-// Adam on one coordinate (Kingma and Ba, bias corrected; ib1 = 1 / (1 -
-// beta1^t), ib2 = 1 / (1 - beta2^t)), then wrapped into [0, L) (L = 0 on an
-// axis bounded by walls leaves the coordinate as it is).  The fused products
-// are written out, so that every kernel rounds a packing's step alike.
-__device__ __forceinline__ double adam_coord(double th, double g, double &m, double &v,
-                                             double b1, double b2, double ib1, double ib2,
-                                             double eta, double eps, double L)
-{
-#pragma clang fp contract(off)
-    m = fma(1.0 - b1, g, b1 * m);
-    v = fma(1.0 - b2, g * g, b2 * v);
-    const double mh = m * ib1, vh = v * ib2;
-    // sqrt(vh) as vh / sqrt(vh); below 1e-200, where the estimate loses range
-    // (0 among them: a sphere without contacts), of 2^600 vh
-    const bool tiny = vh < 1e-200;
-    const double vs = tiny ? vh * 0x1p600 : vh;
-    const double y = vs * fast_rsq(fmax(vs, 1e-300));
-    const double sv = tiny ? y * 0x1p-300 : y;
-    double t = fma(-(eta * mh), fast_rcp(sv + eps), th);
-    if (t < 0.0) t += L;
-    if (t >= L) t -= L;
-    return t;
-}
-
 struct IterScalars {
     double kappa, L, hL, iL, b1, b2, ib1, ib2, eta, eps;
     // per axis: 1 / L and the wrap period L, both 0 on an axis bounded by
@@ -224,21 +200,6 @@ __device__ __forceinline__ IterPtrs select_ptrs(const SegPtrs *__restrict__ P, i
     return p;
 }
 
-// One coordinate's Adam update from preloaded operands; returns the new
-// coordinate and adds its squared (minimum image) displacement from the
-// list reference to d2.
-__device__ __forceinline__ double update_coord(double xi, double g, double m, double v, double r,
-                                               double *mm, double *vv, const IterScalars &c,
-                                               int64_t i, double &d2, double period)
-{
-    const double xn = adam_coord(xi, g, m, v, c.b1, c.b2, c.ib1, c.ib2, c.eta, c.eps, period);
-    gstore(mm, i, m);
-    gstore(vv, i, v);
-    const double dd = min_image(xn - r, c.L, c.hL);
-    d2 += dd * dd;
-    return xn;
-}
-
 struct Pre {
     double m0, m1, m2, v0, v1, v2;
     float r0, r1, r2;
@@ -262,6 +223,53 @@ __device__ __forceinline__ Pre preload(const IterPtrs &p, int64_t i)
     return q;
 }
 
+// Adam on one sphere's coordinates (Kingma and Ba, bias corrected; ib1 = 1 /
+// (1 - beta1^t), ib2 = 1 / (1 - beta2^t)): the moments m and v with the
+// gradient g, the corrected first one and the root of the corrected second.
+// The fused products are written out, so that every kernel rounds a packing's
+// step alike.
+template <int kDim>
+__device__ __forceinline__ void adam_moments(const double (&g)[3], double (&m)[3], double (&v)[3],
+                                             double (&mh)[3], double (&sv)[3], const IterScalars &c)
+{
+#pragma clang fp contract(off)
+    bool rare = false;
+#pragma unroll
+    for (int a = 0; a < kDim; ++a) {
+        m[a] = fma(1.0 - c.b1, g[a], c.b1 * m[a]);
+        v[a] = fma(1.0 - c.b2, g[a] * g[a], c.b2 * v[a]);
+        mh[a] = m[a] * c.ib1;
+        const double vh = v[a] * c.ib2;
+        // sqrt(vh) as vh / sqrt(vh)
+        sv[a] = vh * fast_rsq(fmax(vh, kTinyV));
+        rare = rare || (vh < kTinyV && vh > 0.0);
+    }
+    // below kTinyV, where the estimate loses range, the IEEE root; 0 (a sphere
+    // without contacts) needs none.  One branch for all coordinates: with one
+    // each, 3e6 spheres took 4.7 us a launch more (of 131).
+    if (__builtin_expect(rare, 0)) {
+#pragma unroll
+        for (int a = 0; a < kDim; ++a) {
+            double w = v[a];
+            asm("" : "+v"(w));   // (formed again: kept, it costs registers)
+            const double vh = w * c.ib2;
+            if (vh < kTinyV) sv[a] = sqrt(vh);
+        }
+    }
+}
+
+// The step of one coordinate, wrapped into [0, L) (L = 0 on an axis bounded by
+// walls leaves the coordinate as it is).
+__device__ __forceinline__ double adam_move(double th, double mh, double sv, double eta, double eps,
+                                            double L)
+{
+#pragma clang fp contract(off)
+    double t = fma(-(eta * mh), fast_rcp(sv + eps), th);
+    if (t < 0.0) t += L;
+    if (t >= L) t -= L;
+    return t;
+}
+
 // Adam on particle i's coordinates, new position stored (the three
 // coordinates: the record's D0 in the output buffer is already in place,
 // written when the list order was set; with `full` the whole record);
@@ -278,11 +286,23 @@ __device__ __forceinline__ double update_particle(const IterPtrs &p, const IterS
         return 0.0;
     }
     double d2 = 0.0;
+    double m[3] = {q.m0, q.m1, q.m2}, v[3] = {q.v0, q.v1, q.v2}, mh[3], sv[3];
+    const double g[3] = {gx, gy, gz}, x[3] = {qi.x, qi.y, qi.z}, r[3] = {q.r0, q.r1, q.r2};
+    double *const mm[3] = {p.m0, p.m1, p.m2}, *const vv[3] = {p.v0, p.v1, p.v2};
+    adam_moments<kDim>(g, m, v, mh, sv, c);
+    double xn[3] = {0.0, 0.0, qi.z};
+#pragma unroll
+    for (int a = 0; a < kDim; ++a) {
+        xn[a] = adam_move(x[a], mh[a], sv[a], c.eta, c.eps, c.Pa[a]);
+        gstore(mm[a], i, m[a]);
+        gstore(vv[a], i, v[a]);
+        const double dd = min_image(xn[a] - r[a], c.L, c.hL);
+        d2 += dd * dd;
+    }
     P4 o;
-    o.x = update_coord(qi.x, gx, q.m0, q.v0, q.r0, p.m0, p.v0, c, i, d2, c.Pa[0]);
-    o.y = update_coord(qi.y, gy, q.m1, q.v1, q.r1, p.m1, p.v1, c, i, d2, c.Pa[1]);
-    o.z = kDim == 3 ? update_coord(qi.z, gz, q.m2, q.v2, q.r2, p.m2, p.v2, c, i, d2, c.Pa[2])
-                    : qi.z;
+    o.x = xn[0];
+    o.y = xn[1];
+    o.z = xn[2];
     o.d = qi.d;
     if (full) store_p4(p.qo, (int32_t)i, o);
     else store_xyz(p.qo, (int32_t)i, o.x, o.y, o.z);
