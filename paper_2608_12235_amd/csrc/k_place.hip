@@ -328,7 +328,9 @@ __global__ __launch_bounds__(kBlock) void k_seat(SeatArgs a, int64_t ng)
     const int32_t i = a.gidx[t];
     const double di = a.gd[t];
     const int64_t nc = a.nc;
-    const int64_t lo3 = nc >= 3 ? -1 : 0, hi3 = nc >= 3 ? 1 : nc - 1;
+    // fewer than three cells per axis: every cell once
+    const bool wrap = nc >= 3;
+    const int64_t m = wrap ? 3 : nc;
     for (int64_t att = 0; att < a.max_attempts; ++att) {
         double p[3];
         for (int ax = 0; ax < 3; ++ax) {
@@ -339,11 +341,12 @@ __global__ __launch_bounds__(kBlock) void k_seat(SeatArgs a, int64_t ng)
         const int64_t cx = place_cell(p[0], a.inv_w, nc), cy = place_cell(p[1], a.inv_w, nc),
                       cz = place_cell(p[2], a.inv_w, nc);
         bool ok = true;
-        for (int64_t ox = lo3; ox <= hi3 && ok; ++ox)
-            for (int64_t oy = lo3; oy <= hi3 && ok; ++oy)
-                for (int64_t oz = lo3; oz <= hi3 && ok; ++oz) {
-                    int64_t ax = cx + ox, ay = cy + oy, az = cz + oz;
-                    if (nc >= 3) {
+        for (int64_t ox = 0; ox < m && ok; ++ox)
+            for (int64_t oy = 0; oy < m && ok; ++oy)
+                for (int64_t oz = 0; oz < m && ok; ++oz) {
+                    int64_t ax = ox, ay = oy, az = oz;
+                    if (wrap) {
+                        ax += cx - 1, ay += cy - 1, az += cz - 1;
                         ax = ax < 0 ? ax + nc : (ax >= nc ? ax - nc : ax);
                         ay = ay < 0 ? ay + nc : (ay >= nc ? ay - nc : ay);
                         az = az < 0 ? az + nc : (az >= nc ? az - nc : az);
