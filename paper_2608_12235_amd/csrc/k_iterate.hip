@@ -1629,14 +1629,15 @@ void launch_tail(const SegState *S, SegState *So, const double *partials, int ns
 __global__ __launch_bounds__(kBlock) void k_start(const SegPtrs *__restrict__ P,
                                                  SegState *__restrict__ S, SchedDev q0,
                                                  const SchedDev *__restrict__ qs, int reset_adam,
-                                                 int32_t set_flags, int64_t iter_limit)
+                                                 int32_t set_flags, int64_t iter_limit, int per)
 {
-    const int seg = (int)blockIdx.y;
+    // (`per` blocks a packing)
+    const int seg = (int)(blockIdx.x / (unsigned)per), b = (int)(blockIdx.x % (unsigned)per);
     SegState *s = S + seg;
     if (reset_adam) {
         const SegPtrs &p = P[seg];
-        const int64_t n = s->n, step = (int64_t)gridDim.x * kBlock;
-        for (int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x; i < n; i += step) {
+        const int64_t n = s->n, step = (int64_t)per * kBlock;
+        for (int64_t i = (int64_t)b * kBlock + threadIdx.x; i < n; i += step) {
 #pragma unroll
             for (int a = 0; a < 3; ++a) {
                 gstore(p.m[a], i, 0.0);
@@ -1644,7 +1645,7 @@ __global__ __launch_bounds__(kBlock) void k_start(const SegPtrs *__restrict__ P,
             }
         }
     }
-    if (blockIdx.x != 0 || threadIdx.x != 0) return;
+    if (b != 0 || threadIdx.x != 0) return;
     s->sched = qs ? qs[seg] : q0;
     s->rung = 0;
     s->it_rung = 0;
@@ -1667,10 +1668,9 @@ void launch_start(const SegPtrs *P, SegState *S, int nseg, int64_t nmax, const S
                   hipStream_t st)
 {
     if (nseg <= 0) return;
-    const int64_t want = (nmax + kBlock - 1) / kBlock, most = std::max(1, 8192 / nseg);
-    const unsigned gx = reset_adam ? (unsigned)std::max<int64_t>(1, std::min(want, most)) : 1u;
-    hipLaunchKernelGGL(k_start, dim3(gx, nseg), dim3(kBlock), 0, st, P, S, q0, qs, reset_adam,
-                       set_flags, iter_limit);
+    const int per = reset_adam ? (int)blocks_per_packing(nseg, nmax) : 1;
+    hipLaunchKernelGGL(k_start, dim3((unsigned)nseg * (unsigned)per), dim3(kBlock), 0, st, P, S, q0,
+                       qs, reset_adam, set_flags, iter_limit, per);
 }
 
 __global__ void k_set_flags(SegState *S, int seg, int32_t clear, int32_t set)

@@ -341,9 +341,10 @@ int radix_sort_segs(const SortSeg *sg, int nseg, int64_t ntiles, int64_t most_ti
         if (mode != kSingle)
             hipLaunchKernelGGL(k_radix_hist, dim3((unsigned)ntiles), dim3(kBlock), 0, s, sg, nseg,
                                par, shift, bits, mode == kFew ? 1 : 0, hist);
-        if (mode == kScanned)
-            hipLaunchKernelGGL(k_radix_rowscan, dim3((unsigned)nseg << bits), dim3(kBlock), 0, s,
-                               sg, bits, hist, totals);
+        const int64_t some = packings_per_scan(bits);
+        for (int64_t j = 0; mode == kScanned && j < nseg; j += some)
+            hipLaunchKernelGGL(k_radix_rowscan, dim3((unsigned)std::min(some, nseg - j) << bits),
+                               dim3(kBlock), 0, s, sg + j, bits, hist, totals + (j << bits));
         if (vals)
             launch_scatter<true>(mode, ntiles, s, sg, nseg, par, shift, bits, hist, totals);
         else

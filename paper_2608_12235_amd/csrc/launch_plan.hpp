@@ -1,6 +1,7 @@
 // Host arithmetic of the launches, free of HIP so that it can be compiled and
 // checked on its own: the cut of a packing's rows into work items, what runs an
-// iteration's tail, and how many iterations are launched in a row.
+// iteration's tail, how many iterations are launched in a row, and grids that
+// grow with the number of packings.
 #pragma once
 #include "rcp.h"
 
@@ -114,5 +115,20 @@ inline int64_t schedule_left(const int64_t *budget, int n_rungs, int rung, int64
     for (int r = rung; r < n_rungs; ++r) left = budget[r] < most - left ? left + budget[r] : most;
     return std::max<int64_t>(0, left - done);
 }
+
+// Blocks of kBlock threads a launch takes along x (fewer than 2^32 threads);
+// along y and z it takes 65535, so the packings of a census lie along x.
+constexpr int64_t kGridBlocks = (((int64_t)1 << 32) - 1) / kBlock;
+
+// Blocks per packing for a pass over nseg packings of up to nmax spheres: about
+// 8192 in all.
+inline int64_t blocks_per_packing(int64_t nseg, int64_t nmax)
+{
+    const int64_t most = std::max<int64_t>(1, 8192 / nseg);
+    return std::max<int64_t>(1, std::min((nmax + kBlock - 1) / kBlock, most));
+}
+
+// Packings a launch takes with a block for each digit of `bits` bits.
+inline int64_t packings_per_scan(int bits) { return kGridBlocks >> bits; }
 
 }  // namespace rcp

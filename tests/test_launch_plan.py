@@ -1,6 +1,7 @@
 """The host arithmetic of the launches (csrc/launch_plan.hpp), compiled on its
 own with the host compiler: the cut of the rows into work items, what runs an
-iteration's tail, and how many iterations are launched in a row."""
+iteration's tail, how many iterations are launched in a row, and grids that grow
+with the number of packings."""
 import ctypes as C
 import os
 import subprocess
@@ -27,6 +28,8 @@ int64_t ahead(int64_t iters, int64_t since_it, int64_t interval, double disp2, d
     return iterations_ahead({iters, since_it, interval, disp2, lim, to_limit, to_end}, K);
 }
 int64_t left(const int64_t *budget, int n, int rung, int64_t done) { return schedule_left(budget, n, rung, done); }
+int64_t per_packing(int64_t nseg, int64_t nmax) { return blocks_per_packing(nseg, nmax); }
+int64_t per_scan(int bits) { return packings_per_scan(bits); }
 int fused(const rcp_tuning *t, int waves) { return fuses_tail(*t, waves); }
 }
 """
@@ -41,6 +44,8 @@ def plan(tmp_path_factory):
     subprocess.run(["g++", "-std=c++17", "-O1", "-Wall", "-Werror", "-shared", "-fPIC", "-I", CSRC,
                     "-I", os.path.join(ROOT, "include"), src, "-o", lib], check=True)
     L = C.CDLL(lib)
+    L.per_packing.restype = L.per_scan.restype = C.c_int64
+    L.per_packing.argtypes = [C.c_int64, C.c_int64]
     L.slots.restype = L.ahead.restype = L.left.restype = C.c_int64
     i64 = C.c_int64
     L.ahead.argtypes = [i64, i64, i64, C.c_double, C.c_double, i64, i64, i64]
@@ -124,3 +129,16 @@ def test_what_is_left_of_a_schedule(plan):
     assert plan.left(b, 1, 0, 0) == 10 and plan.left(b, 2, 0, 3) == 27 and plan.left(b, 2, 1, 3) == 17
     assert plan.left(b, 1, 0, 25) == 0 and plan.left(b, 0, 0, 0) == 0
     assert plan.left(b, 4, 0, 7) == (1 << 62) - 7 == plan.left(b, 4, 2, 7)
+
+
+def test_grids_of_many_packings(plan):
+    # a launch takes fewer than 2^32 threads along x; 65535 blocks, no more,
+    # along y, where a census of 65536 packings would not fit
+    for nseg in (1, 2, 16, 8191, 8193, 65535, 65536, 1 << 20):
+        for nmax in (1, 256, 257, 100000, 1 << 24):
+            per = plan.per_packing(nseg, nmax)
+            assert 1 <= per <= max(1, (nmax + 255) // 256)
+            assert nseg * per <= max(nseg, 8192) and nseg * per * 256 < 1 << 32
+    for bits in range(1, 10):
+        assert plan.per_scan(bits) >= 32767
+        assert (plan.per_scan(bits) << bits) * 256 < 1 << 32
