@@ -131,8 +131,9 @@ typedef struct {
  *     spheres or large ones; the kernels that variant bits 0-5 and fused_tail
  *     select take a block's four items as one; 1 <=
  *     row_cost <= 65536 and 1 <= item_work <= R * row_cost, R = 512 with
- *     variant bit 5 and 256 otherwise (an item then never holds more than R
- *     rows). */
+ *     variant bit 5 and 256 otherwise (a block's four items then never hold
+ *     more than R rows).  A wave that takes an item on its own needs 64 rows
+ *     or fewer: evaluations cut items of their own where R is 512. */
 typedef struct {
     uint32_t size;
     int32_t graph_iters;
@@ -304,7 +305,7 @@ int rcp_place_device(rcp_ctx *ctx, int k, uint64_t seed, int64_t window, int64_t
  * result reports kappa and phi as they are (the release that follows, a
  * new context with every sphere free, ends with the shrink).  mask = NULL
  * (or all zero) frees every sphere.  While any packing of the context has
- * frozen spheres, the iteration uses the two-gather kernel whatever the
+ * frozen spheres, the iteration uses the wave-per-item kernel whatever the
  * tuning variant, and the tail is not fused.  RCP_EINVAL when every sphere
  * would be frozen, or when the packing has walls (rcp_set_boundary). */
 int rcp_set_frozen(rcp_ctx *ctx, int k, const uint8_t *mask);
@@ -334,7 +335,7 @@ int rcp_set_frozen(rcp_ctx *ctx, int k, const uint8_t *mask);
  * RCP_INIT_NONE, set the boundary, then place with rcp_place_device or set
  * positions with rcp_set_state.  The list is rebuilt before the next
  * evaluation.  While any packing has walls, the iteration uses the
- * two-gather kernel whatever the tuning variant, and the tail is not
+ * wave-per-item kernel whatever the tuning variant, and the tail is not
  * fused.  walls = round = 0 is the periodic box.  RCP_EINVAL for an axis
  * beyond dim, an axis in both masks, a round container of one axis, or a
  * packing with frozen spheres (walls and frozen spheres are not

@@ -914,8 +914,9 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(kWaves))
 // size ratio 5e5, 17.8 against 13.8 us on 1e5 spheres with 5.2 partners,
 // 15.5 against 9.2 us on 8784 with rows up to 284, 15.3 against 10.3 us on
 // 1e5 disks.  Registers matter: at 75 (six waves per SIMD) 128 us on 3e6
-// spheres, at 62-70 (seven) 122-126; loading the moments before the
-// partner loop (+15 registers) takes 47 us on 1e6.
+// spheres, at 62-72 (seven) 122-126; loading the moments before the
+// partner loop (+15 registers) takes 47 us on 1e6.  A row a lane: items of at
+// most kWave rows, which the host sees to (item_rows_max).
 struct WaveLds {
     P4 own[kWave];
     double F[3][kWave];
