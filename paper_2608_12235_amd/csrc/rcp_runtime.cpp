@@ -397,12 +397,14 @@ static void fill_items(rcp_ctx *c, int k, hipStream_t st)
 }
 
 // Lay out the work-item slots of all packings (a graph captured before is
-// invalid afterwards) and fill them.
+// invalid afterwards) and fill them.  On failure the table stays as it was.
 static int build_work(rcp_ctx *c)
 {
+    const int ns = (int)c->segs.size();
+    std::vector<int> blocks(ns);
     int64_t total = 0;
-    for (size_t k = 0; k < c->segs.size(); ++k) {
-        Seg &s = c->segs[k];
+    for (int k = 0; k < ns; ++k) {
+        const Seg &s = c->segs[k];
         // room for slot_entries, and for the list there is: under the cut it
         // was laid out for, a table may hold a few entries more than that
         const int64_t entries = s.built ? std::max(s.slot_entries, s.nnz) : s.slot_entries;
@@ -410,22 +412,32 @@ static int build_work(rcp_ctx *c)
         const int64_t nb = s.parked ? 0 : slots_for(c, s.n, entries) / kWavesPerBlock;
         if (nb > (int64_t)INT32_MAX / 4 || total + nb > (int64_t)INT32_MAX / 4)
             return fail(RCP_ENOMEM, "work table too large");
-        s.blocks = (int)nb;
-        s.first_item = total;
+        blocks[k] = (int)nb;
         total += nb;
     }
     if (total > c->items_cap) {
+        WorkItem *work = nullptr;
+        double *partials = nullptr;
+        CHK(dalloc(&work, (size_t)total * kWavesPerBlock));
+        const int rc = dalloc(&partials, 2 * 4 * (size_t)total);
+        if (rc != RCP_OK) {
+            dfree(work);
+            return rc;
+        }
         dfree(c->d_work);
         dfree(c->d_partials);
-        c->d_work = nullptr;
-        c->d_partials = nullptr;
-        CHK(dalloc(&c->d_work, (size_t)total * kWavesPerBlock));
-        CHK(dalloc(&c->d_partials, 2 * 4 * (size_t)total));
+        c->d_work = work;
+        c->d_partials = partials;
         c->items_cap = total;
+    }
+    int64_t first = 0;
+    for (int k = 0; k < ns; ++k) {
+        c->segs[k].blocks = blocks[k];
+        c->segs[k].first_item = first;
+        first += blocks[k];
     }
     c->nitems = (int)total;
     c->item_rows = item_rows_max(c->tuning, waves_only(c));
-    const int ns = (int)c->segs.size();
     for (int k = 0; k < ns; ++k) {
         c->h_layout[2 * k] = c->segs[k].blocks;
         c->h_layout[2 * k + 1] = c->segs[k].first_item;
@@ -1931,10 +1943,12 @@ int rcp_set_tuning(rcp_ctx *c, const rcp_tuning *t)
     if (t->time_kernels < 0 || t->time_kernels > 2) return fail(RCP_EINVAL, "bad tuning values");
     CHK(after_dev(c, c->stream));
     const bool relayout = t->row_cost != c->tuning.row_cost || t->item_work != c->tuning.item_work;
+    const rcp_tuning before = c->tuning;
     c->tuning = *t;
     c->graph_valid = false;
-    if (relayout && !c->segs.empty()) CHK(build_work(c));
-    return RCP_OK;
+    const int rc = relayout && !c->segs.empty() ? build_work(c) : RCP_OK;
+    if (rc != RCP_OK) c->tuning = before;
+    return rc;
 }
 
 static int check_k(rcp_ctx *c, int k)
@@ -2454,14 +2468,21 @@ static int start_schedule(rcp_ctx *c, const rcp_schedule *sched, int per_packing
     std::vector<SchedDev> qs(ns);
     for (int k = 0; k < ns; ++k) CHK(to_sched(per_packing ? sched + k : sched, qs[k]));
     // every packing runs again: packings parked by an earlier run get slots
-    bool parked = false;
-    for (auto &s : c->segs) {
-        parked = parked || s.parked;
+    std::vector<int> parked;
+    for (int k = 0; k < ns; ++k) {
+        Seg &s = c->segs[k];
+        if (s.parked) parked.push_back(k);
         s.parked = false;
         s.err = 0;
         s.begin_count(0);
     }
-    if (parked) CHK(build_work(c));
+    if (!parked.empty()) {
+        const int rc = build_work(c);
+        if (rc != RCP_OK) {
+            for (int k : parked) c->segs[k].parked = true;
+            return rc;
+        }
+    }
     int64_t nmax = 0;
     for (const auto &s : c->segs) nmax = std::max(nmax, s.n);
     if (ns > 1) {
