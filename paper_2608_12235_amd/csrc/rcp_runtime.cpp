@@ -890,6 +890,30 @@ static int check_list_size(int k, int64_t m)
     return RCP_OK;
 }
 
+__global__ void k_drop_list(SegPtrs *P, SegState *S, int seg, SegPtrs p, int cur)
+{
+    P[seg] = p;
+    S[seg].cur = cur;
+    S[seg].flags |= F_STALE;
+}
+
+// The packings of a batch whose build failed after its front half: their
+// arrays are in the new order already, in the other set, and it is that set
+// that counts from here on; they have no list.
+static void drop_lists(rcp_ctx *c, const std::vector<BuildJob> &jobs)
+{
+    for (const BuildJob &j : jobs) {
+        Seg &s = c->segs[j.k];
+        SegPtrs p;
+        ptrs_of(s, p);
+        hipLaunchKernelGGL(k_drop_list, dim3(1), dim3(1), 0, c->stream, c->d_ptrs, c->d_state, j.k,
+                           p, s.cur);
+        s.built = false;
+    }
+}
+
+static int build_lists(rcp_ctx *c, std::vector<BuildJob> &jobs, int nl);
+
 // Build the lists of packings ks[i] at kb = kappas[i], sharing one host
 // round trip.  rcs[i] receives each packing's status (RCP_EBOX leaves that
 // packing untouched); the return value is the first error that is not a
@@ -929,6 +953,20 @@ static int rebuild_batch(rcp_ctx *c, const std::vector<int> &ks, const std::vect
     std::pair<hipEvent_t, hipEvent_t> ev;
     CHK(rebuild_events(c, ev));
     HIPCHK(hipEventRecord(ev.first, c->stream));
+    const int rc = build_lists(c, jobs, nl);
+    if (rc != RCP_OK) {
+        drop_lists(c, jobs);
+        c->rb_pool.push_back(ev);
+        return rc;
+    }
+    HIPCHK(hipEventRecord(ev.second, c->stream));
+    c->rb_pending.push_back(ev);
+    return RCP_OK;
+}
+
+// Both halves of a batch of planned builds.
+static int build_lists(rcp_ctx *c, std::vector<BuildJob> &jobs, int nl)
+{
     CHK(build_fronts(c, jobs, nl));
     CHK(join_lanes(c, nl));
     HIPCHK(hipMemcpyAsync(c->h_bcount, c->bcount, sizeof(unsigned long long) * jobs.size(),
@@ -970,8 +1008,6 @@ static int rebuild_batch(rcp_ctx *c, const std::vector<int> &ks, const std::vect
         CHK(grow_cols(c->segs[jobs[q].k], m1[0]));
         CHK(build_backs(c, one, std::vector<int>{0}, m1, &relayout));
     }
-    HIPCHK(hipEventRecord(ev.second, c->stream));
-    c->rb_pending.push_back(ev);
     if (relayout) CHK(build_work(c));
     return RCP_OK;
 }
