@@ -506,7 +506,9 @@ int rcp_shrink(rcp_ctx *ctx, int k, double *kappa_shrunk, double *phi);
  * on it.  The list is rebuilt at (x_dev, kappa) if it is not valid there
  * (this synchronises the stream): packing 0 then takes x_dev and kappa as
  * its state, exactly as rcp_set_state would (its optimiser state is reset),
- * so a context used for evaluation should not also carry a run.
+ * so a context used for evaluation should not also carry a run.  Calls on
+ * different streams, and calls on the context's own stream after them, need
+ * not be waited for in between: each waits on the device for the one before.
  * rcp_energy_dev writes E = E_overlap + E_growth to E_dev[0] and max overlap
  * to E_dev[1].  rcp_adjoint_dev writes dE/dx (n, 3, user order) to gx_dev
  * and dE/dkappa to gk_dev[0]. */
